@@ -19,10 +19,10 @@
 //   5. with a fused output, the rounded values are expanded into one padded
 //      row in LDS and the strips are stored on the s_b output rows.
 // Mirror padding (Algorithm 2 step 4, Algorithm 3 step 3) is never
-// materialised: padded rows fold to a source row per row, and padded columns
-// fold per byte in the few strips that cross the right edge (which become
-// one-row items so their byte loads overlap).  The unpadded mode (Algorithm
-// 1) skips those rows and columns and divides by real pixel counts.
+// materialised: padded rows fold to a source row per row, and a padded
+// column's sums are copies of the sums of the column it mirrors, already in
+// LDS.  The unpadded mode (Algorithm 1) skips those rows and columns and
+// divides by real pixel counts.
 #include "dppix_internal.h"
 #include "dppix_tiles.h"
 
@@ -47,8 +47,13 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // 16-byte streaming accesses through global (not flat) address space: frame
 // pointers come from device tables, so the compiler cannot infer the address
 // space, and flat accesses would make every wait cover LDS traffic as well.
-typedef __attribute__((address_space(1))) v4u g_v4u;
-typedef __attribute__((address_space(1))) v4f g_v4f;
+// Rows start at any byte (any float): global vector accesses need no more
+// than that, and a row of 16-byte strips off the line grid costs one more line
+// per wave, where single bytes would cost sixteen times the accesses.
+typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef __attribute__((address_space(1))) v4u_any g_v4u;
+typedef __attribute__((address_space(1))) v4f_any g_v4f;
 typedef __attribute__((address_space(1))) const uint8_t g_u8;
 typedef __attribute__((address_space(1))) uint8_t g_u8w;
 typedef __attribute__((address_space(1))) uint16_t g_u16w;
@@ -251,6 +256,17 @@ __device__ __forceinline__ uint32_t nz_bytes(uint32_t w)
 // subgrid row has at most 256 rows of bytes, so 255 * 256 fits).
 __device__ __forceinline__ void store_colsums16(uint16_t* dst, const uint32_t (&e)[4], const uint32_t (&o)[4])
 {
+    if ((reinterpret_cast<uintptr_t>(dst) & 15) != 0) {
+        // the last strip of a tile's real columns, moved back to end with them
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            dst[4 * d] = (uint16_t)e[d];
+            dst[4 * d + 1] = (uint16_t)o[d];
+            dst[4 * d + 2] = (uint16_t)(e[d] >> 16);
+            dst[4 * d + 3] = (uint16_t)(o[d] >> 16);
+        }
+        return;
+    }
     v4u* d4 = reinterpret_cast<v4u*>(dst);
     d4[0] = v4u{(e[0] & 0xFFFFu) | (o[0] << 16), (e[0] >> 16) | (o[0] & 0xFFFF0000u),
                 (e[1] & 0xFFFFu) | (o[1] << 16), (e[1] >> 16) | (o[1] & 0xFFFF0000u)};
@@ -258,35 +274,47 @@ __device__ __forceinline__ void store_colsums16(uint16_t* dst, const uint32_t (&
                 (e[3] & 0xFFFFu) | (o[3] << 16), (e[3] >> 16) | (o[3] & 0xFFFF0000u)};
 }
 
-// Gather one 16-byte strip of a padded row byte by byte: columns past the
-// image fold back (mirror; zero in the unpadded mode), bytes past the tile
-// end read as zero.  Only the strips that cross the right edge or a
-// misaligned row take this path.
-template <int C>
-__device__ __noinline__ v4u gather_strip_u8(const uint8_t* row, int p0, int tile_end, int W, int pad)
+// How a tile's rows are cut into strips of `unit` elements (16 bytes, or 4
+// floats): `real` elements of the tile's padded width lie in the frame.  With
+// `vec` every real element is read by a whole vector (`nvec` strips, the last
+// one moved back to end with the real columns: the columns it shares with its
+// neighbour are written twice with equal sums), and the padded columns after
+// them are copies of column sums the tile already has (a column's mirror
+// image has its sum) or zero.  A tile of fewer real columns than one strip,
+// or than its padding mirrors, is read element by element instead.
+// 24 RGB photos of odd widths (22.9 MP, b 16 / s_b 4), before (strips off the
+// 16-byte grid and at the right edge gathered and stored byte by byte) and
+// after: forward 151 -> 46 us, reconstruction 89 -> 27 us, plan 53 -> 15 us;
+// 64 fp32 crops of 218 x 178: forward 40 -> 30 us.  Aligned batches unchanged.
+struct Strips {
+    int real, nvec;
+    bool vec;
+};
+
+__device__ __forceinline__ Strips tile_strips_of(int width, int real, int unit, int per_pixel, int pad)
 {
-    const g_u8* src = (const g_u8*)row;
-    // source offsets first (folding branches), then 16 unconditional byte
-    // loads issued back to back; bytes past the tile end are masked after
-    // (the unpadded mode reads columns past the frame as zero)
-    const int end = pad == kPadNone ? min(tile_end, W * C) : tile_end;
-    int idx[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int p = p0 + q;
-        const int x = p / C, ch = p - x * C;
-        idx[q] = p < end ? fold(x, W, pad) * C + ch : 0;
-    }
-    uint32_t v[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q)
-        v[q] = src[idx[q]];
-#pragma unroll
-    for (int q = 0; q < 16; ++q)
-        v[q] = p0 + q < end ? v[q] : 0u;
-    return v4u{v[0] | (v[1] << 8) | (v[2] << 16) | (v[3] << 24), v[4] | (v[5] << 8) | (v[6] << 16) | (v[7] << 24),
-               v[8] | (v[9] << 8) | (v[10] << 16) | (v[11] << 24),
-               v[12] | (v[13] << 8) | (v[14] << 16) | (v[15] << 24)};
+    Strips s;
+    s.real = real;
+    const int padded = (width - real) / per_pixel, px = real / per_pixel;
+    s.vec = real >= unit && (padded == 0 || pad == kPadNone || padded <= px - (pad == 1 ? 1 : 0));
+    s.nvec = (real + unit - 1) / unit;
+    return s;
+}
+
+// Tile-local source column of padded column x (both in pixels; px real ones).
+__device__ __forceinline__ int mirror_col(int x, int px, int pad) { return pad == 1 ? 2 * px - 2 - x : 2 * px - 1 - x; }
+
+// 16 bytes of LDS from any byte address.
+__device__ __forceinline__ v4u lds16(const uint8_t* p)
+{
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p);
+    if ((at & 15) == 0)
+        return *reinterpret_cast<const v4u*>(p);
+    const uint32_t sh = (uint32_t)(at & 3);
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(p - sh);
+    const uint32_t w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3], w4 = sh ? w[4] : 0u;
+    return v4u{__builtin_amdgcn_alignbyte(w1, w0, sh), __builtin_amdgcn_alignbyte(w2, w1, sh),
+               __builtin_amdgcn_alignbyte(w3, w2, sh), __builtin_amdgcn_alignbyte(w4, w3, sh)};
 }
 
 // Cell classes and class-local indices of the tile's cells (wave 0):
@@ -488,6 +516,17 @@ __device__ __forceinline__ void spread_strip(const uint32_t (&e)[4], const uint3
         atomicAdd(cc + cell, run);
 }
 
+// Clear the counts of a strip's columns outside [c0, c1).
+__device__ __forceinline__ void mask_cols(uint32_t (&e)[4], uint32_t (&o)[4], int c0, int c1)
+{
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int x = 4 * d;
+        e[d] &= (x >= c0 && x < c1 ? 0xFFFFu : 0u) | (x + 2 >= c0 && x + 2 < c1 ? 0xFFFF0000u : 0u);
+        o[d] &= (x + 1 >= c0 && x + 1 < c1 ? 0xFFFFu : 0u) | (x + 3 >= c0 && x + 3 < c1 ? 0xFFFF0000u : 0u);
+    }
+}
+
 // Mask counts of every cell of the unit into cellcnt[j * KCs + kc].
 __device__ void plan_count(const TileArgs& a, const FrameRec& F, const uint8_t* mask, int r0, int nb, int c0, int KC,
                            int KCs, uint32_t* cellcnt)
@@ -496,23 +535,34 @@ __device__ void plan_count(const TileArgs& a, const FrameRec& F, const uint8_t* 
     const int b = F.b, H = F.H, W = F.W, pad = F.pad;
     const int64_t X0 = (int64_t)c0 * b;
     const int WB = KC * b;
-    const int nstr = (WB + 15) >> 4;
     const int RI = min(b, kPlanRows);
     const int groups = (b + RI - 1) / RI;
     const int64_t lim = min(X0 + WB, (int64_t)W);
-    const bool aligned = ((reinterpret_cast<uintptr_t>(mask) | (uintptr_t)W | (uintptr_t)X0) & 15) == 0;
-    // strips [0, nfast) are whole 16-byte vectors inside the frame; the rest
-    // (right edge, or every strip of a misaligned mask) are gathered byte by
-    // byte, one padded row per item so that their latencies overlap
-    const int nfast = aligned ? (int)min((int64_t)nstr, (lim - X0) >> 4) : 0;
-    const int nslow = nstr - nfast;
-    const int per_band = nfast * groups;
+    // Strips [0, nfast) cover the unit's real columns, the last one moved back
+    // to end with them (the columns it shares with its neighbour masked off).
+    // The padded columns all lie in the frame's last cell (there are fewer
+    // than b of them), so their count is that of the columns they mirror,
+    // [ms, me): strips [nfast, nfast + nmir), added to that cell whole.
+    // Without whole vectors (fewer than 16 real columns, or than the padding
+    // mirrors) every column is counted byte by byte.
+    const int real = (int)(lim - X0);
+    const int padded = WB - real;
+    const bool vec = real >= 16 && (padded == 0 || pad == kPadNone || padded <= W - (pad == 1 ? 1 : 0));
+    const int nfast = vec ? (real + 15) >> 4 : 0;
+    const int me = pad == 1 ? W - 1 : W, ms = me - padded;
+    const int nmir = vec && pad != kPadNone ? (padded + 15) >> 4 : 0;
+    const int ncol = nfast + nmir;
+    const int per_band = ncol * groups;
     for (int item = tid; item < nb * per_band; item += NT) {
         const int j = item / per_band;
         const int rem = item - j * per_band;
-        const int g = rem / nfast;
-        const int st = rem - g * nfast;
-        const int64_t p0 = X0 + 16 * st;
+        const int g = rem / ncol;
+        const int st = rem - g * ncol;
+        const bool mir = st >= nfast;
+        // first column of the strip, and the columns [va, vb) it counts
+        const int va = mir ? ms + 16 * (st - nfast) : (int)X0 + 16 * st;
+        const int vb = min(va + 16, mir ? me : (int)lim);
+        const int64_t p0 = min(va, mir ? W - 16 : (int)lim - 16);
         const int row0 = (r0 + j) * b;
         const int k0 = g * RI, k1 = min(b, k0 + RI);
         uint32_t e[4] = {0, 0, 0, 0}, o[4] = {0, 0, 0, 0};
@@ -556,7 +606,16 @@ __device__ void plan_count(const TileArgs& a, const FrameRec& F, const uint8_t* 
                     acc_bytes(nz_strip(w[i]), e, o);
             }
         }
-        if ((b & 15) == 0) {
+        if (vb - va < 16 || va != p0)
+            mask_cols(e, o, va - (int)p0, vb - (int)p0);
+        if (mir) {
+            const uint32_t t = (e[0] + e[1] + e[2] + e[3]) + (o[0] + o[1] + o[2] + o[3]);
+            const uint32_t cnt = (t & 0xFFFFu) + (t >> 16);
+            if (cnt != 0u)
+                atomicAdd(cellcnt + j * KCs + KC - 1, cnt);
+        } else if (va != p0) {
+            spread_strip(e, o, cellcnt + j * KCs, KC, b, (int)(p0 - X0));
+        } else if ((b & 15) == 0) {
             // b a multiple of 16: the strip lies in one cell, one counter
             // update (a 16-bit half sums at most 8 columns of 16 rows)
             const uint32_t t = (e[0] + e[1] + e[2] + e[3]) + (o[0] + o[1] + o[2] + o[3]);
@@ -568,18 +627,19 @@ __device__ void plan_count(const TileArgs& a, const FrameRec& F, const uint8_t* 
             spread_strip(e, o, cellcnt + j * KCs, KC, b, 16 * st);
         }
     }
-    for (int item = tid; item < nb * b * nslow; item += NT) {
-        const int st = nfast + item % nslow;
-        const int rest = item / nslow;
-        const int k = rest % b, j = rest / b;
-        const int64_t p0 = X0 + 16 * st;
-        if ((r0 + j) * b + k >= H && pad == kPadNone)
-            continue;
-        uint32_t e[4] = {0, 0, 0, 0}, o[4] = {0, 0, 0, 0};
-        acc_bytes(nz_strip(gather_strip_u8<1>(mask + (int64_t)fold((r0 + j) * b + k, H, pad) * W, (int)p0,
-                                              (int)(X0 + WB), W, pad)),
-                  e, o);
-        spread_strip(e, o, cellcnt + j * KCs, KC, b, 16 * st);
+    if (!vec) {
+        for (int item = tid; item < nb * WB; item += NT) {
+            const int j = item / WB, p = item - j * WB;
+            const int x = (int)X0 + p;
+            const int row0 = (r0 + j) * b;
+            const int rows = pad == kPadNone ? (x < W ? min(b, H - row0) : 0) : b;
+            const g_u8* src = (const g_u8*)(mask + (pad == kPadNone ? x : fold(x, W, pad)));
+            uint32_t cnt = 0u;
+            for (int k = 0; k < rows; ++k)
+                cnt += src[(int64_t)fold(row0 + k, H, pad) * W] != 0;
+            if (cnt != 0u)
+                atomicAdd(cellcnt + j * KCs + p / b, cnt);
+        }
     }
 }
 
@@ -630,7 +690,8 @@ __device__ __forceinline__ void plan_unit(const TileArgs& a, uint8_t* lds, Count
     }
 }
 
-__global__ __launch_bounds__(kMaxThreads) void k_plan(TileArgs a)
+// Five waves per SIMD (96 VGPRs): the loads of more items in flight.
+__global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_plan(TileArgs a)
 {
     extern __shared__ __align__(16) uint8_t lds[];
     plan_unit(a, lds, [&](const FrameRec& F, int f, int r0, int nb, int c0, int KC, int KCs, uint32_t* cellcnt) {
@@ -1272,7 +1333,7 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
     const int64_t pitch = F.pitch;
     const uint8_t* img = static_cast<const uint8_t*>(a.images[tc.f]);
     uint8_t* out = a.outs ? static_cast<uint8_t*>(a.outs[tc.f]) : nullptr;
-    const bool in_aligned = ((reinterpret_cast<uintptr_t>(img) | (uintptr_t)pitch | (uintptr_t)X0) & 15) == 0;
+    const Strips sp = tile_strips_of(WB, (int)(lim - X0), 16, C, pad);
     // bands without vertical padding address rows by 32-bit offsets from the
     // band's first byte of the tile (uniform base, one offset register)
     const bool band_inside = F.off32 && (r + 1) * b <= H;
@@ -1307,19 +1368,8 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
         // Whole-vector strips ([0, nfast)): one item per (q subgrid rows,
         // strip); consecutive lanes read consecutive strips of a row and all
         // q * s_b rows of an item (8 or fewer) are loaded before they are
-        // added.  Other strips (right edge, misaligned rows): one padded row
-        // per item, added into the column sums with LDS atomics so that their
-        // latencies overlap.
-        const int nfast = in_aligned ? (int)min((int64_t)nstr, (lim - X0) >> 4) : 0;
-        const int nslow = nstr - nfast;
-        if (nslow > 0) {
-            uint32_t* c32 = reinterpret_cast<uint32_t*>(col16);
-            for (int i = tid; i < ng * nslow * 8; i += NT) {
-                const int g = i / (nslow * 8);
-                c32[(g * rowbuf + 16 * nfast) / 2 + (i - g * nslow * 8)] = 0u;
-            }
-            lds_barrier();
-        }
+        // added.
+        const int nfast = sp.vec ? sp.nvec : 0;
         const int q = band_inside ? rows_per_item(s) : 1;
         const int ngq = (ng + q - 1) / q;
         for (int it = tid; it < nfast * ngq; it += NT) {
@@ -1327,14 +1377,15 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
             const int st = it - gq * nfast;
             const int g0 = gq * q;
             const int qq = min(q, ng - g0);
-            uint16_t* dst = col16 + g0 * rowbuf + 16 * st;
+            const int po = min(16 * st, sp.real - 16);   // the last strip ends with the real columns
+            uint16_t* dst = col16 + g0 * rowbuf + po;
             if (!band_inside) {
                 // last band: padded rows fold back into the frame
-                strip_rows_fold(img + X0 + 16 * st, pitch, r * b + (fr0 + g0) * s, s, H, pad, dst);
+                strip_rows_fold(img + X0 + po, pitch, r * b + (fr0 + g0) * s, s, H, pad, dst);
                 continue;
             }
             // rows inside the frame: 32-bit offsets from the band's first row
-            const uint32_t off = (uint32_t)((fr0 + g0) * s) * upitch + 16u * (uint32_t)st;
+            const uint32_t off = (uint32_t)((fr0 + g0) * s) * upitch + (uint32_t)po;
             switch (q) {
             case 4: strip_rows_q<2>(band_in, off, upitch, qq, dst, rowbuf); break;
             case 2:
@@ -1346,30 +1397,33 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
             default: strip_rows_1(band_in, off, upitch, s, dst); break;
             }
         }
-        for (int it = tid; it < nslow * ng * s; it += NT) {
-            const int st = nfast + it % nslow;
-            const int rest = it / nslow;
-            const int k = rest % s, g = rest / s;
-            const int64_t p0 = X0 + 16 * st;
-            if (r * b + (fr0 + g) * s + k >= H && pad == kPadNone)
-                continue;
-            const uint8_t* rp = img + (int64_t)fold(r * b + (fr0 + g) * s + k, H, pad) * pitch;
-            const v4u v = (in_aligned && p0 + 16 <= lim) ? ld16_nt(rp + p0)
-                                                         : gather_strip_u8<C>(rp, (int)p0, (int)tile_end, W, pad);
-            // column pairs (2m, 2m+1) packed as in store_colsums16; a 16-bit
-            // half holds at most 255 * 256, so no carry crosses into the other
-            uint32_t* cw = reinterpret_cast<uint32_t*>(col16 + g * rowbuf + 16 * st);
-            atomicAdd(cw + 0, (v.x & 0xFFu) | ((v.x & 0xFF00u) << 8));
-            atomicAdd(cw + 1, ((v.x >> 16) & 0xFFu) | ((v.x >> 24) << 16));
-            atomicAdd(cw + 2, (v.y & 0xFFu) | ((v.y & 0xFF00u) << 8));
-            atomicAdd(cw + 3, ((v.y >> 16) & 0xFFu) | ((v.y >> 24) << 16));
-            atomicAdd(cw + 4, (v.z & 0xFFu) | ((v.z & 0xFF00u) << 8));
-            atomicAdd(cw + 5, ((v.z >> 16) & 0xFFu) | ((v.z >> 24) << 16));
-            atomicAdd(cw + 6, (v.w & 0xFFu) | ((v.w & 0xFF00u) << 8));
-            atomicAdd(cw + 7, ((v.w >> 16) & 0xFFu) | ((v.w >> 24) << 16));
+        if (!sp.vec) {
+            // a tile too narrow for vectors: one byte column per item
+            for (int it = tid; it < ng * WB; it += NT) {
+                const int g = it / WB, p = it - g * WB;
+                const int x = x0c * b + p / C;
+                const int sx = pad == kPadNone ? x : fold(x, W, pad);
+                const int row0 = r * b + (fr0 + g) * s;
+                const int rows = pad == kPadNone ? (x < W ? max(0, min(s, H - row0)) : 0) : s;
+                const g_u8* src = (const g_u8*)(img + (int64_t)sx * C + p % C);
+                uint32_t sum = 0u;
+                for (int k = 0; k < rows; ++k)
+                    sum += src[(int64_t)fold(row0 + k, H, pad) * pitch];
+                col16[g * rowbuf + p] = (uint16_t)sum;
+            }
         }
-        // classes and store indices of the tile's cells (wave 0), read while
-        // the row loads above are still in flight
+        if (sp.vec && sp.real < WB) {
+            // padded columns: the sums of the columns they mirror, or nothing
+            const int np = WB - sp.real;
+            if (pad != kPadNone)
+                lds_barrier();
+            for (int i = tid; i < ng * np; i += NT) {
+                const int g = i / np, p = sp.real + (i - g * np);
+                const int x = p / C, ch = p - x * C;
+                col16[g * rowbuf + p] =
+                    pad == kPadNone ? (uint16_t)0 : col16[g * rowbuf + mirror_col(x, sp.real / C, pad) * C + ch];
+            }
+        }
         lds_barrier();
         // running sums of every (subcell column, channel) for the coarse cells
         if ((s & 1) == 0) {
@@ -1458,7 +1512,7 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
     // The expanded row alternates between two LDS buffers, so one barrier per
     // subgrid row suffices: a buffer is rewritten two rows later, after every
     // lane has passed the barrier that follows its last read.
-    const bool out_aligned = ((reinterpret_cast<uintptr_t>(out) | (uintptr_t)pitch | (uintptr_t)X0) & 15) == 0;
+    const int real = sp.real;
     uint8_t* band_out = out + (int64_t)r * b * pitch + X0;
     for (int fr = 0; fr < n; ++fr) {
         uint8_t* exb = ex + (fr & 1) * (16 * nstr);
@@ -1473,26 +1527,27 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
         for (int it = tid; it < nstr * parts; it += NT) {
             const int part = it / nstr;
             const int st = it - part * nstr;
-            const int64_t p0 = X0 + 16 * st;
             const int k0 = part * per, k1 = min(rows, k0 + per);
-            if (p0 >= lim)
+            if (16 * st >= real)
                 continue;
-            const v4u v = *reinterpret_cast<const v4u*>(exb + 16 * st);
-            if (out_aligned && p0 + 16 <= lim) {
+            if (real >= 16) {
+                // the last strip ends with the real columns (the bytes it
+                // shares with its neighbour are written twice, alike)
+                const int po = min(16 * st, real - 16);
+                const v4u v = lds16(exb + po);
                 if (F.off32) {
-                    const uint32_t off = (uint32_t)(fr * s) * upitch + 16u * (uint32_t)st;
+                    const uint32_t off = (uint32_t)(fr * s) * upitch + (uint32_t)po;
                     for (int k = k0; k < k1; ++k)
                         st16_nt(band_out + (off + (uint32_t)k * upitch), v);
                 } else {
                     for (int k = k0; k < k1; ++k)
-                        st16_nt(out + (int64_t)(row0 + k) * pitch + p0, v);
+                        st16_nt(out + (int64_t)(row0 + k) * pitch + X0 + po, v);
                 }
             } else {
-                const uint8_t* vb = exb + 16 * st;
                 for (int k = k0; k < k1; ++k) {
-                    g_u8w* op = (g_u8w*)(out + (int64_t)(row0 + k) * pitch);
-                    for (int q = 0; q < 16 && p0 + q < lim; ++q)
-                        op[p0 + q] = vb[q];
+                    g_u8w* op = (g_u8w*)(out + (int64_t)(row0 + k) * pitch + X0);
+                    for (int q = 0; q < real; ++q)
+                        op[q] = exb[q];
                 }
             }
         }
@@ -1516,7 +1571,7 @@ __device__ void broadcast_tile_f32(const FrameRec& F, int r, int64_t X0, int64_t
     const int b = F.b, s = F.s, n = F.n, H = F.H, C = F.C;
     const int kn = Kt * n;
     const int64_t pitch = F.pitch, plane = pitch * H;
-    const bool out_aligned = ((reinterpret_cast<uintptr_t>(out) | (uintptr_t)(pitch * 4) | (uintptr_t)(X0 * 4)) & 15) == 0;
+    const int real = (int)(lim - X0);
     for (int ch = 0; ch < C; ++ch) {
         float* pl = out + plane * ch;
         for (int fr = 0; fr < n; ++fr) {
@@ -1531,23 +1586,38 @@ __device__ void broadcast_tile_f32(const FrameRec& F, int r, int64_t X0, int64_t
             const int row0 = r * b + fr * s;
             const int rows = min(s, H - row0);
             for (int st = tid; st < nstr; st += NT) {
-                const int64_t p0 = X0 + 4 * st;
-                if (p0 >= lim)
+                if (4 * st >= real)
                     continue;
-                const v4f v = reinterpret_cast<const v4f*>(exf)[st];
-                if (out_aligned && p0 + 4 <= lim) {
+                if (real >= 4) {
+                    // the last strip ends with the real columns (the floats it
+                    // shares with its neighbour are written twice, alike)
+                    const int po = min(4 * st, real - 4);
+                    const float* e = exf + po;
+                    const v4f v = (po & 3) == 0 ? *reinterpret_cast<const v4f*>(e) : v4f{e[0], e[1], e[2], e[3]};
                     for (int k = 0; k < rows; ++k)
-                        st16f_nt(pl + (int64_t)(row0 + k) * pitch + p0, v);
+                        st16f_nt(pl + (int64_t)(row0 + k) * pitch + X0 + po, v);
                 } else {
-                    const float vv[4] = {v.x, v.y, v.z, v.w};
-                    g_f32w* pg = (g_f32w*)pl;
+                    g_f32w* pg = (g_f32w*)(pl + X0);
                     for (int k = 0; k < rows; ++k)
-                        for (int q = 0; q < 4 && p0 + q < lim; ++q)
-                            pg[(int64_t)(row0 + k) * pitch + p0 + q] = vv[q];
+                        for (int q = 0; q < real; ++q)
+                            pg[(int64_t)(row0 + k) * pitch + q] = exf[q];
                 }
             }
         }
     }
+}
+
+// Column sums of one 4-float strip at any float of a row buffer.
+__device__ __forceinline__ void store_colsums4(float* dst, const v4f& v)
+{
+    if ((reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
+        *reinterpret_cast<v4f*>(dst) = v;
+        return;
+    }
+    dst[0] = v.x;
+    dst[1] = v.y;
+    dst[2] = v.z;
+    dst[3] = v.w;
 }
 
 __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const TileCoord& tc, uint8_t* lds)
@@ -1566,7 +1636,7 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
     const int64_t plane = pitch * H;
     const float* img = static_cast<const float*>(a.images[tc.f]);
     float* out = a.outs ? static_cast<float*>(a.outs[tc.f]) : nullptr;
-    const bool in_aligned = ((reinterpret_cast<uintptr_t>(img) | (uintptr_t)(pitch * 4) | (uintptr_t)(X0 * 4)) & 15) == 0;
+    const Strips sp = tile_strips_of(WB, (int)(lim - X0), 4, 1, pad);
 
     const double inv_s = exact_inv_area(F, s), inv_b = exact_inv_area(F, b);
     const LdsPlan L = lds_plan(kFwdF32, F.K, b, n, C);
@@ -1592,18 +1662,20 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
     const int kn4 = 4 * nstr;                 // floats of one row buffer
     for (int fr0 = 0; fr0 < n; fr0 += kRowGroupF) {
         const int ng = min(kRowGroupF, n - fr0);
-        for (int it = tid; it < C * ng * nstr; it += NT) {
-            const int st = it % nstr;
-            const int rest = it / nstr;
+        const int nit = sp.vec ? sp.nvec : nstr;
+        for (int it = tid; it < C * ng * nit; it += NT) {
+            const int st = it % nit;
+            const int rest = it / nit;
             const int g = rest % ng, ch = rest / ng;
             const float* pl = img + plane * ch;
             const int row0 = r * b + (fr0 + g) * s;
-            const int64_t p0 = X0 + 4 * st;
+            const int po = sp.vec ? min(4 * st, sp.real - 4) : 4 * st;   // the last strip ends with the real columns
+            const int64_t p0 = X0 + po;
             // rows past the frame are absent in the unpadded mode
             const int srows = pad == kPadNone ? max(0, min(s, H - row0)) : s;
             const int64_t cend = pad == kPadNone ? lim : tile_end;
             v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
-            if (in_aligned && p0 + 4 <= lim) {
+            if (p0 + 4 <= lim) {
                 int k = 0;
                 for (; k + 4 <= srows; k += 4) {
                     v4f w[4];
@@ -1626,7 +1698,18 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
                     acc.x += v[0]; acc.y += v[1]; acc.z += v[2]; acc.w += v[3];
                 }
             }
-            reinterpret_cast<v4f*>(colsum)[(ch * ng + g) * nstr + st] = acc;
+            store_colsums4(colsum + (ch * ng + g) * kn4 + po, acc);
+        }
+        if (sp.vec && sp.real < WB) {
+            // padded columns: the sums of the columns they mirror, or nothing
+            const int np = WB - sp.real;
+            if (pad != kPadNone)
+                lds_barrier();
+            for (int i = tid; i < C * ng * np; i += NT) {
+                float* cs = colsum + (i / np) * kn4;
+                const int x = sp.real + i % np;
+                cs[x] = pad == kPadNone ? 0.f : cs[mirror_col(x, sp.real, pad)];
+            }
         }
         lds_barrier();
         for (int j = tid; j < C * kn; j += NT) {
@@ -1787,7 +1870,7 @@ __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const 
             vgc[j] = to_u8(a.fg[fg_base + ((uint64_t)cidx[kc] * nn + fr * n + jj) * C + ch]);
     }
     lds_barrier();
-    const bool out_aligned = ((reinterpret_cast<uintptr_t>(out) | (uintptr_t)pitch | (uintptr_t)X0) & 15) == 0;
+    const int real = (int)(lim - X0);
     const uint32_t upitch = (uint32_t)pitch;
     uint8_t* band_out = out + (int64_t)r * b * pitch + X0;
     for (int fr = 0; fr < n; ++fr) {
@@ -1803,26 +1886,27 @@ __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const 
         for (int it = tid; it < nstr * parts; it += NT) {
             const int part = it / nstr;
             const int st = it - part * nstr;
-            const int64_t p0 = X0 + 16 * st;
             const int k0 = part * per, k1 = min(rows, k0 + per);
-            if (p0 >= lim)
+            if (16 * st >= real)
                 continue;
-            const v4u v = *reinterpret_cast<const v4u*>(exb + 16 * st);
-            if (out_aligned && p0 + 16 <= lim) {
+            if (real >= 16) {
+                // the last strip ends with the real columns (the bytes it
+                // shares with its neighbour are written twice, alike)
+                const int po = min(16 * st, real - 16);
+                const v4u v = lds16(exb + po);
                 if (F.off32) {
-                    const uint32_t off = (uint32_t)(fr * s) * upitch + 16u * (uint32_t)st;
+                    const uint32_t off = (uint32_t)(fr * s) * upitch + (uint32_t)po;
                     for (int k = k0; k < k1; ++k)
                         st16_nt(band_out + (off + (uint32_t)k * upitch), v);
                 } else {
                     for (int k = k0; k < k1; ++k)
-                        st16_nt(out + (int64_t)(row0 + k) * pitch + p0, v);
+                        st16_nt(out + (int64_t)(row0 + k) * pitch + X0 + po, v);
                 }
             } else {
-                const uint8_t* vb = exb + 16 * st;
                 for (int k = k0; k < k1; ++k) {
-                    g_u8w* op = (g_u8w*)(out + (int64_t)(row0 + k) * pitch);
-                    for (int q = 0; q < 16 && p0 + q < lim; ++q)
-                        op[p0 + q] = vb[q];
+                    g_u8w* op = (g_u8w*)(out + (int64_t)(row0 + k) * pitch + X0);
+                    for (int q = 0; q < real; ++q)
+                        op[q] = exb[q];
                 }
             }
         }
@@ -1867,7 +1951,7 @@ __device__ void reconstruct_tile_f32(const TileArgs& a, const FrameRec& F, const
             vgc[j] = a.fg[fg_base + ((uint64_t)cidx[kc] * nn + fr * n + jj) * C + ch];
     }
     lds_barrier();
-    const bool out_aligned = ((reinterpret_cast<uintptr_t>(out) | (uintptr_t)(pitch * 4) | (uintptr_t)(X0 * 4)) & 15) == 0;
+    const int real = (int)(lim - X0);
     for (int ch = 0; ch < C; ++ch) {
         float* pl = out + plane * ch;
         for (int fr = 0; fr < n; ++fr) {
@@ -1882,19 +1966,21 @@ __device__ void reconstruct_tile_f32(const TileArgs& a, const FrameRec& F, const
             const int row0 = r * b + fr * s;
             const int rows = min(s, H - row0);
             for (int st = tid; st < nstr; st += NT) {
-                const int64_t p0 = X0 + 4 * st;
-                if (p0 >= lim)
+                if (4 * st >= real)
                     continue;
-                const v4f v = reinterpret_cast<const v4f*>(exf)[st];
-                if (out_aligned && p0 + 4 <= lim) {
+                if (real >= 4) {
+                    // the last strip ends with the real columns (the floats it
+                    // shares with its neighbour are written twice, alike)
+                    const int po = min(4 * st, real - 4);
+                    const float* e = exf + po;
+                    const v4f v = (po & 3) == 0 ? *reinterpret_cast<const v4f*>(e) : v4f{e[0], e[1], e[2], e[3]};
                     for (int k = 0; k < rows; ++k)
-                        st16f_nt(pl + (int64_t)(row0 + k) * pitch + p0, v);
+                        st16f_nt(pl + (int64_t)(row0 + k) * pitch + X0 + po, v);
                 } else {
-                    const float vv[4] = {v.x, v.y, v.z, v.w};
-                    g_f32w* pg = (g_f32w*)pl;
+                    g_f32w* pg = (g_f32w*)(pl + X0);
                     for (int k = 0; k < rows; ++k)
-                        for (int q = 0; q < 4 && p0 + q < lim; ++q)
-                            pg[(int64_t)(row0 + k) * pitch + p0 + q] = vv[q];
+                        for (int q = 0; q < real; ++q)
+                            pg[(int64_t)(row0 + k) * pitch + q] = exf[q];
                 }
             }
         }
@@ -1934,7 +2020,8 @@ __device__ void backward_reduce_tile(const TileArgs& a, const FrameRec& F, const
     const int64_t lim = min(X0 + WB, (int64_t)W);
     const int64_t pitch = F.pitch, plane = pitch * H;
     const float* go = a.grad_out[tc.f];
-    const bool aligned = ((reinterpret_cast<uintptr_t>(go) | (uintptr_t)(pitch * 4) | (uintptr_t)(X0 * 4)) & 15) == 0;
+    // real columns only: padded ones have no output
+    const Strips sp = tile_strips_of(WB, (int)(lim - X0), 4, 1, kPadNone);
     const LdsPlan L = lds_plan(kBwd, F.K, b, n, C);
     float* colsum = reinterpret_cast<float*>(lds + L.colsum);
     double* cspart = reinterpret_cast<double*>(lds + L.cspart);
@@ -1954,16 +2041,18 @@ __device__ void backward_reduce_tile(const TileArgs& a, const FrameRec& F, const
     const int kn4 = 4 * nstr;
     for (int fr0 = 0; fr0 < n; fr0 += kRowGroupF) {
         const int ng = min(kRowGroupF, n - fr0);
-        for (int it = tid; it < C * ng * nstr; it += NT) {
-            const int st = it % nstr;
-            const int rest = it / nstr;
+        const int nit = sp.vec ? sp.nvec : nstr;
+        for (int it = tid; it < C * ng * nit; it += NT) {
+            const int st = it % nit;
+            const int rest = it / nit;
             const int g = rest % ng, ch = rest / ng;
             const float* pl = go + plane * ch;
             const int row0 = r * b + (fr0 + g) * s;
             const int rows = max(0, min(s, H - row0));   // real rows only
-            const int64_t p0 = X0 + 4 * st;
+            const int po = sp.vec ? min(4 * st, sp.real - 4) : 4 * st;   // the last strip ends with the real columns
+            const int64_t p0 = X0 + po;
             v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
-            if (aligned && p0 + 4 <= lim) {
+            if (p0 + 4 <= lim) {
                 const float* col = pl + (int64_t)row0 * pitch + p0;
                 int k = 0;
                 for (; k + 4 <= rows; k += 4) {
@@ -1986,7 +2075,12 @@ __device__ void backward_reduce_tile(const TileArgs& a, const FrameRec& F, const
                     acc.w += (p0 + 3 < lim) ? rk[p0 + 3] : 0.f;
                 }
             }
-            reinterpret_cast<v4f*>(colsum)[(ch * ng + g) * nstr + st] = acc;
+            store_colsums4(colsum + (ch * ng + g) * kn4 + po, acc);
+        }
+        if (sp.vec && sp.real < WB) {
+            const int np = WB - sp.real;
+            for (int i = tid; i < C * ng * np; i += NT)
+                colsum[(i / np) * kn4 + sp.real + i % np] = 0.f;
         }
         lds_barrier();
         for (int j = tid; j < C * kn; j += NT) {

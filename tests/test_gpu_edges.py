@@ -1,0 +1,129 @@
+"""GPU parity at the edges of the vector paths: rows that start at any byte
+(or float), a last strip moved back to end with the real columns, padded
+columns copied from the sums of the columns they mirror, and tiles too narrow
+for either (fewer real columns than one strip, or than the padding mirrors).
+Every frame against the oracle; bytes past each row's end keep their sentinel.
+
+Tolerances are those of the other parity tests: flags and counts exact,
+statistics within 1e-3, bytes within one level, gradients within 1e-5.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from tests.helpers import chw_to_hwc, compare_frame, oracle_params
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+dp = pytest.importorskip("paper_2511_04261_amd")
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+# width, b, s_b, channels, tile_cells: the last tile holds 1 to 17 real
+# columns, fewer or more than its padding, on and off the strip grid
+WIDTHS = [(16, 16, 4, 1, 0), (17, 16, 4, 1, 1), (31, 16, 8, 1, 1), (33, 8, 2, 3, 2), (65, 16, 4, 3, 4),
+          (47, 5, 5, 3, 3), (63, 32, 8, 1, 1), (49, 48, 16, 2, 1), (70, 32, 4, 4, 2), (101, 20, 10, 3, 0),
+          (1, 4, 2, 3, 0), (5, 64, 16, 3, 0), (23, 3, 1, 1, 4), (257, 256, 32, 1, 1), (130, 24, 3, 3, 0)]
+
+
+def _frames(layout, pad, width_pad):
+    fps = []
+    for i, (w, b, s, c, k) in enumerate(WIDTHS):
+        h = (b + 1, 2 * b - 1, 2 * b, 7)[i % 4]
+        pitch = (w + width_pad) if layout == dp.F32_CHW else (w * c + width_pad)
+        fps.append(dp.FrameParams(h, w, c, layout, b=b, sb=s, m=8, eps_bg=1.0, eps_fg=0.5, tau=1 + i % 2, pad_mode=pad,
+                                  seed=9, frame_index=i, pitch=pitch, tile_cells=k))
+    return fps
+
+
+def _strided(fp, dev, offset, fill):
+    """(buffer, frame view) with the view's first element `offset` into the buffer."""
+    if fp.layout == dp.F32_CHW:
+        shape, stride = (fp.channels, fp.height, fp.width), (fp.height * fp.pitch, fp.pitch, 1)
+        n, dtype = fp.channels * fp.height * fp.pitch, torch.float32
+    else:
+        shape, stride = (fp.height, fp.width, fp.channels), (fp.pitch, fp.channels, 1)
+        n, dtype = fp.height * fp.pitch, torch.uint8
+    buf = torch.full((n + 2 * offset,), fill, dtype=dtype, device=dev)
+    return buf, buf.as_strided(shape, stride, offset)
+
+
+def _untouched(buf, view, fill):
+    """Every element of the buffer outside the view still holds `fill`."""
+    rest = torch.ones_like(buf, dtype=torch.bool)
+    rest.as_strided(view.shape, view.stride(), view.storage_offset()).fill_(False)
+    return bool((buf[rest] == fill).all())
+
+
+@pytest.mark.parametrize("pad", [0, 1, 2])
+@pytest.mark.parametrize("offset,width_pad", [(0, 0), (1, 3), (16, 16)])
+def test_u8_rows_at_any_byte(dev, pad, offset, width_pad):
+    say("case: u8 edges", pad, offset, width_pad)
+    r = np.random.Generator(np.random.PCG64(100 * pad + offset))
+    fps = _frames(dp.U8_HWC, pad, width_pad)
+    xs = [r.integers(0, 256, (f.height, f.width, f.channels)).astype(np.uint8) for f in fps]
+    ms = [(r.random((f.height, f.width)) < 0.02).astype(np.uint8) * 3 for f in fps]
+    ins = [_strided(f, dev, offset, 0) for f in fps]
+    for (_, v), x in zip(ins, xs):
+        v.copy_(torch.from_numpy(x).to(dev))
+    fused, rebuilt = ([_strided(f, dev, offset, 77) for f in fps] for _ in range(2))
+    plan = dp.Plan(fps, device=dev)
+    plan.plan([torch.from_numpy(m).to(dev) for m in ms])
+    plan.forward([v for _, v in ins], out=[v for _, v in fused])
+    plan.reconstruct([v for _, v in rebuilt])
+    torch.cuda.synchronize()
+    store = plan.store_host()
+    for i, f in enumerate(fps):
+        want = oracle.forward(xs[i], ms[i], oracle_params(f))
+        for buf, v in (fused[i], rebuilt[i]):
+            compare_frame(store[i], want, v.cpu().numpy(), "frame %d" % i)
+            assert _untouched(buf, v, 77), i
+    plan.close()
+
+
+@pytest.mark.parametrize("pad", [0, 1, 2])
+@pytest.mark.parametrize("offset,width_pad", [(0, 0), (1, 1), (4, 4)])
+def test_f32_rows_at_any_float(dev, pad, offset, width_pad):
+    say("case: f32 edges", pad, offset, width_pad)
+    r = np.random.Generator(np.random.PCG64(1000 + 100 * pad + offset))
+    fps = _frames(dp.F32_CHW, pad, width_pad)
+    xs = [(r.random((f.channels, f.height, f.width)) * 255.0).astype(np.float32) for f in fps]
+    gs = [r.standard_normal((f.channels, f.height, f.width)).astype(np.float32) for f in fps]
+    ms = [(r.random((f.height, f.width)) < 0.02).astype(np.uint8) for f in fps]
+    ins, gos = ([_strided(f, dev, offset, 0.0) for f in fps] for _ in range(2))
+    for (_, v), (_, g), x, gx in zip(ins, gos, xs, gs):
+        v.copy_(torch.from_numpy(x).to(dev))
+        g.copy_(torch.from_numpy(gx).to(dev))
+    fused, rebuilt, gis = ([_strided(f, dev, offset, -7.0) for f in fps] for _ in range(3))
+    plan = dp.Plan(fps, device=dev)
+    clip = plan.clip_buffers()
+    plan.plan([torch.from_numpy(m).to(dev) for m in ms])
+    plan.forward([v for _, v in ins], out=[v for _, v in fused], clip=clip)
+    plan.reconstruct([v for _, v in rebuilt])
+    plan.backward([v for _, v in gos], [v for _, v in gis], clip)
+    torch.cuda.synchronize()
+    store = plan.store_host()
+    for i, f in enumerate(fps):
+        want = oracle.forward(chw_to_hwc(xs[i]), ms[i], oracle_params(f))
+        for buf, v in (fused[i], rebuilt[i]):
+            compare_frame(store[i], want, chw_to_hwc(v.cpu().numpy()), "frame %d" % i)
+            assert _untouched(buf, v, -7.0), i
+        gw = oracle.backward(chw_to_hwc(xs[i]).astype(np.float64), ms[i], chw_to_hwc(gs[i]).astype(np.float64),
+                             oracle_params(f))
+        got = chw_to_hwc(gis[i][1].cpu().numpy())
+        assert np.abs(got - gw).max() <= 1e-5 * max(1.0, np.abs(gw).max()), i
+        assert _untouched(gis[i][0], gis[i][1], -7.0), i
+    plan.close()
