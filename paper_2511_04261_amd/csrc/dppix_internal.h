@@ -42,6 +42,8 @@ struct WsLayout {
     size_t tile_map;      // int32[n_tiles][2]: (frame, tile within frame) per scheduling index
     size_t unit_map;      // int32[n_units][2]: (frame, plan unit within frame), frame-major
     size_t border_map;    // int32[n_border][2]: (frame, tile) of the tiles the adjoint's mirror pass visits
+    size_t met_map;       // int32[n_met][2]: (frame, unit within frame) of the metrics, by channel count
+    size_t met_base;      // int64[n_frames][2]: first metrics unit of each frame, and their number
     size_t simple_counts; // uint64[n_frames][4]: store counts of a call without masks (every cell simple)
     size_t total;
 };
@@ -96,8 +98,11 @@ struct TileArgs {
     // complexity label
     uint8_t* const* masks_out;
     int32_t edge_threshold;
-    // utility metrics: per tile (SSIM partial sum, squared-error sum)
+    // utility metrics: per unit (SSIM partial sum, squared-error sum)
+    const int32_t* met_map;
+    const int64_t* met_base;
     double* met_partial;
+    int32_t met_rows;         // rows of a metrics unit
 };
 
 // Host-side launchers (defined in dppix_kernels.hip).
@@ -121,7 +126,8 @@ hipError_t launch_backward_mirror(const TileArgs& a, int threads, int grid, hipS
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
 hipError_t launch_noise_advance(uint64_t* noise, int32_t n, uint64_t step, hipStream_t s);
 hipError_t launch_edge_mask(const TileArgs& a, int C, int threads, hipStream_t s);
-hipError_t launch_metrics(const TileArgs& a, int C, int threads, hipStream_t s);
+hipError_t launch_metrics(const TileArgs& a, int C, int64_t n_units, hipStream_t s);
+int metrics_unit_pixels(int C);   // pixels of a row one metrics unit covers
 hipError_t launch_metrics_reduce(const TileArgs& a, double* out, hipStream_t s);
 hipError_t occupancy_forward(int layout, int C, int threads, size_t lds, int* blocks_per_cu);
 

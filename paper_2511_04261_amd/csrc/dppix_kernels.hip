@@ -30,6 +30,7 @@
 
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
 // Register budget of the u8 forward kernel, as resident waves per SIMD: 4
@@ -2294,100 +2295,76 @@ __global__ __launch_bounds__(kMaxThreads) void k_edge_mask(TileArgs a)
 //   D = s0^2 + s1^2 + 49^2 c1,        E = 49 (s2 + s3) - s0^2 - s1^2 + 49 * 48 c2,
 // every integer part below 2^31.
 //
-// A tile's window centres are covered in chunks of one lane per (channel,
-// pixel) pair and up to kMetRowsMax centre rows; the chunk's rows, with 3
-// more on each side, are staged in LDS as one plane per channel (all of them
-// inside the frame, since every window is), so that the 7 taps of a window
-// row are consecutive bytes: a lane reads them as two words and forms the
-// row's five moments with byte dot products.  A lane walks down its column:
-// the moments of each new row go into a ring of the last 7 rows in
-// registers, and the window sum is updated by the new row minus the row
-// that leaves it.
+// The kernel is bound by its vector instructions (the frames are read once,
+// 2 bytes per pixel and channel against about 40 instructions), so the work
+// is laid out to share them.  A unit is kCw pixels x a segment of rows of
+// one frame, whatever the plan's tiles: a lane takes the two windows that
+// start at one even pixel of one channel and walks down the rows.  The eight
+// taps of the pair are two words of a channel plane in LDS; byte dot products
+// add them onto running sums (one per moment and window) that are never
+// reset, and a window's sum is the running sum minus its value seven rows
+// earlier (a ring in registers): one subtraction per moment.  SSIM needs the
+// sum of x^2 and y^2 only together, and the pair's two quotients share one
+// reciprocal.  Rows come in blocks of seven (the ring's length), each block's
+// vectors loaded while the one before is worked on (two LDS buffers, one
+// barrier per block).
+// 16 x 1080p RGB: 275 -> 164 us; 6000 x 4000 RGB: 380 -> 125 us; 24 photos of
+// odd widths: 417 -> 124 us (before: one window per lane, 38-row chunks staged
+// per tile, squared errors by a second read, vectors only for aligned rows,
+// and one lane per frame for the final sums).
 // ==========================================================================
-constexpr int kMetRowsMax = 32;                 // window-centre rows per chunk
-constexpr int kMetStage = kMetRowsMax + 6;      // staged rows per chunk
+constexpr int kMetBlock = 7;                    // rows per block: the window's height
 
-// Window-centre pixels per chunk (at most 256 lanes of (channel, pixel)) and
-// bytes per staged plane row: a row holds the chunk's pixels and the 6 of the
-// windows' reach, starting up to 15 pixels early at a 16-pixel boundary, and
-// a lane's three words read past its last tap stay inside it.
+// Pixels of a unit (their windows start in it, and their squared errors are
+// its own), 16-pixel groups of a staged row (the windows reach 6 pixels
+// further), and bytes of a staged plane row.
 template <int C>
 struct MetShape {
-    static constexpr int kCw = 256 / C;
-    static constexpr int kRow = (kCw + 26 + 15) & ~15;
+    static constexpr int kCw = C == 3 ? 160 : 512 / C;
+    static constexpr int kGroups = kCw / 16 + 1;
+    static constexpr int kRow = 16 * kGroups;
 };
 
 template <int C>
 struct MetLds {
-    alignas(16) uint8_t x[C][kMetStage][MetShape<C>::kRow];
-    alignas(16) uint8_t y[C][kMetStage][MetShape<C>::kRow];
-    double red[kMaxThreads / 64];
-    unsigned long long red_se[kMaxThreads / 64];
+    alignas(16) uint8_t px[2][2][C][kMetBlock][MetShape<C>::kRow];   // [buffer][frame]
+    double red[4];
+    unsigned long long red_se[4];
 };
 
-// Squared differences of the 16 bytes of two 16-byte vectors.
-__device__ __forceinline__ uint32_t sq_diff16(const v4u& x, const v4u& y)
+// Add the moments of one row's pair of windows, the 7 taps from byte `sh` of
+// xr[0] and the 7 from the byte after it, onto the running sums: per window
+// sum x, sum y, sum x^2 + y^2, sum xy.
+__device__ __forceinline__ void add_row_moments(const uint32_t* xr, const uint32_t* yr, uint32_t sh,
+                                                uint32_t (&t)[2][4])
 {
-    uint32_t acc = 0u;
-    const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int d = (int)((xs[k] >> (8 * q)) & 0xFFu) - (int)((ys[k] >> (8 * q)) & 0xFFu);
-            acc += (uint32_t)(d * d);
-        }
-    return acc;
+    const uint32_t xa = __builtin_amdgcn_alignbyte(xr[1], xr[0], sh), xb = __builtin_amdgcn_alignbyte(xr[2], xr[1], sh);
+    const uint32_t ya = __builtin_amdgcn_alignbyte(yr[1], yr[0], sh), yb = __builtin_amdgcn_alignbyte(yr[2], yr[1], sh);
+    const uint32_t xb0 = xb & 0x00FFFFFFu, yb0 = yb & 0x00FFFFFFu, xa1 = xa & 0xFFFFFF00u, ya1 = ya & 0xFFFFFF00u;
+    constexpr uint32_t one = 0x01010101u, low = 0x00010101u, high = 0x01010100u;
+    t[0][0] = __builtin_amdgcn_udot4(xb, low, __builtin_amdgcn_udot4(xa, one, t[0][0], false), false);
+    t[0][1] = __builtin_amdgcn_udot4(yb, low, __builtin_amdgcn_udot4(ya, one, t[0][1], false), false);
+    t[1][0] = __builtin_amdgcn_udot4(xb, one, __builtin_amdgcn_udot4(xa, high, t[1][0], false), false);
+    t[1][1] = __builtin_amdgcn_udot4(yb, one, __builtin_amdgcn_udot4(ya, high, t[1][1], false), false);
+    t[0][2] = __builtin_amdgcn_udot4(xb, xb0, __builtin_amdgcn_udot4(xa, xa, t[0][2], false), false);
+    t[0][2] = __builtin_amdgcn_udot4(yb, yb0, __builtin_amdgcn_udot4(ya, ya, t[0][2], false), false);
+    t[1][2] = __builtin_amdgcn_udot4(xb, xb, __builtin_amdgcn_udot4(xa, xa1, t[1][2], false), false);
+    t[1][2] = __builtin_amdgcn_udot4(yb, yb, __builtin_amdgcn_udot4(ya, ya1, t[1][2], false), false);
+    t[0][3] = __builtin_amdgcn_udot4(xb0, yb, __builtin_amdgcn_udot4(xa, ya, t[0][3], false), false);
+    t[1][3] = __builtin_amdgcn_udot4(xb, yb, __builtin_amdgcn_udot4(xa1, ya, t[1][3], false), false);
 }
 
-struct Moments {
-    uint32_t s[4];   // sum x | sum y << 16, sum x^2, sum y^2, sum xy
-};
-
-// The five moments of the 7 taps that start `a` bytes into the word xr[0]
-// (and yr[0]) of a plane row: the taps as two words (the second one's top
-// byte cleared), byte sums and byte products by 4-way dot products.  The two
-// byte sums (at most 7 * 255 each) share a word, and so do their window sums
-// (at most 49 * 255): a window update adds and subtracts both at once, and
-// neither half carries into the other.
-__device__ __forceinline__ Moments row_moments(const uint32_t* xr, const uint32_t* yr, uint32_t a)
+// A quarter of SSIM's numerator and its denominator (A B / 4 and D E above)
+// of one window, from sum x, sum y, sum x^2 + y^2 and sum xy.  Every integer
+// is below 2^53, so the products are exact and each factor is rounded once.
+__device__ __forceinline__ void ssim_ratio(uint32_t s0, uint32_t s1, uint32_t s23, uint32_t s4, double& num, double& den)
 {
-    const uint32_t x0 = __builtin_amdgcn_alignbyte(xr[1], xr[0], a);
-    const uint32_t x1 = __builtin_amdgcn_alignbyte(xr[2], xr[1], a) & 0x00FFFFFFu;
-    const uint32_t y0 = __builtin_amdgcn_alignbyte(yr[1], yr[0], a);
-    const uint32_t y1 = __builtin_amdgcn_alignbyte(yr[2], yr[1], a) & 0x00FFFFFFu;
-    constexpr uint32_t one = 0x01010101u;
-    Moments m;
-    const uint32_t sx = __builtin_amdgcn_udot4(x1, one, __builtin_amdgcn_udot4(x0, one, 0u, false), false);
-    const uint32_t sy = __builtin_amdgcn_udot4(y1, one, __builtin_amdgcn_udot4(y0, one, 0u, false), false);
-    m.s[0] = sx | (sy << 16);
-    m.s[1] = __builtin_amdgcn_udot4(x1, x1, __builtin_amdgcn_udot4(x0, x0, 0u, false), false);
-    m.s[2] = __builtin_amdgcn_udot4(y1, y1, __builtin_amdgcn_udot4(y0, y0, 0u, false), false);
-    m.s[3] = __builtin_amdgcn_udot4(x1, y1, __builtin_amdgcn_udot4(x0, y0, 0u, false), false);
-    return m;
-}
-
-// Every factor of a product here is below 2^24 (s0, s1 <= 49 * 255, s4 and
-// s2 + s3 <= 2 * 49 * 255^2), so the 24-bit multiplier forms them exactly at
-// full rate.  The quotient: the hardware reciprocal refined by one Newton
-// step, which squares its relative error (the mean of the windows is held to
-// 1e-9 of the oracle's; the denominator is a normal number of at most 2^62,
-// so no scaling is needed), times the numerator.  t[0] packs sum x (low
-// half) and sum y (high half), each at most 49 * 255; t[1..3] are sum x^2,
-// sum y^2 and sum xy.
-__device__ __forceinline__ double ssim_window(const uint32_t (&t)[4])
-{
-    const double c1 = (0.01 * 255.0) * (0.01 * 255.0), c2 = (0.03 * 255.0) * (0.03 * 255.0);
-    const uint32_t s0 = t[0] & 0xFFFFu, s1 = t[0] >> 16;
-    const int32_t p01 = (int32_t)__umul24(s0, s1), q = (int32_t)(__umul24(s0, s0) + __umul24(s1, s1));
-    const double A = (double)(2 * p01) + 2401.0 * c1;
-    const double B = (double)(2 * ((int32_t)__umul24(49u, t[3]) - p01)) + 2352.0 * c2;
-    const double D = (double)q + 2401.0 * c1;
-    const double E = (double)((int32_t)__umul24(49u, t[1] + t[2]) - q) + 2352.0 * c2;
-    const double num = A * B, den = D * E;
-    double r = __builtin_amdgcn_rcp(den);
-    r = fma(r, fma(-den, r, 1.0), r);
-    return num * r;
+    constexpr double c1 = (0.01 * 255.0) * (0.01 * 255.0), c2 = (0.03 * 255.0) * (0.03 * 255.0);
+    const double x = (double)s0, y = (double)s1;
+    const double p = x * y, q = fma(x, x, y * y);
+    const double B = fma(49.0, (double)s4, -p), E = fma(49.0, (double)s23, -q);
+    num = (p + 0.5 * (2401.0 * c1)) * (B + 0.5 * (2352.0 * c2));
+    den = (q + 2401.0 * c1) * (E + 2352.0 * c2);
 }
 
 // Sixteen pixels of C interleaved channels (C 16-byte vectors; pixel i's
@@ -2427,203 +2404,267 @@ __device__ __forceinline__ void deinterleave16(const v4u (&v)[C], v4u (&p)[C])
         p[c] = v4u{o[4 * c], o[4 * c + 1], o[4 * c + 2], o[4 * c + 3]};
 }
 
-// Stage nrs rows (row k at byte r0 + k * pitch) of the pixels [p0, p0 + np)
-// of both frames, all inside the frame's width W, as channel planes: channel
-// c of pixel p0 + q in row k goes to L.x[c][k][q].  With 16-byte aligned rows
-// (`vec`) and p0 a multiple of 16, the 16-pixel groups that end inside the
-// width move as C 16-byte vectors per frame (the last one may stage pixels
-// past p0 + np, inside the frame and the plane row); the pixels after them
-// move byte by byte.  Loads of a batch of items are all issued before the
-// first LDS write.
-template <int C>
-__device__ __forceinline__ void stage_metrics_planes(const g_u8* X, const g_u8* Y, int64_t pitch, int64_t r0, int p0,
-                                                     int np, int nrs, int W, bool vec, MetLds<C>& L)
+// A plane of 16 bytes with its last 16 - sh bytes moved to the front, zeros
+// behind them.
+__device__ __forceinline__ void drop_bytes(v4u& w, int sh)
 {
-    const int tid = threadIdx.x, NT = blockDim.x;
-    const int ngv = vec ? min((np + 15) >> 4, (W - p0) >> 4) : 0;
-    const int nv = nrs * ngv;
-    // items (frame, row, group): a lane holds one group's C vectors at a time
-    for (int it = tid; it < 2 * nv; it += NT) {
-        const int fy = it >= nv, r = it - fy * nv;
-        const int k = r / ngv, g = r - k * ngv;
-        const g_u8* src = fy ? Y : X;
-        const int64_t at = r0 + (int64_t)k * pitch + (int64_t)(p0 + 16 * g) * C;
-        v4u w[C], pl[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-            w[c] = ld16_nt((const void*)(src + at + 16 * c));
-        deinterleave16<C>(w, pl);
-        uint8_t(&dst)[C][kMetStage][MetShape<C>::kRow] = fy ? L.y : L.x;
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-            *reinterpret_cast<v4u*>(&dst[c][k][16 * g]) = pl[c];
+    if (sh & 8) {
+        w.x = w.z;
+        w.y = w.w;
+        w.z = w.w = 0u;
     }
-    const int q0 = 16 * ngv, nb = max(0, np - q0) * C, ns = nrs * nb;
-    constexpr int kBb = 4;
-    for (int base = 0; base < ns; base += kBb * NT) {
-        uint8_t bxv[kBb], byv[kBb];
-#pragma unroll
-        for (int i = 0; i < kBb; ++i) {
-            const int it = base + i * NT + tid;
-            if (it < ns) {
-                const int k = it / nb, j = it - k * nb;
-                const int64_t at = r0 + (int64_t)k * pitch + (int64_t)(p0 + q0) * C + j;
-                bxv[i] = X[at];
-                byv[i] = Y[at];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kBb; ++i) {
-            const int it = base + i * NT + tid;
-            if (it < ns) {
-                const int k = it / nb, j = it - k * nb;
-                const int q = j / C, c = j - q * C;
-                L.x[c][k][q0 + q] = bxv[i];
-                L.y[c][k][q0 + q] = byv[i];
-            }
-        }
+    if (sh & 4) {
+        w.x = w.y;
+        w.y = w.z;
+        w.z = w.w;
+        w.w = 0u;
     }
+    const uint32_t b = (uint32_t)(sh & 3);
+    w.x = __builtin_amdgcn_alignbyte(w.y, w.x, b);
+    w.y = __builtin_amdgcn_alignbyte(w.z, w.y, b);
+    w.z = __builtin_amdgcn_alignbyte(w.w, w.z, b);
+    w.w = __builtin_amdgcn_alignbyte(0u, w.w, b);
 }
 
-template <int C>
-__device__ void metrics_tile(const TileArgs& a, const FrameRec& F, const TileCoord& tc, MetLds<C>& L)
+// Squared differences of two planes' 16 bytes: sum x^2 + sum y^2 - 2 sum xy.
+__device__ __forceinline__ uint32_t sq_diff16(const v4u& x, const v4u& y)
 {
-    const int tid = threadIdx.x, NT = blockDim.x;
-    const int b = F.b, H = F.H, W = F.W;
-    const int x0c = tc.ct * F.K;
-    const int Kt = min(F.K, F.GC - x0c);
-    const int y0 = tc.r * b, y1 = min(y0 + b, H);
-    const int xa = x0c * b, xb = min((x0c + Kt) * b, W);
-    const uint8_t* X = static_cast<const uint8_t*>(a.images[tc.f]);
-    const uint8_t* Y = static_cast<const uint8_t*>(a.outs[tc.f]);
-    const g_u8* Xg = (const g_u8*)X;
-    const g_u8* Yg = (const g_u8*)Y;
-    const int64_t pitch = F.pitch;
-    double ssim_acc = 0.0;
-    unsigned long long se = 0;
-    // squared error over the tile's real pixels: 16-byte strips where the
-    // rows allow, single bytes for the rest
-    if (y0 < H && xa < W) {
-        const int64_t b0 = (int64_t)xa * C, b1 = (int64_t)xb * C;
-        const bool aligned = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y) | (uintptr_t)pitch |
-                               (uintptr_t)b0) & 15) == 0;
-        const int nv = aligned ? (int)((b1 - b0) >> 4) : 0;
-        const int rows = y1 - y0;
-        constexpr int kB = 4;   // items whose loads are all in flight together
-        for (int base = 0; base < rows * nv; base += kB * NT) {
-            v4u wx[kB], wy[kB];
+    uint32_t s = 0u, m = 0u;
 #pragma unroll
-            for (int i = 0; i < kB; ++i) {
-                const int it = base + i * NT + tid;
-                if (it < rows * nv) {
-                    const int yy = it / nv, v = it - yy * nv;
-                    const int64_t at = (int64_t)(y0 + yy) * pitch + b0 + 16 * v;
-                    wx[i] = ld16_nt(X + at);
-                    wy[i] = ld16_nt(Y + at);
-                }
-            }
+    for (int k = 0; k < 4; ++k) {
+        s = __builtin_amdgcn_udot4(x[k], x[k], s, false);
+        s = __builtin_amdgcn_udot4(y[k], y[k], s, false);
+        m = __builtin_amdgcn_udot4(x[k], y[k], m, false);
+    }
+    return s - 2u * m;
+}
+
+// One 16-pixel group of one row, C interleaved 16-byte vectors.
+template <int C>
+struct MetGroup {
+    v4u w[C];
+
+    // n < 0: all 16 pixels; else the first n of a frame narrower than that.
+    __device__ __forceinline__ void load(const uint8_t* p, int n)
+    {
+        if (n < 0) {
 #pragma unroll
-            for (int i = 0; i < kB; ++i)
-                if (base + i * NT + tid < rows * nv)
-                    se += sq_diff16(wx[i], wy[i]);
+            for (int c = 0; c < C; ++c)
+                w[c] = ld16_nt(p + 16 * c);
+            return;
         }
-        const int nr = (int)(b1 - b0) - 16 * nv;
-        for (int it = tid; it < rows * nr; it += NT) {
-            const int yy = it / nr, q = it - yy * nr;
-            const int64_t at = (int64_t)(y0 + yy) * pitch + b0 + 16 * nv + q;
-            const int d = (int)Xg[at] - (int)Yg[at];
-            se += (unsigned long long)(d * d);
+        const g_u8* g = (const g_u8*)p;
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                uint32_t v = 0u;
+                for (int b = 0; b < 4; ++b) {
+                    const int i = 16 * c + 4 * k + b;
+                    if (i < n * C)
+                        v |= (uint32_t)g[i] << (8 * b);
+                }
+                w[c][k] = v;
+            }
+    }
+
+    // Into the planes of a staged row, `back` pixels further left (a group
+    // that crosses the right edge is read that far back from its place).
+    __device__ __forceinline__ void store(uint8_t* dst, int plane, int back)
+    {
+        v4u p[C];
+        deinterleave16<C>(w, p);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (back != 0)
+                drop_bytes(p[c], back);
+            *reinterpret_cast<v4u*>(dst + c * plane) = p[c];
         }
     }
-    // SSIM windows centred in this tile's real pixels, 3 away from every edge
-    const int cy0 = max(y0, 3), cy1 = min(y1, H - 3);
-    const int cx0 = max(xa, 3), cx1 = min(xb, W - 3);
-    const int CW = min(NT, 256) / C;                  // window-centre pixels per chunk
-    constexpr int kRowW = MetShape<C>::kRow / 4;      // words per plane row
-    const bool vec = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y) | (uintptr_t)pitch) & 15) == 0;
-    for (int cxb = cx0; cxb < cx1; cxb += CW) {
-        const int cw = min(CW, cx1 - cxb);
-        const int pa = cxb - 3;                         // first pixel a window of the chunk reads
-        const int p0 = vec ? (pa & ~15) : pa;
-        const int sh = pa - p0;
-        const int np = sh + cw + 6;                     // staged pixels from p0
-        const int ch = tid / cw, px = tid - ch * cw;    // this lane's (channel, centre pixel)
-        const uint32_t o = (uint32_t)(sh + px);
-        for (int cyb = cy0; cyb < cy1; cyb += kMetRowsMax) {
-            const int rb = min(kMetRowsMax, cy1 - cyb);
-            const int nrs = rb + 6;
-            stage_metrics_planes<C>(Xg, Yg, pitch, (int64_t)(cyb - 3) * pitch, p0, np, nrs, W, vec, L);
-            lds_barrier();
-            if (ch < C) {
-                const uint32_t* xr = reinterpret_cast<const uint32_t*>(&L.x[ch][0][0]) + (o >> 2);
-                const uint32_t* yr = reinterpret_cast<const uint32_t*>(&L.y[ch][0][0]) + (o >> 2);
-                Moments ring[7];
-                uint32_t t[4] = {0u, 0u, 0u, 0u};
-                for (int k0 = 0; k0 < nrs; k0 += 7) {
+};
+
+// Three waves per SIMD: the ring of a pair of windows is 56 registers, and with
+// the 128 of four waves the kernel spills (444 us instead of 164, 16 x 1080p).
+template <int C>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_metrics(TileArgs a)
+{
+    __shared__ MetLds<C> L;
+    using Sh = MetShape<C>;
+    const int tid = threadIdx.x;
+    const int64_t unit = a.sched_offset + blockIdx.x;
+    const int f = (int)uniform_u32((uint32_t)a.met_map[2 * unit]);
+    const int local = (int)uniform_u32((uint32_t)a.met_map[2 * unit + 1]);
+    const FrameRec& F = a.frames[f];
+    const int H = F.H, W = F.W;
+    const int64_t pitch = F.pitch;
+    const int cols = (W + Sh::kCw - 1) / Sh::kCw;
+    const int seg = local / cols;
+    const int p0 = (local - seg * cols) * Sh::kCw, r0 = seg * a.met_rows;
+    const int own = min(a.met_rows, H - r0);                 // rows whose squared errors are the unit's
+    const int nrow = min(a.met_rows + kMetBlock - 1, H - r0);   // rows its windows read
+    const int nblk = (nrow + kMetBlock - 1) / kMetBlock;
+    const uint8_t* X = static_cast<const uint8_t*>(a.images[f]) + (int64_t)r0 * pitch;
+    const uint8_t* Y = static_cast<const uint8_t*>(a.outs[f]) + (int64_t)r0 * pitch;
+    double acc = 0.0;
+    unsigned long long se = 0;
+
+    // Staging of a block: an item per (frame, row, 16-pixel group).  Where
+    // they do not fill the workgroup, another wave begins each block, so that
+    // every SIMD gets its share.
+    constexpr int kItems = 2 * kMetBlock * Sh::kGroups, kPer = (kItems + 255) / 256;
+    const int narrow = W >= 16 ? -1 : W;
+    MetGroup<C> grp[kPer];
+    struct Item {
+        int y, row, g, px, from;
+        bool in;
+    };
+    auto item = [&](int blk, int i) {
+        const int it = ((tid + 64 * blk) & 255) + 256 * i;
+        Item m;
+        m.y = it / (kMetBlock * Sh::kGroups);
+        const int q = it - m.y * (kMetBlock * Sh::kGroups);
+        m.row = q / Sh::kGroups;
+        m.g = q - m.row * Sh::kGroups;
+        m.px = p0 + 16 * m.g;
+        m.from = W >= 16 ? min(m.px, W - 16) : 0;
+        m.in = it < kItems && m.px < W && blk * kMetBlock + m.row < nrow;
+        return m;
+    };
+    auto load = [&](int blk) {
 #pragma unroll
-                    for (int j = 0; j < 7; ++j) {
-                        const int k = k0 + j;
-                        if (k < nrs) {
-                            const Moments h = row_moments(xr + k * kRowW, yr + k * kRowW, o & 3u);
+        for (int i = 0; i < kPer; ++i) {
+            const Item m = item(blk, i);
+            if (m.in)
+                grp[i].load((m.y ? Y : X) + (int64_t)(blk * kMetBlock + m.row) * pitch + (int64_t)m.from * C, narrow);
+        }
+    };
+    auto store = [&](int blk) {
 #pragma unroll
-                            for (int m = 0; m < 4; ++m)
-                                t[m] = (t[m] + h.s[m]) - (k >= 7 ? ring[j].s[m] : 0u);
-                            ring[j] = h;
-                            if (k >= 6)
-                                ssim_acc += ssim_window(t);
-                        }
-                    }
-                }
+        for (int i = 0; i < kPer; ++i) {
+            const Item m = item(blk, i);
+            if (m.in)
+                grp[i].store(&L.px[blk & 1][m.y][0][m.row][16 * m.g], kMetBlock * Sh::kRow, m.px - m.from);
+        }
+    };
+    // Squared errors of a staged block: a lane per (channel, row, group) of
+    // the unit's own pixels (planes end in zeros past the right edge).
+    constexpr int kOwnGroups = Sh::kCw / 16;
+    const int eg = tid % kOwnGroups, erow = tid / kOwnGroups % kMetBlock, ech = tid / (kOwnGroups * kMetBlock);
+    const bool errs = ech < C && p0 + 16 * eg < W;
+    auto errors = [&](int blk) {
+        if (errs && blk * kMetBlock + erow < own)
+            se += sq_diff16(*reinterpret_cast<const v4u*>(&L.px[blk & 1][0][ech][erow][16 * eg]),
+                            *reinterpret_cast<const v4u*>(&L.px[blk & 1][1][ech][erow][16 * eg]));
+    };
+    // this lane's (channel, pair of windows)
+    constexpr int kPairs = Sh::kCw / 2;
+    const int ch = tid / kPairs, pair = tid - ch * kPairs;
+    const bool works = ch < C && p0 + 2 * pair < W - 6 && nrow >= kMetBlock;
+    const double second = p0 + 2 * pair + 1 < W - 6 ? 1.0 : 0.0;
+    const uint32_t sh = 2u * (uint32_t)(pair & 1);
+    const int word = pair >> 1;
+    uint32_t t[2][4] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
+    uint32_t ring[kMetBlock][2][4];
+    // One block of rows.  `first`: windows end only with its last row, and
+    // start at the unit's first; `full`: all seven rows are there (no branch
+    // between them, so their loads and sums interleave).
+    auto rows = [&](int blk, auto first, auto full) {
+        const uint32_t* xr = reinterpret_cast<const uint32_t*>(&L.px[blk & 1][0][ch][0][0]) + word;
+        const uint32_t* yr = reinterpret_cast<const uint32_t*>(&L.px[blk & 1][1][ch][0][0]) + word;
+#pragma unroll
+        for (int j = 0; j < kMetBlock; ++j) {
+            if (!full && blk * kMetBlock + j >= nrow)
+                break;
+            add_row_moments(xr + j * (Sh::kRow / 4), yr + j * (Sh::kRow / 4), sh, t);
+            if (!first || j == kMetBlock - 1) {
+                uint32_t w[2][4];
+#pragma unroll
+                for (int m = 0; m < 8; ++m)
+                    w[m >> 2][m & 3] = t[m >> 2][m & 3] - (first ? 0u : ring[j][m >> 2][m & 3]);
+                double n0, d0, n1, d1;
+                ssim_ratio(w[0][0], w[0][1], w[0][2], w[0][3], n0, d0);
+                ssim_ratio(w[1][0], w[1][1], w[1][2], w[1][3], n1, d1);
+                // n0 / d0 + n1 / d1 over one reciprocal, refined by one
+                // Newton step (it squares the relative error); the
+                // denominators are normal numbers below 2^62
+                const double den = d0 * d1;
+                double r = __builtin_amdgcn_rcp(den);
+                r = fma(r, fma(-den, r, 1.0), r);
+                acc = fma(fma(n0, d1, second * n1 * d0), r, acc);
             }
-            lds_barrier();
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+                ring[j][m >> 2][m & 3] = t[m >> 2][m & 3];
+        }
+    };
+    load(0);
+    store(0);
+    lds_barrier();
+    if (nblk > 1)
+        load(1);
+    errors(0);
+    if (works)
+        rows(0, std::true_type(), std::true_type());
+    for (int blk = 1; blk < nblk; ++blk) {
+        store(blk);
+        lds_barrier();
+        if (blk + 1 < nblk)
+            load(blk + 1);
+        errors(blk);
+        if (works) {
+            if ((blk + 1) * kMetBlock <= nrow)
+                rows(blk, std::false_type(), std::true_type());
+            else
+                rows(blk, std::false_type(), std::false_type());
         }
     }
     // workgroup reduction in a fixed order
-    const int lane = tid & 63, wid = tid >> 6;
+    acc *= 4.0;
     for (int d = 32; d > 0; d >>= 1) {
-        ssim_acc += __shfl_down(ssim_acc, d, 64);
+        acc += __shfl_down(acc, d, 64);
         se += __shfl_down(se, d, 64);
     }
-    if (lane == 0) {
-        L.red[wid] = ssim_acc;
-        L.red_se[wid] = se;
+    if ((tid & 63) == 0) {
+        L.red[tid >> 6] = acc;
+        L.red_se[tid >> 6] = se;
     }
     lds_barrier();
     if (tid == 0) {
-        double tt = 0.0;
-        unsigned long long e = 0;
-        for (int w = 0; w < (NT + 63) / 64; ++w) {
-            tt += L.red[w];
-            e += L.red_se[w];
-        }
-        a.met_partial[2 * tc.t] = tt;
-        reinterpret_cast<unsigned long long*>(a.met_partial)[2 * tc.t + 1] = e;
+        a.met_partial[2 * unit] = (L.red[0] + L.red[1]) + (L.red[2] + L.red[3]);
+        reinterpret_cast<unsigned long long*>(a.met_partial)[2 * unit + 1] =
+            (L.red_se[0] + L.red_se[1]) + (L.red_se[2] + L.red_se[3]);
     }
-    lds_barrier();
 }
 
-template <int C>
-__global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(C < 4 ? 5 : 4))) void k_metrics(TileArgs a)
+// One workgroup per frame: MSE = sum of squared errors / (H W C); SSIM = sum
+// of window values / (windows * C), the units' partial sums added in a fixed
+// order (strided over the lanes, then a tree).
+__global__ __launch_bounds__(256) void k_metrics_reduce(TileArgs a, double* out)
 {
-    __shared__ MetLds<C> L;
-    extern __shared__ __align__(16) uint8_t lds[];
-    run_one_tile(a, [&](const FrameRec& F, const TileCoord& tc) { metrics_tile<C>(a, F, tc, L); });
-}
-
-// One thread per frame: MSE = sum of squared errors / (H W C); SSIM = sum of
-// window values / (windows * C), partials added in tile order.
-__global__ void k_metrics_reduce(TileArgs a, double* out)
-{
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= a.n_frames)
-        return;
-    const FrameRec F = a.frames[f];
+    __shared__ double red[4];
+    __shared__ unsigned long long red_se[4];
+    const int f = blockIdx.x, tid = threadIdx.x;
+    const FrameRec& F = a.frames[f];
+    const int64_t base = a.met_base[2 * f], n = a.met_base[2 * f + 1];
     double t = 0.0;
     unsigned long long e = 0;
-    for (int64_t i = 0; i < (int64_t)F.GR * F.TX; ++i) {
-        t += a.met_partial[2 * (F.tile_base + i)];
-        e += reinterpret_cast<const unsigned long long*>(a.met_partial)[2 * (F.tile_base + i) + 1];
+    for (int64_t i = tid; i < n; i += 256) {
+        t += a.met_partial[2 * (base + i)];
+        e += reinterpret_cast<const unsigned long long*>(a.met_partial)[2 * (base + i) + 1];
     }
+    for (int d = 32; d > 0; d >>= 1) {
+        t += __shfl_down(t, d, 64);
+        e += __shfl_down(e, d, 64);
+    }
+    if ((tid & 63) == 0) {
+        red[tid >> 6] = t;
+        red_se[tid >> 6] = e;
+    }
+    lds_barrier();
+    if (tid != 0)
+        return;
+    t = (red[0] + red[1]) + (red[2] + red[3]);
+    e = (red_se[0] + red_se[1]) + (red_se[2] + red_se[3]);
     const double windows = (double)max(F.H - 6, 0) * (double)max(F.W - 6, 0) * F.C;
     out[2 * f + 0] = (double)e / ((double)F.H * F.W * F.C);
     out[2 * f + 1] = windows > 0 ? t / windows : 0.0;
@@ -2826,21 +2867,33 @@ hipError_t launch_edge_mask(const TileArgs& a, int C, int threads, hipStream_t s
     }
 }
 
-hipError_t launch_metrics(const TileArgs& a, int C, int threads, hipStream_t s)
+hipError_t launch_metrics(const TileArgs& a, int C, int64_t n_units, hipStream_t s)
 {
-    TileArgs b = a;
-    b.persistent = 0;
+    if (n_units == 0)
+        return hipSuccess;
+    const dim3 grid((unsigned)n_units), block(256);
     switch (C) {
-    case 1: return launch_tiles(k_metrics<1>, b, threads, 0, (int)b.n_tiles, s);
-    case 2: return launch_tiles(k_metrics<2>, b, threads, 0, (int)b.n_tiles, s);
-    case 3: return launch_tiles(k_metrics<3>, b, threads, 0, (int)b.n_tiles, s);
-    default: return launch_tiles(k_metrics<4>, b, threads, 0, (int)b.n_tiles, s);
+    case 1: hipLaunchKernelGGL(k_metrics<1>, grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL(k_metrics<2>, grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL(k_metrics<3>, grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL(k_metrics<4>, grid, block, 0, s, a); break;
+    }
+    return hipGetLastError();
+}
+
+int metrics_unit_pixels(int C)
+{
+    switch (C) {
+    case 1: return MetShape<1>::kCw;
+    case 2: return MetShape<2>::kCw;
+    case 3: return MetShape<3>::kCw;
+    default: return MetShape<4>::kCw;
     }
 }
 
 hipError_t launch_metrics_reduce(const TileArgs& a, double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_metrics_reduce, dim3((unsigned)((a.n_frames + 63) / 64)), dim3(64), 0, s, a, out);
+    hipLaunchKernelGGL(k_metrics_reduce, dim3((unsigned)a.n_frames), dim3(256), 0, s, a, out);
     return hipGetLastError();
 }
 

@@ -127,3 +127,31 @@ def test_f32_rows_at_any_float(dev, pad, offset, width_pad):
         assert np.abs(got - gw).max() <= 1e-5 * max(1.0, np.abs(gw).max()), i
         assert _untouched(gis[i][0], gis[i][1], -7.0), i
     plan.close()
+
+
+@pytest.mark.parametrize("offset,width_pad", [(0, 0), (1, 5), (16, 16)])
+def test_metrics_at_unit_edges(dev, offset, width_pad):
+    """Frames around the metrics kernel's pixel groups, units of columns and
+    blocks of rows, for every channel count: MSE exact, SSIM within 1e-9."""
+    say("case: metrics edges", offset, width_pad)
+    r = np.random.Generator(np.random.PCG64(500 + offset))
+    shapes = [(7, 7, 3), (8, 13, 1), (14, 16, 2), (13, 17, 4), (15, 31, 3), (7, 165, 3), (21, 166, 3), (9, 167, 3),
+              (64, 128, 4), (16, 133, 4), (70, 135, 4), (20, 262, 2), (71, 257, 2), (65, 518, 1), (10, 519, 1),
+              (77, 320, 3), (6, 200, 3), (40, 6, 3), (1, 1, 1), (133, 337, 3)]
+    fps, xs, ys = [], [], []
+    for i, (h, w, c) in enumerate(shapes):
+        fps.append(dp.FrameParams(h, w, c, dp.U8_HWC, b=(8, 16, 5)[i % 3], pitch=w * c + width_pad))
+        x = r.integers(0, 256, (h, w, c))
+        xs.append(x.astype(np.uint8))
+        ys.append(np.clip(x // 3 + r.integers(0, 90, (h, w, c)), 0, 255).astype(np.uint8))
+    ti, to = ([_strided(f, dev, offset, 255)[1] for f in fps] for _ in range(2))
+    for i in range(len(shapes)):
+        ti[i].copy_(torch.from_numpy(xs[i]).to(dev))
+        to[i].copy_(torch.from_numpy(ys[i]).to(dev))
+    plan = dp.Plan(fps, device=dev)
+    got = plan.metrics(ti, to).cpu().numpy()
+    for i, (h, w, c) in enumerate(shapes):
+        assert got[i, 0] == pytest.approx(((xs[i].astype(float) - ys[i].astype(float)) ** 2).mean(), rel=1e-15, abs=0), i
+        ssim = oracle.metrics(xs[i], ys[i])[1] if h >= 7 and w >= 7 else 0.0
+        assert abs(got[i, 1] - ssim) <= 1e-9, (i, got[i, 1], ssim)
+    plan.close()
