@@ -266,8 +266,9 @@ int32_t metrics_units(dppix_plan& p, std::vector<int32_t>& map, std::vector<int6
     int32_t m = 10;
     while (m > 2 && total(7 * m - 6) < kMetUnits)
         --m;
-    // huge batches: no more units than twice the tiles (the table's size)
-    while (m < (1 << 20) && total(7 * m - 6) > 2 * p.n_tiles + (1 << 20))
+    // huge batches: no more units than twice the tiles (the table's size); a
+    // lane's squared errors (at most 16 * 255^2 a block) fit 32 bits up to m = 4096
+    while (m < 2048 && total(7 * m - 6) > 2 * p.n_tiles + (1 << 20))
         m *= 2;
     const int32_t rows = 7 * m - 6;
     for (int C = 1; C <= 4; ++C) {

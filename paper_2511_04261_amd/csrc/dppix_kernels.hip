@@ -2506,7 +2506,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     const uint8_t* X = static_cast<const uint8_t*>(a.images[f]) + (int64_t)r0 * pitch;
     const uint8_t* Y = static_cast<const uint8_t*>(a.outs[f]) + (int64_t)r0 * pitch;
     double acc = 0.0;
-    unsigned long long se = 0;
+    uint32_t se = 0u;
 
     // Staging of a block: an item per (frame, row, 16-pixel group).  Where
     // they do not fill the workgroup, another wave begins each block, so that
@@ -2620,13 +2620,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
     // workgroup reduction in a fixed order
     acc *= 4.0;
+    unsigned long long se64 = se;
     for (int d = 32; d > 0; d >>= 1) {
         acc += __shfl_down(acc, d, 64);
-        se += __shfl_down(se, d, 64);
+        se64 += __shfl_down(se64, d, 64);
     }
     if ((tid & 63) == 0) {
         L.red[tid >> 6] = acc;
-        L.red_se[tid >> 6] = se;
+        L.red_se[tid >> 6] = se64;
     }
     lds_barrier();
     if (tid == 0) {
