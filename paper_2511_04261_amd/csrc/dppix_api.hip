@@ -60,8 +60,12 @@ struct dppix_plan {
     std::vector<int64_t> sched_base;
     int64_t n_tiles = 0;
     int64_t n_units = 0;
-    int32_t met_rows = 0;               // rows of a metrics unit
-    std::vector<int64_t> met_lo;        // metrics units of each channel count C: [met_lo[C - 1], met_lo[C])
+    // units of the metrics, the plan from labels and the label masks: those of
+    // the frames with C channels are [lo[C - 1], lo[C]) of their map
+    int32_t met_rows = 0, edge_rows = 0;    // rows of a unit
+    std::vector<int64_t> met_lo, lab_lo, edge_lo;
+    int lab_threads = 64, edge_threads = 64;
+    size_t lab_cells = 0;               // counters of the largest unit of the plan from labels
     int64_t n_border = 0;               // tiles with pixels that mirrored padding folds onto
     bool prefix_scan = false;           // the plan's scan needs no hand-off between workgroups
     int64_t total_cells = 0;
@@ -237,56 +241,91 @@ int tile_threads(const FrameRec& F)
     return nstr * ngq <= 320 ? 128 : kDefaultThreads;
 }
 
-// Units of the utility metrics, frames of one channel count after another:
-// columns of metrics_unit_pixels(C) pixels x segments of `rows` rows.  A
-// unit reads six rows more than it has, and works in blocks of seven, so a
-// segment is 7 m - 6 rows; m is the largest up to 10 that still gives the GPU
-// kMetUnits units, four rounds of the 768 workgroups it holds at once (16 x
-// 1080p: m = 3 / 6 / 10: 196 / 170 / 164 us; one 6000 x 4000 frame: m = 3 / 6 /
-// 8 / 10: 155 / 131 / 125 / 129 us).
-constexpr int64_t kMetUnits = 3000;
-
-int32_t metrics_units(dppix_plan& p, std::vector<int32_t>& map, std::vector<int64_t>& base)
+// A map of units, frames of one channel count after another (lo: see
+// dppix_plan): (frame, unit within frame) pairs; first: each frame's first
+// unit and their number.
+template <typename Units>
+void map_units(const dppix_plan& p, Units units, std::vector<int32_t>& map, std::vector<int64_t>& lo,
+               std::vector<int64_t>* first)
 {
     const int32_t n = (int32_t)p.frames.size();
-    base.assign(2 * (size_t)n, 0);
-    p.met_lo.assign(5, 0);
-    if (p.any_f32)   // metrics compare bytes
-        return 1;
-    auto units = [&](const FrameRec& F, int32_t rows) {
-        const int64_t cw = metrics_unit_pixels(F.C);
-        return ((F.W + cw - 1) / cw) * (int64_t)((F.H + rows - 1) / rows);
-    };
-    auto total = [&](int32_t rows) {
-        int64_t t = 0;
-        for (const FrameRec& F : p.frames)
-            t += units(F, rows);
-        return t;
-    };
-    int32_t m = 10;
-    while (m > 2 && total(7 * m - 6) < kMetUnits)
-        --m;
-    // huge batches: no more units than twice the tiles (the table's size); a
-    // lane's squared errors (at most 16 * 255^2 a block) fit 32 bits up to m = 4096
-    while (m < 2048 && total(7 * m - 6) > 2 * p.n_tiles + (1 << 20))
-        m *= 2;
-    const int32_t rows = 7 * m - 6;
+    lo.assign(5, 0);
+    if (first != nullptr)
+        first->assign(2 * (size_t)n, 0);
     for (int C = 1; C <= 4; ++C) {
-        for (int32_t f = 0; f < n; ++f) {
-            const FrameRec& F = p.frames[f];
-            if (F.C != C)
+        for (int32_t f = 0; f < n && !p.any_f32; ++f) {   // (the metrics and labels take bytes)
+            if (p.frames[f].C != C)
                 continue;
-            const int64_t u = units(F, rows);
-            base[2 * (size_t)f] = (int64_t)map.size() / 2;
-            base[2 * (size_t)f + 1] = u;
+            const int64_t u = units(p.frames[f]);
+            if (first != nullptr) {
+                (*first)[2 * (size_t)f] = (int64_t)map.size() / 2;
+                (*first)[2 * (size_t)f + 1] = u;
+            }
             for (int64_t i = 0; i < u; ++i) {
                 map.push_back(f);
                 map.push_back((int32_t)i);
             }
         }
-        p.met_lo[C] = (int64_t)map.size() / 2;
+        lo[C] = (int64_t)map.size() / 2;
     }
-    return rows;
+}
+
+// Rows of a unit, step * m - over for the largest m up to `most` that gives
+// the batch `wanted` units; units(F, rows) counts a frame's.  Huge batches:
+// no more units than twice the tiles (the map's size).
+template <typename Units>
+int32_t unit_rows(const dppix_plan& p, Units units, int32_t step, int32_t over, int32_t most, int64_t wanted)
+{
+    auto total = [&](int32_t m) {
+        int64_t t = 0;
+        for (const FrameRec& F : p.frames)
+            t += units(F, step * m - over);
+        return t;
+    };
+    int32_t m = most;
+    while (m > 2 && total(m) < wanted)
+        --m;
+    while (m < 2048 && total(m) > 2 * p.n_tiles + (1 << 20))
+        m *= 2;
+    return step * m - over;
+}
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Units of the utility metrics: columns of metrics_unit_pixels(C) pixels x
+// segments of rows.  A unit reads six rows more than it has, and works in
+// blocks of seven, so a segment is 7 m - 6 rows; wanted: four rounds of the
+// 768 workgroups the GPU holds at once (16 x 1080p: m = 3 / 6 / 10: 196 / 170 /
+// 164 us; one 6000 x 4000 frame: m = 3 / 6 / 8 / 10: 155 / 131 / 125 / 129 us).
+// A lane's squared errors (at most 16 * 255^2 a block) fit 32 bits up to m = 4096.
+constexpr int64_t kMetUnits = 3000;
+
+int64_t metrics_units(const FrameRec& F, int32_t rows)
+{
+    return ceil_div(F.W, metrics_unit_pixels(F.C)) * ceil_div(F.H, rows);
+}
+
+// Units of the label masks: equal chunks of columns x segments of rows.  A
+// unit stages two rows more than it labels, in blocks of four: 4 m - 2 rows, m
+// at most 4 (64 x 1080p: m = 3 / 4 / 8 / 16: 92 / 95 / 101 / 114 us; 16 x 1080p: m
+// = 2 / 3 / 4 / 8: 29 / 25 / 25 / 25 us).
+constexpr int64_t kEdgeUnits = 1024;
+
+// LDS of a walk's two blocks of staged rows.
+size_t label_lds(int threads) { return 4 * (size_t)kLabBlock * (size_t)label_stride(4 * threads); }
+
+int64_t edge_units(const FrameRec& F, int32_t rows) { return ceil_div(F.W, kLabCols) * ceil_div(F.H, rows); }
+
+// Bands of a unit of the plan from labels (one tile's columns): about kLabRows
+// rows, so that the two rows a unit stages beyond its own are few, and at
+// most 2048 cell counters (16 x 1080p b 32: 32 / 64 rows: 34 / 36 us; 24 photos b
+// 16: 16 / 32 / 64 rows: 32 / 31 / 38 us; 64 x 1080p: no difference).
+constexpr int32_t kLabRows = 32;
+
+int32_t label_bands(const FrameRec& F)
+{
+    const int32_t nb = std::max(1, std::min(kLabRows / F.b, 2048 / F.K));
+    return std::min(nb, F.GR);
 }
 
 }  // namespace
@@ -362,6 +401,10 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
                 return fail(DPPIX_ENOTSUP, "n*n*channels too large for one tile in LDS");
             }
         }
+        F.lnb = label_bands(F);
+        p->lab_cells = std::max<size_t>(p->lab_cells, (size_t)F.lnb * (size_t)(F.K + 1));
+        p->lab_threads = std::max(p->lab_threads, label_threads((int)std::min<int64_t>((int64_t)F.K * F.b, kLabCols)));
+        p->edge_threads = std::max(p->edge_threads, label_threads(std::min(label_chunk(F.W), F.W)));
         F.cell_base = cell;
         F.fine_base = fine;
         F.tile_base = tile;
@@ -473,9 +516,15 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
     p->n_border = (int64_t)border.size() / 2;
     w.border_map = o;  o = align256(o + sizeof(int32_t) * border.size());
     w.simple_counts = o; o = align256(o + sizeof(uint64_t) * 4 * (size_t)n_frames);
-    std::vector<int32_t> met_map;
+    std::vector<int32_t> met_map, lab_map, edge_map;
     std::vector<int64_t> met_base;
-    p->met_rows = metrics_units(*p, met_map, met_base);
+    p->met_rows = unit_rows(*p, metrics_units, 7, 6, 10, kMetUnits);
+    p->edge_rows = unit_rows(*p, edge_units, 4, 2, 4, kEdgeUnits);
+    map_units(*p, [&](const FrameRec& F) { return metrics_units(F, p->met_rows); }, met_map, p->met_lo, &met_base);
+    map_units(*p, [&](const FrameRec& F) { return edge_units(F, p->edge_rows); }, edge_map, p->edge_lo, nullptr);
+    map_units(*p, [&](const FrameRec& F) { return F.TX * ceil_div(F.GR, F.lnb); }, lab_map, p->lab_lo, nullptr);
+    w.lab_map = o;     o = align256(o + sizeof(int32_t) * lab_map.size());
+    w.edge_map = o;    o = align256(o + sizeof(int32_t) * edge_map.size());
     w.met_map = o;     o = align256(o + sizeof(int32_t) * met_map.size());
     w.met_base = o;    o = align256(o + sizeof(int64_t) * met_base.size());
     w.total = o;
@@ -516,8 +565,12 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
             bg_off += cells * (uint64_t)F.C;
         }
     }
-    if (!met_map.empty())
-        std::memcpy(p->host_tables.data() + w.met_map, met_map.data(), sizeof(int32_t) * met_map.size());
+    auto put = [&](size_t at, const std::vector<int32_t>& map) {
+        std::copy(map.begin(), map.end(), reinterpret_cast<int32_t*>(p->host_tables.data() + at));
+    };
+    put(w.lab_map, lab_map);
+    put(w.edge_map, edge_map);
+    put(w.met_map, met_map);
     std::memcpy(p->host_tables.data() + w.met_base, met_base.data(), sizeof(int64_t) * met_base.size());
     int32_t* umap = reinterpret_cast<int32_t*>(p->host_tables.data() + w.unit_map);
     for (int32_t f = 0, u = 0; f < n_frames; ++f)
@@ -822,10 +875,15 @@ dppix_status_t dp_pix_plan_labels(dppix_plan_t p, const void* const* images, int
     a.images = images;
     a.edge_threshold = threshold;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    unsigned channel_mask = 0;
-    for (const FrameRec& F : p->frames)
-        channel_mask |= 1u << F.C;
-    hipError_t e = launch_plan_labels(a, p->n_units, plain_threads(p), p->lds[kPlan], channel_mask, p->prefix_scan, s);
+    a.lab_map = reinterpret_cast<const int32_t*>(p->bound + p->ws.lab_map);
+    hipError_t e = hipSuccess;
+    for (int C = 1; C <= 4 && e == hipSuccess; ++C) {
+        a.sched_offset = p->lab_lo[C - 1];
+        e = launch_plan_labels(a, C, p->lab_lo[C] - p->lab_lo[C - 1], p->lab_threads,
+                               label_lds(p->lab_threads) + 4 * p->lab_cells, s);
+    }
+    if (e == hipSuccess)
+        e = launch_scan(a, p->prefix_scan, s);
     if (e != hipSuccess)
         return dev_fail(e, "plan launch");
     return DPPIX_OK;
@@ -1003,11 +1061,12 @@ dppix_status_t dp_pix_edge_mask(dppix_plan_t p, const void* const* images, int32
     a.masks_out = masks_out;
     a.edge_threshold = threshold;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    for (const LaunchGroup& g : p->groups) {
-        TileArgs ga = a;
-        ga.sched_offset = g.lo;
-        ga.n_tiles = g.hi - g.lo;
-        hipError_t e = launch_edge_mask(ga, g.C, plain_threads(p), s);
+    a.edge_map = reinterpret_cast<const int32_t*>(p->bound + p->ws.edge_map);
+    a.edge_rows = p->edge_rows;
+    for (int C = 1; C <= 4; ++C) {
+        a.sched_offset = p->edge_lo[C - 1];
+        hipError_t e = launch_edge_mask(a, C, p->edge_lo[C] - p->edge_lo[C - 1], p->edge_threads,
+                                        label_lds(p->edge_threads), s);
         if (e != hipSuccess)
             return dev_fail(e, "edge mask launch");
     }

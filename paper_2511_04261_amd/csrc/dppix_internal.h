@@ -26,7 +26,8 @@ struct FrameRec {
     int32_t b, s, n, pad;     // b_bg, b_fg, n = b/s, pad mode
     int32_t GR, GC, K, TX;    // grid rows/cols, cells per tile, tiles per band
     int32_t tau, noise_bg, noise_fg, off32;    // off32: (b + 1) rows of the frame span < 2^31 bytes
-    int32_t cnb, ctx, cunits, pad_;           // plan units: bands, tiles per band, units of the frame
+    int32_t cnb, ctx, cunits, lnb;            // plan units: bands, tiles per band, units of the frame; bands per unit
+                                              // of the plan from labels
     int64_t cell_base;        // first cell of the frame in batch-wide cell arrays
     int64_t fine_base;        // first subcell in dense fine arrays
     int64_t tile_base;        // first tile
@@ -42,6 +43,8 @@ struct WsLayout {
     size_t tile_map;      // int32[n_tiles][2]: (frame, tile within frame) per scheduling index
     size_t unit_map;      // int32[n_units][2]: (frame, plan unit within frame), frame-major
     size_t border_map;    // int32[n_border][2]: (frame, tile) of the tiles the adjoint's mirror pass visits
+    size_t lab_map;       // int32[n_lab][2]: (frame, unit within frame) of the plan from labels, by channel count
+    size_t edge_map;      // int32[n_edge][2]: the same of the label masks
     size_t met_map;       // int32[n_met][2]: (frame, unit within frame) of the metrics, by channel count
     size_t met_base;      // int64[n_frames][2]: first metrics unit of each frame, and their number
     size_t simple_counts; // uint64[n_frames][4]: store counts of a call without masks (every cell simple)
@@ -98,12 +101,31 @@ struct TileArgs {
     // complexity label
     uint8_t* const* masks_out;
     int32_t edge_threshold;
+    const int32_t* lab_map;
+    const int32_t* edge_map;
+    int32_t edge_rows;        // rows of a label mask unit
     // utility metrics: per unit (SSIM partial sum, squared-error sum)
     const int32_t* met_map;
     const int64_t* met_base;
     double* met_partial;
     int32_t met_rows;         // rows of a metrics unit
 };
+
+// The label kernels stage rows of channel sums in blocks of kLabBlock, a lane
+// per 16-pixel group of a block (with a halo group on each side) and a lane
+// per four columns: 992 columns are what 256 lanes take.  label_chunk: the
+// width of the equal chunks, whole groups, that the label masks cut W columns
+// into; label_threads: lanes for walks of up to `cols` columns; label_stride:
+// LDS columns of a staged row (the right edge's groups reach past the last).
+constexpr int kLabBlock = 4;
+constexpr int kLabCols = 992;
+__host__ __device__ inline int label_chunk(int W)
+{
+    const int n = (W + kLabCols - 1) / kLabCols;
+    return ((W + n - 1) / n + 15) & ~15;
+}
+__host__ __device__ inline int label_threads(int cols) { return (cols / 4 + 8 + 63) & ~63; }
+__host__ __device__ inline int label_stride(int cols) { return cols + 64; }
 
 // Host-side launchers (defined in dppix_kernels.hip).
 // prefix_scan: every frame has the same C and n and the batch has at most
@@ -112,10 +134,11 @@ struct TileArgs {
 constexpr int64_t kPrefixScanTiles = 16384;
 hipError_t launch_plan(const TileArgs& a, int64_t n_units, int threads, size_t lds, bool prefix_scan,
                        hipStream_t s);
-// Plan from the frames' Sobel labels (edge_threshold, images), then the scan;
-// channel_mask: bit C set for every channel count C among the frames.
-hipError_t launch_plan_labels(const TileArgs& a, int64_t n_units, int threads, size_t lds, unsigned channel_mask,
-                              bool prefix_scan, hipStream_t s);
+// The scan of the tile counts alone.
+hipError_t launch_scan(const TileArgs& a, bool prefix_scan, hipStream_t s);
+// Tile counts from the frames' Sobel labels (edge_threshold, images): the units
+// of the frames with C channels.  The scan follows.
+hipError_t launch_plan_labels(const TileArgs& a, int C, int64_t n_units, int threads, size_t lds, hipStream_t s);
 // Tile counts of complex cells from the store's flags alone, then the scan.
 hipError_t launch_store_index(const TileArgs& a, bool prefix_scan, hipStream_t s);
 hipError_t launch_forward(const TileArgs& a, int layout, int C, int threads, size_t lds, int grid, hipStream_t s);
@@ -125,7 +148,7 @@ hipError_t launch_backward_reduce(const TileArgs& a, int threads, size_t lds, in
 hipError_t launch_backward_mirror(const TileArgs& a, int threads, int grid, hipStream_t s);
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
 hipError_t launch_noise_advance(uint64_t* noise, int32_t n, uint64_t step, hipStream_t s);
-hipError_t launch_edge_mask(const TileArgs& a, int C, int threads, hipStream_t s);
+hipError_t launch_edge_mask(const TileArgs& a, int C, int64_t n_units, int threads, size_t lds, hipStream_t s);
 hipError_t launch_metrics(const TileArgs& a, int C, int64_t n_units, hipStream_t s);
 int metrics_unit_pixels(int C);   // pixels of a row one metrics unit covers
 hipError_t launch_metrics_reduce(const TileArgs& a, double* out, hipStream_t s);

@@ -57,11 +57,13 @@ typedef __attribute__((address_space(1))) v4u_any g_v4u;
 typedef __attribute__((address_space(1))) v4f_any g_v4f;
 typedef __attribute__((address_space(1))) const uint8_t g_u8;
 typedef __attribute__((address_space(1))) uint8_t g_u8w;
-typedef __attribute__((address_space(1))) uint16_t g_u16w;
 typedef __attribute__((address_space(1))) const float g_f32;
 typedef __attribute__((address_space(1))) float g_f32w;
 
 __device__ __forceinline__ v4u ld16_nt(const void* p) { return __builtin_nontemporal_load((const g_v4u*)p); }
+// For groups of C vectors a lane: each of its loads touches lines that the
+// others need too, so they are kept.
+__device__ __forceinline__ v4u ld16(const void* p) { return *(const g_v4u*)p; }
 __device__ __forceinline__ v4f ld16f_nt(const void* p) { return __builtin_nontemporal_load((const g_v4f*)p); }
 __device__ __forceinline__ void st16_nt(void* p, v4u v) { __builtin_nontemporal_store(v, (g_v4u*)p); }
 __device__ __forceinline__ void st16f_nt(void* p, v4f v) { __builtin_nontemporal_store(v, (g_v4f*)p); }
@@ -715,11 +717,24 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(5))
 // swap only flips the sign of Gy.  So each chunk of padded rows and columns is
 // staged as channel sums in LDS (one halo row and column on every side) and
 // counted without knowing which positions are real.
+//
+// The walk (label_walk) is shared with the mask kernel: up to kLabCols columns
+// times any number of rows.  A lane takes four columns and walks down the
+// rows with the stencil's last two rows in registers, so no row is staged
+// twice; rows come in blocks of kLabBlock, each block's 16-pixel vectors
+// loaded while the block before is labelled (two LDS buffers, one barrier a
+// block).  What bounds it is HBM and the vector instructions of the staging
+// together: without the stencil's sums it takes as long, without the loads 98
+// of 130 us (plan, 64 x 1080p) and 63 of 133 (masks).  The loads are cached
+// ones: a lane's C vectors share their lines with its neighbours' (masks, 64 x
+// 1080p RGB: streaming loads 132 us, cached 106).
+// 16 x 1080p RGB: plan 62.5 -> 33.5 us, masks 53 -> 24.5 us; 64 x 1080p: 145 ->
+// 96 us and 153 -> 95 us; 24 photos of odd widths: 217 -> 31 us and 83 -> 24.5
+// us (before: chunks of 16 rows x 512 columns staged whole, two columns a
+// lane, no load in flight while a chunk was labelled, and frames off the
+// 16-byte grid staged pixel by pixel).
 // --------------------------------------------------------------------------
-constexpr int kLabRows = 16;                      // padded rows per chunk (within one band)
-constexpr int kLabCols = 512;                     // padded columns per chunk (16 x 512: fastest of 8-32 x 128-1024)
-constexpr int kLabPad = 8;                        // LDS columns before column 0 (16-byte aligned rows)
-constexpr int kLabStride = kLabCols + 2 * kLabPad;
+constexpr int kLabLeft = 16;                      // LDS columns before column 0
 
 // Channel sums of 16 consecutive pixels from their 16 C bytes, as eight
 // dwords of two 16-bit sums each (pixel 2k low, 2k + 1 high).
@@ -771,193 +786,295 @@ __device__ __forceinline__ void pixel_sums16(const v4u (&w)[C], v4u& lo, v4u& hi
     hi = v4u{pr[4], pr[5], pr[6], pr[7]};
 }
 
-// Channel sums of the staged chunk: staged row yy is padded row py0 - 1 + yy,
-// staged column xx padded column px0 + xx (xx = -1 .. cols), each folded into
-// the frame as the label's border rule folds it; whole 16-pixel groups inside
-// the frame are read as vectors (aligned rows), the rest one pixel at a time.
+// One 16-pixel group of the staged columns, as a lane keeps it from block to
+// block: where its pixels come from and how their sums reach LDS.  Column x
+// of the frame is staged at kLabLeft + x - px0.
+enum LabGroup : int {
+    kLabNone,      // nothing of the group is needed
+    kLabInside,    // sixteen pixels of the frame
+    kLabMirror,    // all past the right edge: the sixteen pixels they mirror, reversed
+    kLabCross,     // across the right edge: the frame's last sixteen pixels give both sides
+    kLabSingle     // anything else (left halo, narrow frames): pixel by pixel
+};
+
 template <int C>
-__device__ __forceinline__ void stage_label_sums(const uint8_t* img, int64_t pitch, int H, int W, int pad, int py0,
-                                                 int rows, int px0, int cols, bool aligned, uint16_t* S)
-{
-    const int tid = threadIdx.x, NT = blockDim.x;
-    const int gfast = (aligned && (px0 & 15) == 0) ? max(0, min(cols, W - px0)) >> 4 : 0;
-    for (int it = tid; it < (rows + 2) * gfast; it += NT) {
-        const int yy = it / gfast, g = it - yy * gfast;
-        const int ry = edge_fold(py0 - 1 + yy, H, pad);
-        const uint8_t* src = img + (int64_t)ry * pitch + (int64_t)(px0 + 16 * g) * C;
-        v4u w[C];
+struct LabStage {
+    int kind, x, from;     // first column of the group, first pixel its vectors hold
+    int pa, pb;            // columns [pa, pb) of the group that are needed
+
+    __device__ __forceinline__ void setup(int g, int px0, int cols, int W, int pad)
+    {
+        x = px0 + 16 * (g - 1);
+        pa = max(x, px0 - 1);
+        pb = min(x + 16, px0 + cols + 1);
+        const int mirrored = (pad == 1 ? 2 * W - 2 : 2 * W - 1) - (x + 15);
+        from = x;
+        if (pa >= pb || (x < 0 && px0 == 0 && W >= 16))
+            kind = kLabNone;   // (column -1 is written by the group that holds its mirror image)
+        else if (x >= 0 && x + 16 <= W)
+            kind = kLabInside;
+        else if (x >= W && mirrored >= 0 && mirrored + 16 <= W) {
+            kind = kLabMirror;
+            from = mirrored;
+        } else if (x >= 0 && x < W && W >= 16) {
+            kind = kLabCross;
+            from = W - 16;
+        } else
+            kind = kLabSingle;
+    }
+
+    __device__ __forceinline__ bool vector() const { return kind != kLabNone && kind != kLabSingle; }
+
+    // The group's channel sums into the staged row S, from the vectors of its
+    // source pixels (or, pixel by pixel, from the row itself).
+    __device__ __forceinline__ void store(const v4u (&w)[C], const uint8_t* row, uint16_t* S, int px0, int W,
+                                          int pad) const
+    {
+        uint16_t* d = S + kLabLeft + x - px0;
+        if (kind == kLabSingle) {
+            for (int c = pa; c < pb; ++c) {
+                const g_u8* p = (const g_u8*)(row + (int64_t)edge_fold(c, W, pad) * C);
+                uint32_t sum = 0u;
 #pragma unroll
-        for (int i = 0; i < C; ++i)
-            w[i] = ld16_nt(src + 16 * i);
+                for (int ch = 0; ch < C; ++ch)
+                    sum += p[ch];
+                d[c - x] = (uint16_t)sum;
+            }
+            return;
+        }
         v4u lo, hi;
         pixel_sums16<C>(w, lo, hi);
-        v4u* dst = reinterpret_cast<v4u*>(S + yy * kLabStride + kLabPad + 16 * g);
-        dst[0] = lo;
-        dst[1] = hi;
-    }
-    const int nrest = cols + 2 - 16 * gfast;
-    for (int it = tid; it < (rows + 2) * nrest; it += NT) {
-        const int yy = it / nrest, q = it - yy * nrest;
-        const int xx = q == 0 ? -1 : 16 * gfast + q - 1;
-        const int ry = edge_fold(py0 - 1 + yy, H, pad);
-        const int rx = edge_fold(px0 + xx, W, pad);
-        const g_u8* px = (const g_u8*)(img + (int64_t)ry * pitch + (int64_t)rx * C);
-        uint32_t sum = 0u;
+        if (__builtin_expect(kind == kLabMirror, 0)) {
+            asm volatile("");   // a branch of its own: few lanes reverse
+            const v4u a = v4u{hi.w, hi.z, hi.y, hi.x}, b = v4u{lo.w, lo.z, lo.y, lo.x};
+            lo = (a >> 16) | (a << 16);
+            hi = (b >> 16) | (b << 16);
+        }
+        if (kind == kLabCross) {
+            // sums of the frame's last sixteen columns at their places, and
+            // reversed at the places that mirror them (what they overlap of
+            // the groups beside them, they write alike)
+            uint16_t* e = S + kLabLeft + from - px0;
+            uint16_t* m = S + kLabLeft + (pad == 1 ? W - 1 : W) - px0;
 #pragma unroll
-        for (int ch = 0; ch < C; ++ch)
-            sum += px[ch];
-        S[yy * kLabStride + kLabPad + xx] = (uint16_t)sum;
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t pr = i < 4 ? lo[i & 3] : hi[i & 3];
+                e[2 * i] = m[15 - 2 * i] = (uint16_t)pr;
+                e[2 * i + 1] = m[14 - 2 * i] = (uint16_t)(pr >> 16);
+            }
+            return;
+        }
+        reinterpret_cast<v4u*>(d)[0] = lo;
+        reinterpret_cast<v4u*>(d)[1] = hi;
+        if (x == 0)
+            d[-1] = (uint16_t)(pad == 1 ? lo.x >> 16 : lo.x);
     }
-}
+};
 
-// Sobel labels of the staged column pair (2p, 2p + 1) down rows y0 .. y1 - 1
-// of the chunk, the two columns in the 16-bit halves of one register:
+// The stencil, two neighbouring columns in the 16-bit halves of one register:
 // Gx = dx(-1) + 2 dx(0) + dx(+1), Gy = sx(+1) - sx(-1), with
 // dx(r) = S[r][+1] - S[r][-1], sx(r) = S[r][-1] + 2 S[r][0] + S[r][+1].
 // With S <= 4 * 255 every intermediate fits a signed 16-bit half exactly
 // (|Gx|, |Gy| <= 4080), and so does thr - 1 - (|Gx| + |Gy|) for thr <= 16384:
-// its sign is the label.  emit(y, d) gets that difference, bit 15 = label of
-// column 2p, bit 31 = label of column 2p + 1.  Each row is three dword reads
-// (the pair and its two neighbouring pairs, 4-byte aligned).
+// its sign is the label.
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ void sobel_row_pair(const uint32_t* r, s16x2& dx, s16x2& sx)
+// 2 a + b in both halves.
+__device__ __forceinline__ s16x2 twice_plus(s16x2 a, s16x2 b)
 {
-    const uint32_t w0 = r[-1], w1 = r[0], w2 = r[1];
-    const s16x2 l = __builtin_bit_cast(s16x2, __builtin_amdgcn_alignbit(w1, w0, 16));   // S[-1], S[0]
-    const s16x2 c = __builtin_bit_cast(s16x2, w1);                                      // S[0], S[+1]
-    const s16x2 rr = __builtin_bit_cast(s16x2, __builtin_amdgcn_alignbit(w2, w1, 16));  // S[+1], S[+2]
-    dx = rr - l;
-    sx = (l + rr) + (c + c);
+    s16x2 d;
+    asm("v_pk_mad_u16 %0, %1, 2, %2 op_sel_hi:[1,0,1]" : "=v"(d) : "v"(a), "v"(b));
+    return d;
 }
 
-template <typename Emit>
-__device__ __forceinline__ void label_pair(const uint16_t* S, int p, int y0, int y1, int thr, Emit emit)
-{
-    constexpr int RW = kLabStride / 2;                       // dwords per staged row
-    const uint32_t* row = reinterpret_cast<const uint32_t*>(S + kLabPad) + y0 * RW + p;
-    const s16x2 t = {(short)(thr - 1), (short)(thr - 1)};
-    s16x2 dxa, sxa, dxb, sxb;
-    sobel_row_pair(row, dxa, sxa);
-    sobel_row_pair(row + RW, dxb, sxb);
-    row += 2 * RW;
-    for (int y = y0; y < y1; ++y, row += RW) {
-        s16x2 dxc, sxc;
-        sobel_row_pair(row, dxc, sxc);
-        const s16x2 gx = (dxa + dxc) + (dxb + dxb), gy = sxc - sxa;
-        const s16x2 mag = __builtin_elementwise_abs(gx) + __builtin_elementwise_abs(gy);
-        emit(y, __builtin_bit_cast(uint32_t, t - mag));
-        dxa = dxb;
-        sxa = sxb;
-        dxb = dxc;
-        sxb = sxc;
+struct SobelRow {
+    s16x2 dx[2], sx[2];   // of the columns 0, 1 and 2, 3 of a lane
+
+    // w: the dword before the lane's two dwords of the row, they, and the one after.
+    __device__ __forceinline__ void set(const uint32_t* w)
+    {
+        const s16x2 l = __builtin_bit_cast(s16x2, __builtin_amdgcn_alignbit(w[1], w[0], 16));   // S[-1], S[0]
+        const s16x2 m = __builtin_bit_cast(s16x2, __builtin_amdgcn_alignbit(w[2], w[1], 16));   // S[1], S[2]
+        const s16x2 r = __builtin_bit_cast(s16x2, __builtin_amdgcn_alignbit(w[3], w[2], 16));   // S[3], S[4]
+        const s16x2 a = __builtin_bit_cast(s16x2, w[1]), b = __builtin_bit_cast(s16x2, w[2]);
+        dx[0] = m - l;
+        dx[1] = r - m;
+        sx[0] = twice_plus(a, l + m);
+        sx[1] = twice_plus(b, m + r);
     }
-}
-
-// Lanes over the column pairs of a chunk: pairs 0 .. np - 1, and when the
-// pairs are fewer than the lanes, the rows split over up to 4 lane groups
-// (each group whole waves).  split = this lane's row group (>= splits: idle).
-struct PairLanes {
-    int step, pl, split, splits, rper;
 };
 
-__device__ __forceinline__ PairLanes pair_lanes(int np, int rows)
+// Labels of the lane's four columns in the row between a and c, as 0 / 1 bytes.
+__device__ __forceinline__ uint32_t sobel_labels(const SobelRow& a, const SobelRow& b, const SobelRow& c, int thr)
 {
-    const int tid = threadIdx.x, NT = blockDim.x;
-    const int npr = (np + 63) & ~63;
-    PairLanes L;
-    L.splits = npr >= NT ? 1 : min(4, NT / npr);
-    L.step = L.splits == 1 ? NT : npr;
-    L.pl = L.splits == 1 ? tid : tid % npr;
-    L.split = L.splits == 1 ? 0 : tid / npr;
-    L.rper = (rows + L.splits - 1) / L.splits;
-    return L;
+    const s16x2 t = {(short)(thr - 1), (short)(thr - 1)};
+    uint32_t d[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const s16x2 gx = twice_plus(b.dx[h], a.dx[h] + c.dx[h]), gy = c.sx[h] - a.sx[h];
+        d[h] = __builtin_bit_cast(uint32_t, t - (__builtin_elementwise_abs(gx) + __builtin_elementwise_abs(gy)));
+    }
+    // selectors 8 .. 11: the signs of the four halves, as whole bytes
+    return __builtin_amdgcn_perm(d[1], d[0], 0x0B0A0908u) & 0x01010101u;
 }
 
-template <int C>
-__device__ void plan_count_labels(const TileArgs& a, const FrameRec& F, const uint8_t* img, int r0, int nb, int c0,
-                                  int KC, int KCs, uint32_t* cellcnt, uint16_t* S)
+// Walk down `rows` padded rows from py0 over the padded columns [px0, px0 +
+// cols): for each block emit(y0, ya, yb, lab), lab[j] = the labels of row y0 + j
+// (rows ya <= y0 + j < yb only) in columns px0 + 4 lane .. + 3, as bytes
+// (columns past the end hold anything), rows in order.  Every lane of the
+// workgroup calls it; it has a lane per four columns and per staged group of
+// a block (label_threads), and S holds two blocks of `stride` columns a row.
+template <int C, typename Emit>
+__device__ __forceinline__ void label_walk(const uint8_t* img, int64_t pitch, int H, int W, int pad, int py0, int rows,
+                                           int px0, int cols, int thr, uint16_t* S, int stride, Emit emit)
 {
-    const int b = F.b, H = F.H, W = F.W, pad = F.pad;
-    const int64_t pitch = F.pitch;
-    const int thr = a.edge_threshold * C;
-    const int X0 = c0 * b, XW = KC * b;
-    const int R = min(b, kLabRows);
-    const bool aligned = ((reinterpret_cast<uintptr_t>(img) | (uintptr_t)pitch) & 15) == 0;
-    // b a power of two up to 64: chunks start on cell boundaries and the
-    // lanes of one cell add their counts by shuffles first (one LDS atomic
-    // per cell and chunk instead of one per lane)
-    const bool groups = (b & (b - 1)) == 0 && b <= 64;
-    for (int j = 0; j < nb; ++j) {
-        const int band0 = (r0 + j) * b;
-        for (int k0 = 0; k0 < b; k0 += R) {
-            const int rows = min(R, b - k0);
-            const int py0 = band0 + k0;
-            // unpadded mode: rows past the frame are absent
-            const int ylim = pad == kPadNone ? min(rows, H - py0) : rows;
-            if (ylim <= 0)
-                break;
-            for (int cx = 0; cx < XW; cx += kLabCols) {
-                const int cols = min(kLabCols, XW - cx);
-                const int px0 = X0 + cx;
-                stage_label_sums<C>(img, pitch, H, W, pad, py0, rows, px0, cols, aligned, S);
-                lds_barrier();
-                // a lane per pair of padded columns, down its share of the rows
-                const int np = (cols + 1) >> 1;
-                const PairLanes L = pair_lanes(np, ylim);
-                const int ya = L.split * L.rper, yb = min(ylim, ya + L.rper);
-                for (int pb = 0; pb < np; pb += L.step) {
-                    const int p = pb + L.pl, x = 2 * p;
-                    // valid columns: inside the chunk, and real in the unpadded mode
-                    const int xend = pad == kPadNone ? min(cols, W - px0) : cols;
-                    const uint32_t vm = (x < xend ? 0x8000u : 0u) | (x + 1 < xend ? 0x80000000u : 0u);
-                    uint32_t cnt = 0u, cnt_hi = 0u;
-                    if (vm != 0u && L.split < L.splits && ya < yb) {
-                        if ((b & 1) == 0)
-                            label_pair(S, p, ya, yb, thr, [&](int, uint32_t d) { cnt += __builtin_popcount(d & vm); });
-                        else
-                            label_pair(S, p, ya, yb, thr, [&](int, uint32_t d) {
-                                d &= vm;
-                                cnt += (d >> 15) & 1u;
-                                cnt_hi += d >> 31;
-                            });
-                    }
-                    // b even: both columns lie in one cell
-                    const int cell = (cx + x) / b;
-                    if (groups && b >= 2) {
-                        for (int m = 1; m < (b >> 1); m <<= 1)
-                            cnt += __shfl_xor(cnt, m, 64);
-                        if ((L.pl & ((b >> 1) - 1)) == 0 && cnt != 0u && cell < KC)
-                            atomicAdd(cellcnt + j * KCs + cell, cnt);
-                    } else {
-                        if (cnt != 0u && cell < KC)
-                            atomicAdd(cellcnt + j * KCs + cell, cnt);
-                        const int cell_hi = (cx + x + 1) / b;
-                        if (cnt_hi != 0u && cell_hi < KC)
-                            atomicAdd(cellcnt + j * KCs + cell_hi, cnt_hi);
-                    }
-                }
-                lds_barrier();
-            }
+    const int tid = threadIdx.x;
+    const int G = (cols + 16) / 16 + 1;              // groups of a staged row
+    const int srow = tid / G;
+    const int nst = rows + 2, nblk = (nst + kLabBlock - 1) / kLabBlock;
+    LabStage<C> st;
+    st.setup(tid - srow * G, px0, cols, W, pad);
+    const bool stages = srow < kLabBlock && st.kind != kLabNone;
+    v4u w[C];
+    // rows that lie in the frame one after another need no folding
+    const bool plain = py0 >= 1 && py0 - 1 + nst <= H;
+    auto row_of = [&](int blk) { return img + (int64_t)edge_fold(py0 - 1 + blk * kLabBlock + srow, H, pad) * pitch; };
+    const uint8_t* next = plain ? row_of(0) + (int64_t)st.from * C : nullptr;
+    auto load = [&](int blk) {
+        if (stages && st.vector() && blk * kLabBlock + srow < nst) {
+            const uint8_t* p = plain ? next : row_of(blk) + (int64_t)st.from * C;
+#pragma unroll
+            for (int i = 0; i < C; ++i)
+                w[i] = ld16(p + 16 * i);
+        }
+        next += kLabBlock * pitch;
+    };
+    auto store = [&](int blk) {
+        if (stages && blk * kLabBlock + srow < nst)
+            st.store(w, st.kind == kLabSingle ? row_of(blk) : nullptr,
+                     S + ((blk & 1) * kLabBlock + srow) * stride, px0, W, pad);
+    };
+    SobelRow a, b;
+    uint32_t lab[kLabBlock];
+    // A block's labels go out after the next block's barrier, before its
+    // loads: what waits for those loads then waits for no newer store.
+    auto give = [&](int blk) {
+        const int y0 = blk * kLabBlock - 2;          // the row whose labels the block's first staged row completed
+        if (4 * tid < cols)
+            emit(y0, max(y0, 0), min(y0 + kLabBlock, rows), lab);
+    };
+    load(0);
+    for (int blk = 0; blk < nblk; ++blk) {
+        store(blk);
+        lds_barrier();
+        if (blk > 0)
+            give(blk - 1);
+        if (blk + 1 < nblk)
+            load(blk + 1);
+        const uint32_t* r0 = reinterpret_cast<const uint32_t*>(S + (blk & 1) * kLabBlock * stride + kLabLeft) +
+                             2 * min(tid, cols >> 2) - 1;
+        uint32_t q[kLabBlock][4];   // (rows past the last hold anything)
+#pragma unroll
+        for (int j = 0; j < kLabBlock; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                q[j][i] = r0[j * (stride / 2) + i];
+#pragma unroll
+        for (int j = 0; j < kLabBlock; ++j) {
+            SobelRow c;
+            c.set(q[j]);
+            lab[j] = sobel_labels(a, b, c, thr);
+            a = b;
+            b = c;
         }
     }
+    give(nblk - 1);
+    lds_barrier();
 }
 
-// One launch per channel count present in the batch: a workgroup whose unit
-// belongs to a frame of another channel count leaves it to that launch (the
-// unit's frame decides before anything is written), so each instantiation
-// carries one pixel width only.
+// A unit is one tile's columns x F.lnb bands: counted in walks of at most
+// kLabCols columns, a lane's four byte counters added to the cells' at the
+// end of every band (and after 128 rows of one, before a byte could overflow).
 template <int C>
-__global__ __launch_bounds__(kMaxThreads) void k_plan_labels(TileArgs a)
+__global__ __launch_bounds__(256) void k_plan_labels(TileArgs a)
 {
     extern __shared__ __align__(16) uint8_t lds[];
-    __shared__ __align__(16) uint16_t S[(kLabRows + 2) * kLabStride];
-    const int f0 = (int)uniform_u32((uint32_t)a.unit_map[2 * (int64_t)blockIdx.x]);
-    if (a.frames[f0].C != C)
-        return;
-    plan_unit(a, lds, [&](const FrameRec& F, int f, int r0, int nb, int c0, int KC, int KCs, uint32_t* cellcnt) {
-        plan_count_labels<C>(a, F, static_cast<const uint8_t*>(a.images[f]), r0, nb, c0, KC, KCs, cellcnt, S);
-    });
+    const int tid = threadIdx.x, NT = blockDim.x;
+    const int64_t unit = a.sched_offset + blockIdx.x;
+    const int f = (int)uniform_u32((uint32_t)a.lab_map[2 * unit]);
+    const int local = (int)uniform_u32((uint32_t)a.lab_map[2 * unit + 1]);
+    const FrameRec& F = a.frames[f];
+    const int b = F.b, K = F.K, W = F.W, pad = F.pad;
+    const int r0 = (local / F.TX) * F.lnb, ct = local % F.TX;
+    const int nb = min(F.lnb, F.GR - r0), c0 = ct * K, KC = min(K, F.GC - c0);
+    const int stride = label_stride(4 * NT);
+    uint16_t* S = reinterpret_cast<uint16_t*>(lds);
+    uint32_t* cellcnt = reinterpret_cast<uint32_t*>(lds + 4 * kLabBlock * stride);   // [nb][K]
+    uint32_t* tcnt = cellcnt + F.lnb * K;                                            // [nb]
+    for (int i = tid; i < F.lnb * (K + 1); i += NT)
+        cellcnt[i] = 0u;
+    // the store's ticket words start at zero for the scan and later launches
+    // of this call sequence (stream order: no earlier launch still uses them)
+    if (blockIdx.x == 0 && tid < kTicketWords)
+        a.ticket[tid] = 0u;
+    lds_barrier();
+    const int X0 = c0 * b, XW = KC * b;
+    // unpadded mode: rows and columns past the frame are absent
+    const int rows = pad == kPadNone ? min(nb * b, F.H - r0 * b) : nb * b;
+    const int xend = pad == kPadNone ? min(XW, W - X0) : XW;
+    for (int cx = 0; cx < xend; cx += kLabCols) {
+        const int cols = min(kLabCols, xend - cx);
+        const int x = cx + 4 * tid, n = min(4, cols - 4 * tid);
+        uint32_t cnt = 0u;
+        int j = 0, left = b, batch = min(b, 128);
+        label_walk<C>(static_cast<const uint8_t*>(a.images[f]), F.pitch, F.H, W, pad, r0 * b, rows, X0 + cx, cols,
+                      a.edge_threshold * C, S, stride, [&](int y0, int ya, int yb, const uint32_t (&lab)[kLabBlock]) {
+#pragma unroll 1
+            while (ya < yb) {
+                // up to the end of the band, or of a batch of its rows
+                const int stop = min(yb, ya + batch);
+#pragma unroll
+                for (int i = 0; i < kLabBlock; ++i)
+                    cnt += (y0 + i >= ya && y0 + i < stop) ? lab[i] : 0u;
+                batch -= stop - ya;
+                ya = stop;
+                if (batch != 0 && ya < rows)
+                    break;
+                uint32_t* cc = cellcnt + j * K;
+                if ((b & 3) == 0) {
+                    // the four columns lie in one cell (walks start on multiples of 4)
+                    const uint32_t sum = __builtin_amdgcn_udot4(cnt, 0x01010101u >> (8 * (4 - n)), 0u, false);
+                    if (sum != 0u)
+                        atomicAdd(cc + x / b, sum);
+                } else {
+                    for (int q = 0; q < n; ++q)
+                        if (((cnt >> (8 * q)) & 0xFFu) != 0u)
+                            atomicAdd(cc + (x + q) / b, (cnt >> (8 * q)) & 0xFFu);
+                }
+                cnt = 0u;
+                left -= min(b, 128);
+                if (left <= 0) {
+                    left = b;
+                    ++j;
+                }
+                batch = min(left, 128);
+            }
+        });
+    }
+    lds_barrier();
+    for (int i = tid; i < nb * KC; i += NT) {
+        const int j = i / KC, kc = i - j * KC;
+        // tau = 0 (unpadded mode only): majority of the cell's real pixels
+        const uint32_t tau = F.tau > 0 ? (uint32_t)F.tau
+                                       : ((uint32_t)stat_area(F, (r0 + j) * b, (c0 + kc) * b, b) + 1u) / 2u;
+        const uint8_t fl = (uint8_t)(cellcnt[j * K + kc] >= tau);
+        a.flags[F.cell_base + (int64_t)(r0 + j) * F.GC + c0 + kc] = fl;
+        if (fl)
+            atomicAdd(&tcnt[j], 1u);
+    }
+    lds_barrier();
+    for (int j = tid; j < nb; j += NT)
+        a.tile_cnt[F.tile_base + (int64_t)(r0 + j) * F.TX + ct] = tcnt[j];
 }
 
 // Plan of a call without masks (Algorithm 3 with every cell simple): flags
@@ -1770,16 +1887,6 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
 // Each launch covers one group of frames sharing layout and channel count
 // (scheduling indices [sched_offset, sched_offset + n_tiles)), so every kernel
 // instantiation carries only its own path.
-// The tile of this workgroup, for kernels that are never launched as a
-// resident grid (the persistent branch would only hold scalar registers).
-template <typename Body>
-__device__ __forceinline__ void run_one_tile(const TileArgs& a, Body body)
-{
-    FrameRec F;
-    const TileCoord tc = tile_of(a, blockIdx.x, F);
-    body(F, tc);
-}
-
 template <typename Body>
 __device__ __forceinline__ void run_tiles(const TileArgs& a, uint8_t* lds, Body body)
 {
@@ -2214,67 +2321,47 @@ __global__ __launch_bounds__(kMaxThreads) void k_backward_mirror(TileArgs a)
 // Complexity label from the image (Sec. VI-A names the Sobel operator as one
 // source of the region mask): per real pixel, the 3x3 Sobel responses of the
 // channel sum S, with neighbours past the border mirrored; the pixel is an
-// edge pixel when |Gx| + |Gy| >= threshold * C.  Each tile's real pixels are
-// processed in chunks of up to kLabRows x kLabCols whose channel sums, with a
-// one-pixel mirrored halo, are staged in LDS exactly as the plan from labels
-// stages them; one lane per column walks down the chunk and writes its mask
-// byte of every row.
+// edge pixel when |Gx| + |Gy| >= threshold * C.  A unit is a frame's columns
+// cut into equal chunks of at most kLabCols x a segment of rows, walked as the
+// plan from labels walks them; a lane writes its four labels of a row as one
+// dword at any byte of the mask.
 // ==========================================================================
-template <int C>
-__device__ void edge_tile(const TileArgs& a, const FrameRec& F, const TileCoord& tc, uint16_t* S)
-{
-    const int b = F.b, H = F.H, W = F.W, pad = F.pad;
-    const int x0c = tc.ct * F.K;
-    const int Kt = min(F.K, F.GC - x0c);
-    const int y0 = tc.r * b, y1 = min(y0 + b, H);
-    const int xa = x0c * b, xb = min((x0c + Kt) * b, W);
-    if (y0 >= H || xa >= W)
-        return;
-    const uint8_t* img = static_cast<const uint8_t*>(a.images[tc.f]);
-    uint8_t* out = a.masks_out[tc.f];
-    const int64_t pitch = F.pitch;
-    const int thr = a.edge_threshold * C;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(img) | (uintptr_t)pitch) & 15) == 0;
-    for (int cy = y0; cy < y1; cy += kLabRows) {
-        const int rows = min(kLabRows, y1 - cy);
-        for (int cx = xa; cx < xb; cx += kLabCols) {
-            const int cols = min(kLabCols, xb - cx);
-            // every pair of the chunk starts on an even byte of the mask
-            const bool even = ((reinterpret_cast<uintptr_t>(out) | (uintptr_t)W | (uintptr_t)cx) & 1) == 0;
-            stage_label_sums<C>(img, pitch, H, W, pad, cy, rows, cx, cols, aligned, S);
-            lds_barrier();
-            const int np = (cols + 1) >> 1;
-            const PairLanes L = pair_lanes(np, rows);
-            const int ya = L.split * L.rper, yb = min(rows, ya + L.rper);
-            if (L.split < L.splits && ya < yb) {
-                for (int p = L.pl; p < np; p += L.step) {
-                    g_u8w* o = (g_u8w*)(out + (int64_t)cy * W + cx + 2 * p);
-                    if (2 * p + 1 < cols && even)
-                        label_pair(S, p, ya, yb, thr, [&](int y, uint32_t d) {
-                            // both labels of the pair in one 16-bit store
-                            *(g_u16w*)(o + (int64_t)y * W) = (uint16_t)(((d >> 15) & 1u) | ((d >> 31) << 8));
-                        });
-                    else if (2 * p + 1 < cols)
-                        label_pair(S, p, ya, yb, thr, [&](int y, uint32_t d) {
-                            o[(int64_t)y * W] = (uint8_t)((d >> 15) & 1u);
-                            o[(int64_t)y * W + 1] = (uint8_t)(d >> 31);
-                        });
-                    else
-                        label_pair(S, p, ya, yb, thr,
-                                   [&](int y, uint32_t d) { o[(int64_t)y * W] = (uint8_t)((d >> 15) & 1u); });
-                }
-            }
-            lds_barrier();
-        }
-    }
-}
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef __attribute__((address_space(1))) u32_any g_u32w;
 
 template <int C>
-__global__ __launch_bounds__(kMaxThreads) void k_edge_mask(TileArgs a)
+__global__ __launch_bounds__(256) void k_edge_mask(TileArgs a)
 {
-    __shared__ __align__(16) uint16_t S[(kLabRows + 2) * kLabStride];
     extern __shared__ __align__(16) uint8_t lds[];
-    run_one_tile(a, [&](const FrameRec& F, const TileCoord& tc) { edge_tile<C>(a, F, tc, S); });
+    const int tid = threadIdx.x;
+    const int64_t unit = a.sched_offset + blockIdx.x;
+    const int f = (int)uniform_u32((uint32_t)a.edge_map[2 * unit]);
+    const int local = (int)uniform_u32((uint32_t)a.edge_map[2 * unit + 1]);
+    const FrameRec& F = a.frames[f];
+    const int H = F.H, W = F.W;
+    const int chunks = (W + kLabCols - 1) / kLabCols, width = label_chunk(W);
+    const int seg = local / chunks;
+    const int px0 = (local - seg * chunks) * width, py0 = seg * a.edge_rows;
+    const int cols = min(width, W - px0), rows = min(a.edge_rows, H - py0);
+    if (cols <= 0)
+        return;
+    const int n = min(4, cols - 4 * tid);
+    uint8_t* out = a.masks_out[f] + (int64_t)py0 * W + px0 + 4 * tid;
+    label_walk<C>(static_cast<const uint8_t*>(a.images[f]), F.pitch, H, W, F.pad, py0, rows, px0, cols,
+                  a.edge_threshold * C, reinterpret_cast<uint16_t*>(lds), label_stride(4 * (int)blockDim.x),
+                  [&](int y0, int ya, int yb, const uint32_t (&lab)[kLabBlock]) {
+#pragma unroll
+        for (int i = 0; i < kLabBlock; ++i) {
+            if (y0 + i < ya || y0 + i >= yb)
+                continue;
+            uint8_t* o = out + (int64_t)(y0 + i) * W;
+            if (n == 4)
+                __builtin_nontemporal_store(lab[i], (g_u32w*)o);
+            else
+                for (int q = 0; q < n; ++q)
+                    ((g_u8w*)o)[q] = (uint8_t)(lab[i] >> (8 * q));
+        }
+    });
 }
 
 // ==========================================================================
@@ -2727,7 +2814,7 @@ hipError_t allow_lds(K kernel, size_t lds)
     return e;
 }
 
-static hipError_t launch_scan(const TileArgs& a, bool prefix_scan, hipStream_t s)
+hipError_t launch_scan(const TileArgs& a, bool prefix_scan, hipStream_t s)
 {
     if (prefix_scan)
         hipLaunchKernelGGL(k_scan_prefix, dim3((unsigned)a.n_frames), dim3(256), 0, s, a);
@@ -2761,33 +2848,18 @@ hipError_t launch_plan(const TileArgs& a, int64_t n_units, int threads, size_t l
     return launch_scan(a, prefix_scan, s);
 }
 
-template <int C>
-static hipError_t launch_plan_labels_c(const TileArgs& a, int64_t n_units, int threads, size_t lds, hipStream_t s)
-{
-    hipError_t e = allow_lds(k_plan_labels<C>, lds);
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(k_plan_labels<C>, dim3((unsigned)n_units), dim3(threads), lds, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_plan_labels(const TileArgs& a, int64_t n_units, int threads, size_t lds, unsigned channel_mask,
-                              bool prefix_scan, hipStream_t s)
+hipError_t launch_plan_labels(const TileArgs& a, int C, int64_t n_units, int threads, size_t lds, hipStream_t s)
 {
     if (n_units == 0)
         return hipSuccess;
-    hipError_t e = hipSuccess;
-    if (e == hipSuccess && (channel_mask & 2u))
-        e = launch_plan_labels_c<1>(a, n_units, threads, lds, s);
-    if (e == hipSuccess && (channel_mask & 4u))
-        e = launch_plan_labels_c<2>(a, n_units, threads, lds, s);
-    if (e == hipSuccess && (channel_mask & 8u))
-        e = launch_plan_labels_c<3>(a, n_units, threads, lds, s);
-    if (e == hipSuccess && (channel_mask & 16u))
-        e = launch_plan_labels_c<4>(a, n_units, threads, lds, s);
-    if (e != hipSuccess)
-        return e;
-    return launch_scan(a, prefix_scan, s);
+    const dim3 grid((unsigned)n_units), block((unsigned)threads);
+    switch (C) {
+    case 1: hipLaunchKernelGGL(k_plan_labels<1>, grid, block, lds, s, a); break;
+    case 2: hipLaunchKernelGGL(k_plan_labels<2>, grid, block, lds, s, a); break;
+    case 3: hipLaunchKernelGGL(k_plan_labels<3>, grid, block, lds, s, a); break;
+    default: hipLaunchKernelGGL(k_plan_labels<4>, grid, block, lds, s, a); break;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_store_index(const TileArgs& a, bool prefix_scan, hipStream_t s)
@@ -2856,16 +2928,18 @@ hipError_t launch_backward_mirror(const TileArgs& a, int threads, int grid, hipS
     return launch_tiles(k_backward_mirror, a, threads, 0, grid, s);
 }
 
-hipError_t launch_edge_mask(const TileArgs& a, int C, int threads, hipStream_t s)
+hipError_t launch_edge_mask(const TileArgs& a, int C, int64_t n_units, int threads, size_t lds, hipStream_t s)
 {
-    TileArgs b = a;
-    b.persistent = 0;
+    if (n_units == 0)
+        return hipSuccess;
+    const dim3 grid((unsigned)n_units), block((unsigned)threads);
     switch (C) {
-    case 1: return launch_tiles(k_edge_mask<1>, b, threads, 0, (int)b.n_tiles, s);
-    case 2: return launch_tiles(k_edge_mask<2>, b, threads, 0, (int)b.n_tiles, s);
-    case 3: return launch_tiles(k_edge_mask<3>, b, threads, 0, (int)b.n_tiles, s);
-    default: return launch_tiles(k_edge_mask<4>, b, threads, 0, (int)b.n_tiles, s);
+    case 1: hipLaunchKernelGGL(k_edge_mask<1>, grid, block, lds, s, a); break;
+    case 2: hipLaunchKernelGGL(k_edge_mask<2>, grid, block, lds, s, a); break;
+    case 3: hipLaunchKernelGGL(k_edge_mask<3>, grid, block, lds, s, a); break;
+    default: hipLaunchKernelGGL(k_edge_mask<4>, grid, block, lds, s, a); break;
     }
+    return hipGetLastError();
 }
 
 hipError_t launch_metrics(const TileArgs& a, int C, int64_t n_units, hipStream_t s)

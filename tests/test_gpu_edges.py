@@ -155,3 +155,37 @@ def test_metrics_at_unit_edges(dev, offset, width_pad):
         ssim = oracle.metrics(xs[i], ys[i])[1] if h >= 7 and w >= 7 else 0.0
         assert abs(got[i, 1] - ssim) <= 1e-9, (i, got[i, 1], ssim)
     plan.close()
+
+
+@pytest.mark.parametrize("pad", [0, 1, 2])
+@pytest.mark.parametrize("offset,width_pad", [(0, 0), (3, 2)])
+def test_labels_at_group_edges(dev, pad, offset, width_pad):
+    """Widths around the label kernels' 16-pixel groups, four-column lanes and
+    walks of 992 columns, bands of every parity: the masks equal the oracle's,
+    nothing beside them is written, and the fused plan equals the two-step one."""
+    say("case: label edges", pad, offset, width_pad)
+    r = np.random.Generator(np.random.PCG64(700 + 10 * pad + offset))
+    shapes = [(9, 1, 3, 4, 0), (5, 15, 1, 4, 1), (33, 16, 3, 16, 0), (18, 17, 2, 5, 2), (31, 31, 3, 32, 0),
+              (14, 33, 4, 7, 3), (257, 47, 1, 256, 0), (20, 64, 3, 3, 9), (35, 130, 3, 129, 0), (8, 991, 1, 8, 0),
+              (19, 992, 3, 16, 0), (7, 993, 1, 2, 0), (34, 1010, 3, 32, 0), (6, 1999, 2, 12, 100), (300, 21, 3, 150, 1)]
+    fps, xs = [], []
+    for i, (h, w, c, b, k) in enumerate(shapes):
+        fps.append(dp.FrameParams(h, w, c, dp.U8_HWC, b=b, sb=b, m=8, tau=1 + i % 3, pad_mode=pad, pitch=w * c + width_pad,
+                                  tile_cells=k))
+        xs.append(r.integers(0, 256, (h, w, c)).astype(np.uint8) // (1 + 9 * (r.random((h, w, 1)) < 0.7)).astype(np.uint8))
+    ti = [_strided(f, dev, offset, 255)[1] for f in fps]
+    for v, x in zip(ti, xs):
+        v.copy_(torch.from_numpy(x).to(dev))
+    bufs = [torch.full((f.height * f.width + 2 * offset,), 9, dtype=torch.uint8, device=dev) for f in fps]
+    masks = [t[offset:offset + f.height * f.width].view(f.height, f.width) for t, f in zip(bufs, fps)]
+    plan = dp.Plan(fps, device=dev)
+    one, two = plan.new_store(), plan.new_store()
+    plan.edge_masks(ti, 90, out=masks)
+    plan.plan(masks, store=two)
+    plan.plan_labels(ti, 90, store=one)
+    torch.cuda.synchronize()
+    for i, x in enumerate(xs):
+        assert np.array_equal(masks[i].cpu().numpy(), oracle.edge_mask(x, 90, pad)), i
+        assert _untouched(bufs[i], masks[i], 9), i
+    assert torch.equal(one.flags, two.flags) and torch.equal(one.counts, two.counts)
+    plan.close()
