@@ -29,6 +29,12 @@ class DPPixFn(torch.autograd.Function):
         if x.dim() != 4 or x.dtype != torch.float32:
             raise ValueError("x must be float32 (B, C, H, W)")
         x = x.contiguous()
+        ctx.plan = plan
+        ctx.store = None
+        if plan._holds_batch(x):
+            y, kept = plan._forward_batch(x, masks)
+            ctx.save_for_backward(kept)
+            return y
         frames = [x[i] for i in range(x.shape[0])]
         y = torch.empty_like(x)
         outs = [y[i] for i in range(x.shape[0])]
@@ -36,15 +42,19 @@ class DPPixFn(torch.autograd.Function):
         store = plan.new_store()
         plan.plan(masks, store=store)
         plan.forward(frames, out=outs, clip=clip, store=store)
-        ctx.plan = plan
         ctx.store = store
         ctx.save_for_backward(clip[0], clip[1])
         return y
 
     @staticmethod
     def backward(ctx, gy: torch.Tensor):
-        clip_bg, clip_fg = ctx.saved_tensors
         gy = gy.contiguous()
+        if ctx.store is None:
+            kept, = ctx.saved_tensors
+            if not ctx.plan._holds_batch(gy):
+                raise ValueError("the gradient must be a float32 batch like the output, on its device")
+            return ctx.plan._backward_batch(gy, kept), None, None
+        clip_bg, clip_fg = ctx.saved_tensors
         gx = torch.empty_like(gy)
         ctx.plan.backward([gy[i] for i in range(gy.shape[0])], [gx[i] for i in range(gx.shape[0])],
                           (clip_bg, clip_fg), store=ctx.store)
