@@ -1676,51 +1676,56 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
 // Forward, fp32 CHW.  Column sums in fp32 over at most s_b rows, subcell and
 // cell sums in fp64.
 // ==========================================================================
-// Broadcast of a tile's statistics to its real pixels, fp32 CHW: per
-// (channel, subgrid row) one padded row is expanded in LDS (two alternating
-// buffers of 4 * nstr floats at `rowbuf`, one barrier per row) and each lane
-// stores the s_b rows of one 4-float strip.  vgs / vgc hold the values of the
-// simple cells and of the complex subcells (as the fp32 forward lays them out).
-__device__ void broadcast_tile_f32(const FrameRec& F, int r, int64_t X0, int64_t lim, int Kt, int nstr,
-                                   float* rowbuf, const uint8_t* cflag, const float* vgs, const float* vgc,
-                                   float* out)
+// Broadcast of a tile's statistics to its real pixels, fp32 CHW: an item per
+// (channel, subgrid row, 4-float strip) finds the strip's values among the
+// tile's statistics in LDS and stores its s_b rows, consecutive lanes on
+// consecutive strips; nothing is expanded and no lane waits for another.
+// vgs / vgc hold the values of the simple cells and of the complex subcells
+// (as the fp32 forward lays them out).  Bound by the stores.  64 x 3 x 218 x 178,
+// b 8 / s_b 4: forward 29.6 -> 26.1 us, adjoint 47.7 -> 45.1; 32 x 3 x 512 x 512,
+// b 16 / s_b 8: no change at 35 us each (before: one row of one channel
+// expanded in LDS at a time, a barrier each, on as many lanes as it has strips).
+__device__ __forceinline__ void broadcast_tile_f32(const FrameRec& F, int r, int64_t X0, int real, int Kt,
+                                                   const uint8_t* cflag, const float* vgs, const float* vgc,
+                                                   float* out)
 {
     const int tid = threadIdx.x, NT = blockDim.x;
     const int b = F.b, s = F.s, n = F.n, H = F.H, C = F.C;
-    const int kn = Kt * n;
+    const int kn = Kt * n, nst = (real + 3) >> 2;
     const int64_t pitch = F.pitch, plane = pitch * H;
-    const int real = (int)(lim - X0);
-    for (int ch = 0; ch < C; ++ch) {
-        float* pl = out + plane * ch;
-        for (int fr = 0; fr < n; ++fr) {
-            float* exf = rowbuf + ((ch * n + fr) & 1) * (4 * nstr);   // two alternating row buffers
-            for (int fc = tid; fc < kn; fc += NT) {
-                const int kc = fc / n;
-                const float v = cflag[kc] ? vgc[(fr * kn + fc) * C + ch] : vgs[kc * C + ch];
-                for (int x = 0; x < s; ++x)
-                    exf[fc * s + x] = v;
-            }
-            lds_barrier();
-            const int row0 = r * b + fr * s;
-            const int rows = min(s, H - row0);
-            for (int st = tid; st < nstr; st += NT) {
-                if (4 * st >= real)
-                    continue;
-                if (real >= 4) {
-                    // the last strip ends with the real columns (the floats it
-                    // shares with its neighbour are written twice, alike)
-                    const int po = min(4 * st, real - 4);
-                    const float* e = exf + po;
-                    const v4f v = (po & 3) == 0 ? *reinterpret_cast<const v4f*>(e) : v4f{e[0], e[1], e[2], e[3]};
-                    for (int k = 0; k < rows; ++k)
-                        st16f_nt(pl + (int64_t)(row0 + k) * pitch + X0 + po, v);
-                } else {
-                    g_f32w* pg = (g_f32w*)(pl + X0);
-                    for (int k = 0; k < rows; ++k)
-                        for (int q = 0; q < real; ++q)
-                            pg[(int64_t)(row0 + k) * pitch + q] = exf[q];
+    for (int it = tid; it < C * n * nst; it += NT) {
+        const int rest = it / nst, st = it - rest * nst;
+        const int ch = rest / n, fr = rest - ch * n;
+        const int row0 = r * b + fr * s;
+        const int rows = min(s, H - row0);
+        // the last strip ends with the real columns (the floats it shares with
+        // its neighbour are written twice, alike)
+        const int po = real >= 4 ? min(4 * st, real - 4) : 0;
+        int fc = po / s, in = po - fc * s, kc = fc / n, jj = fc - kc * n;
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v[q] = fc >= kn ? 0.f : (cflag[kc] ? vgc[(fr * kn + fc) * C + ch] : vgs[kc * C + ch]);
+            if (++in == s) {
+                in = 0;
+                ++fc;
+                if (++jj == n) {
+                    jj = 0;
+                    ++kc;
                 }
             }
+        }
+        float* o = out + plane * ch + (int64_t)row0 * pitch + X0 + po;
+        if (real >= 4) {
+            const v4f w = v4f{v[0], v[1], v[2], v[3]};
+            for (int k = 0; k < rows; ++k)
+                st16f_nt(o + (int64_t)k * pitch, w);
+        } else {
+            for (int k = 0; k < rows; ++k)
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (q < real)
+                        ((g_f32w*)o)[(int64_t)k * pitch + q] = v[q];
         }
     }
 }
@@ -1879,7 +1884,7 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
     if (out == nullptr)
         return;
     lds_barrier();
-    broadcast_tile_f32(F, r, X0, lim, Kt, nstr, colsum, cflag, vgs, vgc, out);
+    broadcast_tile_f32(F, r, X0, sp.real, Kt, cflag, vgs, vgc, out);
 }
 
 // Persistent workgroups take tiles from an atomic ticket; the last one out
@@ -2024,18 +2029,13 @@ __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const 
 __device__ void reconstruct_tile_f32(const TileArgs& a, const FrameRec& F, const TileCoord& tc, uint8_t* lds)
 {
     const int tid = threadIdx.x, NT = blockDim.x;
-    const int b = F.b, s = F.s, n = F.n, H = F.H, W = F.W, C = F.C;
+    const int b = F.b, n = F.n, W = F.W, C = F.C;
     const int r = tc.r;
     const int x0c = tc.ct * F.K;
     const int Kt = min(F.K, F.GC - x0c);
-    const int WB = Kt * b;
-    const int nstr = (WB + 3) >> 2;
     const int64_t X0 = (int64_t)x0c * b;
-    const int64_t lim = min(X0 + WB, (int64_t)W);
-    const int64_t pitch = F.pitch, plane = pitch * H;
-    float* out = static_cast<float*>(a.outs[tc.f]);
+    const int real = (int)(min(X0 + Kt * b, (int64_t)W) - X0);
     const LdsPlan L = lds_plan(kRecF32, F.K, b, n, C);
-    float* exbase = reinterpret_cast<float*>(lds + L.colsum);
     uint32_t* cidx = reinterpret_cast<uint32_t*>(lds + L.cidx);
     uint8_t* cflag = lds + L.cflag;
     float* vgs = reinterpret_cast<float*>(lds + L.vgs);
@@ -2059,40 +2059,7 @@ __device__ void reconstruct_tile_f32(const TileArgs& a, const FrameRec& F, const
             vgc[j] = a.fg[fg_base + ((uint64_t)cidx[kc] * nn + fr * n + jj) * C + ch];
     }
     lds_barrier();
-    const int real = (int)(lim - X0);
-    for (int ch = 0; ch < C; ++ch) {
-        float* pl = out + plane * ch;
-        for (int fr = 0; fr < n; ++fr) {
-            float* exf = exbase + ((ch * n + fr) & 1) * (4 * nstr);   // two alternating row buffers
-            for (int fc = tid; fc < kn; fc += NT) {
-                const int kc = fc / n;
-                const float v = cflag[kc] ? vgc[(fr * kn + fc) * C + ch] : vgs[kc * C + ch];
-                for (int x = 0; x < s; ++x)
-                    exf[fc * s + x] = v;
-            }
-            lds_barrier();
-            const int row0 = r * b + fr * s;
-            const int rows = min(s, H - row0);
-            for (int st = tid; st < nstr; st += NT) {
-                if (4 * st >= real)
-                    continue;
-                if (real >= 4) {
-                    // the last strip ends with the real columns (the floats it
-                    // shares with its neighbour are written twice, alike)
-                    const int po = min(4 * st, real - 4);
-                    const float* e = exf + po;
-                    const v4f v = (po & 3) == 0 ? *reinterpret_cast<const v4f*>(e) : v4f{e[0], e[1], e[2], e[3]};
-                    for (int k = 0; k < rows; ++k)
-                        st16f_nt(pl + (int64_t)(row0 + k) * pitch + X0 + po, v);
-                } else {
-                    g_f32w* pg = (g_f32w*)(pl + X0);
-                    for (int k = 0; k < rows; ++k)
-                        for (int q = 0; q < real; ++q)
-                            pg[(int64_t)(row0 + k) * pitch + q] = exf[q];
-                }
-            }
-        }
-    }
+    broadcast_tile_f32(F, r, X0, real, Kt, cflag, vgs, vgc, static_cast<float*>(a.outs[tc.f]));
 }
 
 template <int C>
@@ -2232,7 +2199,7 @@ __device__ void backward_reduce_tile(const TileArgs& a, const FrameRec& F, const
     // every real pixel takes its own statistic's gradient (the mirror terms
     // of pixels near padded borders are added by a later pass)
     lds_barrier();
-    broadcast_tile_f32(F, r, X0, lim, Kt, nstr, colsum, cflag, vgs, vgc, gin);
+    broadcast_tile_f32(F, r, X0, sp.real, Kt, cflag, vgs, vgc, gin);
 }
 
 __global__ __launch_bounds__(kMaxThreads) void k_backward_reduce(TileArgs a)
