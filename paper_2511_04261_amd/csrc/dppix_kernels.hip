@@ -74,6 +74,11 @@ __device__ __forceinline__ void st16f_nt(void* p, v4f v) { __builtin_nontemporal
 // constants, the high halves of the products are xored with the other two
 // words and the round key, and the key advances by two Weyl increments.
 // --------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1)
 {
 #pragma unroll
@@ -81,7 +86,8 @@ __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1)
         // one 32x32 -> 64-bit product per multiplier gives both halves
         const uint64_t pa = (uint64_t)0xD2511F53u * c.x;
         const uint64_t pb = (uint64_t)0xCD9E8D57u * c.z;
-        c = make_uint4((uint32_t)(pb >> 32) ^ c.y ^ k0, (uint32_t)pb, (uint32_t)(pa >> 32) ^ c.w ^ k1, (uint32_t)pa);
+        c = make_uint4(xor3((uint32_t)(pb >> 32), c.y, k0), (uint32_t)pb, xor3((uint32_t)(pa >> 32), c.w, k1),
+                       (uint32_t)pa);
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -98,27 +104,47 @@ __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1)
 // only corrects.  ln 2 is split into 42 leading bits (e ln2_hi is exact) and
 // the rest.  Against the C library's log on 2e7 such arguments it agrees
 // exactly on 93 % and within one ulp on all.
+//
+// The draws are vector work (fine grids are bound by them), so the division
+// is the plain refinement of the reciprocal, without the scaling and fix-up
+// that operands of any magnitude need (f and 2 + f are normal and far from the
+// ends of the range, and the quotient is the same, correctly rounded, one),
+// the exponent comes off the high word, and each coefficient is an operand of
+// its fma instead of a register filled beforehand.  A draw with its Philox
+// block took about 450 cycles of a SIMD and takes 330; 16 x 1080p RGB, b 4 /
+// s_b 2: forward 136 -> 128 us, b 2 / s_b 1, 8 frames: 234 -> 218.
+// a b + c with c a constant in scalar registers.
+__device__ __forceinline__ double fma_const(double a, double b, double c)
+{
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+    return d;
+}
+
 __device__ __forceinline__ double ln_unit(double x)
 {
-    int e;
-    double m = frexp(x, &e);
-    if (m < 0.70710678118654752440) {
-        m *= 2.0;
-        e -= 1;
-    }
+    // m = x 2^-e from sqrt(1/2) on (its high word's worth of it)
+    const uint64_t bits = __builtin_bit_cast(uint64_t, x);
+    const int32_t hi = (int32_t)(bits >> 32);
+    const int32_t e = (hi - 0x3FE6A09E) >> 20;
+    const double m = __builtin_bit_cast(double, (bits & 0xFFFFFFFFull) | ((uint64_t)(uint32_t)(hi - (e << 20)) << 32));
     const double f = m - 1.0;
-    const double s = f / (2.0 + f);
+    const double d = 2.0 + f;
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(r, fma(-d, r, 1.0), r);
+    r = fma(r, fma(-d, r, 1.0), r);
+    const double s0 = f * r;
+    const double s = fma(fma(-d, s0, f), r, s0);
     const double z = s * s;
-    double R = 2.0 / 21.0;
-    R = fma(R, z, 2.0 / 19.0);
-    R = fma(R, z, 2.0 / 17.0);
-    R = fma(R, z, 2.0 / 15.0);
-    R = fma(R, z, 2.0 / 13.0);
-    R = fma(R, z, 2.0 / 11.0);
-    R = fma(R, z, 2.0 / 9.0);
-    R = fma(R, z, 2.0 / 7.0);
-    R = fma(R, z, 2.0 / 5.0);
-    R = fma(R, z, 2.0 / 3.0);
+    double R = fma_const(2.0 / 21.0, z, 2.0 / 19.0);
+    R = fma_const(R, z, 2.0 / 17.0);
+    R = fma_const(R, z, 2.0 / 15.0);
+    R = fma_const(R, z, 2.0 / 13.0);
+    R = fma_const(R, z, 2.0 / 11.0);
+    R = fma_const(R, z, 2.0 / 9.0);
+    R = fma_const(R, z, 2.0 / 7.0);
+    R = fma_const(R, z, 2.0 / 5.0);
+    R = fma_const(R, z, 2.0 / 3.0);
     R *= z;
     const double h = 0.5 * f * f;
     const double de = (double)e;
@@ -140,12 +166,12 @@ __device__ __forceinline__ double laplace_sample(const FrameRec& F, uint32_t id,
     uint32_t k0 = __builtin_amdgcn_readfirstlane(F.key0), k1 = __builtin_amdgcn_readfirstlane(F.key1);
     asm volatile("" : "+s"(k0), "+s"(k1));
     const uint4 w = philox10(make_uint4(id, (uint32_t)ch | ((uint32_t)level << 8), F.fi0, F.fi1), k0, k1);
-    const uint64_t bits = ((uint64_t)w.y << 32) | (uint64_t)w.x;
-    const double u = (double)(((bits >> 12) << 1) | 1ull) * 0x1p-53;
+    // u - 1/2 and 2 min(u, 1 - u), exactly: 1 + k 2^-52 is built from its
+    // bits, and every step below stays within 53 bits
+    const uint64_t k = (((uint64_t)w.y << 32) | (uint64_t)w.x) >> 12;
+    const double t = (__builtin_bit_cast(double, k | 0x3FF0000000000000ull) - 1.5) + 0x1p-53;
     // one log per lane: the two tails differ only in its argument and sign
-    const bool lower = u < 0.5;
-    const double l = ln_unit(lower ? 2.0 * u : 2.0 * (1.0 - u));
-    return lower ? sigma * l : -sigma * l;
+    return copysign(sigma * ln_unit(fma(-2.0, fabs(t), 1.0)), t);
 }
 
 // Release one statistic: mean = sum / area, plus noise (Eq. 11 scale given by
@@ -163,8 +189,7 @@ __device__ __forceinline__ float release(double sum, double area, double inv_are
     const double mu = inv_area != 0.0 ? sum * inv_area : sum / area;
     const double z = noisy ? mu + laplace_sample(F, id, ch, level, sigma) : mu;
     pass = (uint8_t)(z >= 0.0 && z <= 255.0);
-    const double v = z < 0.0 ? 0.0 : (z > 255.0 ? 255.0 : z);
-    return (float)v;
+    return (float)fmin(fmax(z, 0.0), 255.0);
 }
 
 __device__ __forceinline__ uint8_t to_u8(float v) { return (uint8_t)rintf(v); }
