@@ -215,6 +215,16 @@ __device__ __forceinline__ int fold(int x, int L, int mode)
     return y < L ? y : p - y;
 }
 
+// Quotients x / d of item numbers by one divisor, 0 <= x < 2^20: the rounded
+// (x + 1/2) / d is off by less than 2^-22 of itself, so less than the half
+// step that keeps it from the next integer.  Three instructions, where the
+// division of any two integers takes about 25.
+struct FastDiv {
+    float inv, half;
+    __device__ __forceinline__ explicit FastDiv(int d) : inv(__builtin_amdgcn_rcpf((float)d)), half(0.5f * inv) {}
+    __device__ __forceinline__ int operator()(int x) const { return (int)fmaf((float)x, inv, half); }
+};
+
 // Unpadded border mode (Algorithm 1): positions past the frame are absent —
 // they add nothing to sums or mask counts, and each (sub)cell's mean divides
 // by its real pixel count.
@@ -398,7 +408,7 @@ __device__ __forceinline__ TileCoord tile_of(const TileArgs& a, int64_t sched_id
     // one load: (frame, tile within frame) of this scheduling index
     const int64_t idx = a.sched_offset + sched_idx;
     tc.f = (int)uniform_u32((uint32_t)a.tile_map[2 * idx]);
-    const int64_t local = (int64_t)uniform_u32((uint32_t)a.tile_map[2 * idx + 1]);
+    const uint32_t local = uniform_u32((uint32_t)a.tile_map[2 * idx + 1]);
     F = a.frames[tc.f];
     if (a.noise != nullptr) {
         // this call's noise counters, read at launch time (a replayed graph
@@ -410,8 +420,8 @@ __device__ __forceinline__ TileCoord tile_of(const TileArgs& a, int64_t sched_id
         F.fi1 = (uint32_t)(ctr >> 32);
     }
     tc.t = F.tile_base + local;
-    tc.r = (int)(local / F.TX);
-    tc.ct = (int)(local - (int64_t)tc.r * F.TX);
+    tc.r = (int)(local / (uint32_t)F.TX);
+    tc.ct = (int)(local - (uint32_t)tc.r * (uint32_t)F.TX);
     return tc;
 }
 
@@ -581,10 +591,11 @@ __device__ void plan_count(const TileArgs& a, const FrameRec& F, const uint8_t* 
     const int nmir = vec && pad != kPadNone ? (padded + 15) >> 4 : 0;
     const int ncol = nfast + nmir;
     const int per_band = ncol * groups;
+    const FastDiv by_band(per_band), by_col(ncol), by_cell(b);
     for (int item = tid; item < nb * per_band; item += NT) {
-        const int j = item / per_band;
+        const int j = by_band(item);
         const int rem = item - j * per_band;
-        const int g = rem / ncol;
+        const int g = by_col(rem);
         const int st = rem - g * ncol;
         const bool mir = st >= nfast;
         // first column of the strip, and the columns [va, vb) it counts
@@ -648,7 +659,7 @@ __device__ void plan_count(const TileArgs& a, const FrameRec& F, const uint8_t* 
             // update (a 16-bit half sums at most 8 columns of 16 rows)
             const uint32_t t = (e[0] + e[1] + e[2] + e[3]) + (o[0] + o[1] + o[2] + o[3]);
             const uint32_t cnt = (t & 0xFFFFu) + (t >> 16);
-            const int cell = (16 * st) / b;
+            const int cell = by_cell(16 * st);
             if (cnt != 0u && cell < KC)
                 atomicAdd(cellcnt + j * KCs + cell, cnt);
         } else {
@@ -701,19 +712,20 @@ __device__ __forceinline__ void plan_unit(const TileArgs& a, uint8_t* lds, Count
     lds_barrier();
     count(F, f, r0, nb, c0, KC, KCs, cellcnt);
     lds_barrier();
+    const FastDiv by_kc(KC), by_k(F.K), by_nt(nt);
     for (int i = tid; i < nb * KC; i += NT) {
-        const int j = i / KC, kc = i - j * KC;
+        const int j = by_kc(i), kc = i - j * KC;
         // tau = 0 (unpadded mode only): majority of the cell's real pixels
         const uint32_t tau = F.tau > 0 ? (uint32_t)F.tau
                                        : ((uint32_t)stat_area(F, (r0 + j) * F.b, (c0 + kc) * F.b, F.b) + 1u) / 2u;
         const uint8_t fl = (uint8_t)(cellcnt[j * KCs + kc] >= tau);
         a.flags[F.cell_base + (int64_t)(r0 + j) * F.GC + c0 + kc] = fl;
         if (fl)
-            atomicAdd(&tcnt[j * F.ctx + kc / F.K], 1u);
+            atomicAdd(&tcnt[j * F.ctx + by_k(kc)], 1u);
     }
     lds_barrier();
     for (int i = tid; i < nb * nt; i += NT) {
-        const int j = i / nt, ti = i - j * nt;
+        const int j = by_nt(i), ti = i - j * nt;
         a.tile_cnt[F.tile_base + (int64_t)(r0 + j) * F.TX + t0 + ti] = tcnt[j * F.ctx + ti];
     }
 }
@@ -1339,10 +1351,11 @@ __device__ __forceinline__ void expand_row_u8(uint8_t* exb, int kn, int n, int s
                                               const uint8_t* vgs, const uint8_t* vgc)
 {
     const int tid = threadIdx.x, NT = blockDim.x;
+    const FastDiv by_n(n);
     if (((s * C) & 3) == 0) {
         const int words = (s * C) >> 2;
         for (int fc = tid; fc < kn; fc += NT) {
-            const int kc = fc / n;
+            const int kc = by_n(fc);
             const uint8_t* v = cflag[kc] ? vgc + (fr * kn + fc) * C : vgs + kc * C;
             uint32_t pix = 0;   // the pixel's C bytes, first channel lowest
 #pragma unroll
@@ -1366,7 +1379,7 @@ __device__ __forceinline__ void expand_row_u8(uint8_t* exb, int kn, int n, int s
     }
     for (int j = tid; j < kn * C; j += NT) {
         const int fc = j / C, ch = j - fc * C;
-        const int kc = fc / n;
+        const int kc = by_n(fc);
         const uint8_t v = cflag[kc] ? vgc[(fr * kn + fc) * C + ch] : vgs[kc * C + ch];
         uint8_t* e = exb + fc * s * C + ch;
         for (int x = 0; x < s; ++x)
@@ -1515,8 +1528,9 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
         const int nfast = sp.vec ? sp.nvec : 0;
         const int q = band_inside ? rows_per_item(s) : 1;
         const int ngq = (ng + q - 1) / q;
+        const FastDiv by_strip(nfast);
         for (int it = tid; it < nfast * ngq; it += NT) {
-            const int gq = it / nfast;
+            const int gq = by_strip(it);
             const int st = it - gq * nfast;
             const int g0 = gq * q;
             const int qq = min(q, ng - g0);
@@ -1558,10 +1572,11 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
         if (sp.vec && sp.real < WB) {
             // padded columns: the sums of the columns they mirror, or nothing
             const int np = WB - sp.real;
+            const FastDiv by_np(np);
             if (pad != kPadNone)
                 lds_barrier();
             for (int i = tid; i < ng * np; i += NT) {
-                const int g = i / np, p = sp.real + (i - g * np);
+                const int g = by_np(i), p = sp.real + (i - g * np);
                 const int x = p / C, ch = p - x * C;
                 col16[g * rowbuf + p] =
                     pad == kPadNone ? (uint16_t)0 : col16[g * rowbuf + mirror_col(x, sp.real / C, pad) * C + ch];
@@ -1597,10 +1612,11 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
         // sums and releases its C channels
         const int ncx = (int)s_ncx;
         const int per_cx = ng * n;
+        const FastDiv by_cx(per_cx), by_n(n);
         for (int it = tid; it < ncx * per_cx; it += NT) {
-            const int q = it / per_cx;
+            const int q = by_cx(it);
             const int rem = it - q * per_cx;
-            const int g = rem / n, jj = rem - g * n;
+            const int g = by_n(rem), jj = rem - g * n;
             const int kc = cxl[q];
             const int fc = kc * n + jj, fr = fr0 + g;
             uint32_t S[C];
@@ -1656,6 +1672,7 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
     // subgrid row suffices: a buffer is rewritten two rows later, after every
     // lane has passed the barrier that follows its last read.
     const int real = sp.real;
+    const FastDiv by_nstr(nstr);
     uint8_t* band_out = out + (int64_t)r * b * pitch + X0;
     for (int fr = 0; fr < n; ++fr) {
         uint8_t* exb = ex + (fr & 1) * (16 * nstr);
@@ -1668,7 +1685,7 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
         const int parts = max(1, min(rows, NT / nstr));
         const int per = (rows + parts - 1) / max(parts, 1);
         for (int it = tid; it < nstr * parts; it += NT) {
-            const int part = it / nstr;
+            const int part = by_nstr(it);
             const int st = it - part * nstr;
             const int k0 = part * per, k1 = min(rows, k0 + per);
             if (16 * st >= real)
@@ -1718,15 +1735,16 @@ __device__ __forceinline__ void broadcast_tile_f32(const FrameRec& F, int r, int
     const int b = F.b, s = F.s, n = F.n, H = F.H, C = F.C;
     const int kn = Kt * n, nst = (real + 3) >> 2;
     const int64_t pitch = F.pitch, plane = pitch * H;
+    const FastDiv by_nst(nst), by_n(n), by_s(s);
     for (int it = tid; it < C * n * nst; it += NT) {
-        const int rest = it / nst, st = it - rest * nst;
-        const int ch = rest / n, fr = rest - ch * n;
+        const int rest = by_nst(it), st = it - rest * nst;
+        const int ch = by_n(rest), fr = rest - ch * n;
         const int row0 = r * b + fr * s;
         const int rows = min(s, H - row0);
         // the last strip ends with the real columns (the floats it shares with
         // its neighbour are written twice, alike)
         const int po = real >= 4 ? min(4 * st, real - 4) : 0;
-        int fc = po / s, in = po - fc * s, kc = fc / n, jj = fc - kc * n;
+        int fc = by_s(po), in = po - fc * s, kc = by_n(fc), jj = fc - kc * n;
         float v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -1808,13 +1826,14 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
     // lane per (channel, subcell column) adds the s_b column sums (fp64) per
     // subgrid row and releases the complex subcells.
     const int kn4 = 4 * nstr;                 // floats of one row buffer
+    const FastDiv by_kn(kn), by_n(n);
     for (int fr0 = 0; fr0 < n; fr0 += kRowGroupF) {
         const int ng = min(kRowGroupF, n - fr0);
         const int nit = sp.vec ? sp.nvec : nstr;
+        const FastDiv by_nit(nit), by_ng(ng);
         for (int it = tid; it < C * ng * nit; it += NT) {
-            const int st = it % nit;
-            const int rest = it / nit;
-            const int g = rest % ng, ch = rest / ng;
+            const int rest = by_nit(it), st = it - rest * nit;
+            const int ch = by_ng(rest), g = rest - ch * ng;
             const float* pl = img + plane * ch;
             const int row0 = r * b + (fr0 + g) * s;
             const int po = sp.vec ? min(4 * st, sp.real - 4) : 4 * st;   // the last strip ends with the real columns
@@ -1853,16 +1872,18 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
             const int np = WB - sp.real;
             if (pad != kPadNone)
                 lds_barrier();
+            const FastDiv by_np(np);
             for (int i = tid; i < C * ng * np; i += NT) {
-                float* cs = colsum + (i / np) * kn4;
-                const int x = sp.real + i % np;
+                const int row = by_np(i);
+                float* cs = colsum + row * kn4;
+                const int x = sp.real + i - row * np;
                 cs[x] = pad == kPadNone ? 0.f : cs[mirror_col(x, sp.real, pad)];
             }
         }
         lds_barrier();
         for (int j = tid; j < C * kn; j += NT) {
-            const int ch = j / kn, fc = j - ch * kn;
-            const int kc = fc / n, jj = fc - kc * n;
+            const int ch = by_kn(j), fc = j - ch * kn;
+            const int kc = by_n(fc), jj = fc - kc * n;
             const int ci = fc * C + ch;
             double part = fr0 == 0 ? 0.0 : cspart[ci];
             for (int g = 0; g < ng; ++g) {
@@ -1889,8 +1910,9 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
         }
         lds_barrier();
     }
+    const FastDiv by_c(C);
     for (int j = tid; j < Kt * C; j += NT) {
-        const int kc = j / C, ch = j - kc * C;
+        const int kc = by_c(j), ch = j - kc * C;
         if (cflag[kc])
             continue;
         double S = 0.0;
@@ -1992,6 +2014,7 @@ __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const 
     const uint64_t bg_base = a.counts[4 * tc.f + 2];
     const uint64_t fg_base = a.counts[4 * tc.f + 3];
     const int nn = n * n, kn = Kt * n;
+    const FastDiv by_kn(kn), by_n(n);
     lds_barrier();
     for (int j = tid; j < Kt * C; j += NT) {
         const int kc = j / C, ch = j - kc * C;
@@ -2002,13 +2025,14 @@ __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const 
         // j = ((fr * kn) + fc) * C + ch
         const int ch = j % C;
         const int q = j / C;
-        const int fr = q / kn, fc = q - fr * kn;
-        const int kc = fc / n, jj = fc - kc * n;
+        const int fr = by_kn(q), fc = q - fr * kn;
+        const int kc = by_n(fc), jj = fc - kc * n;
         if (cflag[kc])
             vgc[j] = to_u8(a.fg[fg_base + ((uint64_t)cidx[kc] * nn + fr * n + jj) * C + ch]);
     }
     lds_barrier();
     const int real = (int)(lim - X0);
+    const FastDiv by_nstr(nstr);
     const uint32_t upitch = (uint32_t)pitch;
     uint8_t* band_out = out + (int64_t)r * b * pitch + X0;
     for (int fr = 0; fr < n; ++fr) {
@@ -2022,7 +2046,7 @@ __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const 
         const int parts = max(1, min(rows, NT / nstr));
         const int per = (rows + parts - 1) / max(parts, 1);
         for (int it = tid; it < nstr * parts; it += NT) {
-            const int part = it / nstr;
+            const int part = by_nstr(it);
             const int st = it - part * nstr;
             const int k0 = part * per, k1 = min(rows, k0 + per);
             if (16 * st >= real)
@@ -2069,6 +2093,7 @@ __device__ void reconstruct_tile_f32(const TileArgs& a, const FrameRec& F, const
     const uint64_t bg_base = a.counts[4 * tc.f + 2];
     const uint64_t fg_base = a.counts[4 * tc.f + 3];
     const int nn = n * n, kn = Kt * n;
+    const FastDiv by_kn(kn), by_n(n);
     lds_barrier();
     for (int j = tid; j < Kt * C; j += NT) {
         const int kc = j / C, ch = j - kc * C;
@@ -2078,8 +2103,8 @@ __device__ void reconstruct_tile_f32(const TileArgs& a, const FrameRec& F, const
     for (int j = tid; j < Kt * nn * C; j += NT) {
         const int ch = j % C;
         const int q = j / C;
-        const int fr = q / kn, fc = q - fr * kn;
-        const int kc = fc / n, jj = fc - kc * n;
+        const int fr = by_kn(q), fc = q - fr * kn;
+        const int kc = by_n(fc), jj = fc - kc * n;
         if (cflag[kc])
             vgc[j] = a.fg[fg_base + ((uint64_t)cidx[kc] * nn + fr * n + jj) * C + ch];
     }
@@ -2139,13 +2164,14 @@ __device__ void backward_reduce_tile(const TileArgs& a, const FrameRec& F, const
     // of kRowGroupF subgrid rows, real rows only, in order, then one lane per
     // (channel, subcell column)
     const int kn4 = 4 * nstr;
+    const FastDiv by_kn(kn), by_n(n);
     for (int fr0 = 0; fr0 < n; fr0 += kRowGroupF) {
         const int ng = min(kRowGroupF, n - fr0);
         const int nit = sp.vec ? sp.nvec : nstr;
+        const FastDiv by_nit(nit), by_ng(ng);
         for (int it = tid; it < C * ng * nit; it += NT) {
-            const int st = it % nit;
-            const int rest = it / nit;
-            const int g = rest % ng, ch = rest / ng;
+            const int rest = by_nit(it), st = it - rest * nit;
+            const int ch = by_ng(rest), g = rest - ch * ng;
             const float* pl = go + plane * ch;
             const int row0 = r * b + (fr0 + g) * s;
             const int rows = max(0, min(s, H - row0));   // real rows only
@@ -2179,13 +2205,16 @@ __device__ void backward_reduce_tile(const TileArgs& a, const FrameRec& F, const
         }
         if (sp.vec && sp.real < WB) {
             const int np = WB - sp.real;
-            for (int i = tid; i < C * ng * np; i += NT)
-                colsum[(i / np) * kn4 + sp.real + i % np] = 0.f;
+            const FastDiv by_np(np);
+            for (int i = tid; i < C * ng * np; i += NT) {
+                const int row = by_np(i);
+                colsum[row * kn4 + sp.real + i - row * np] = 0.f;
+            }
         }
         lds_barrier();
         for (int j = tid; j < C * kn; j += NT) {
-            const int ch = j / kn, fc = j - ch * kn;
-            const int kc = fc / n, jj = fc - kc * n;
+            const int ch = by_kn(j), fc = j - ch * kn;
+            const int kc = by_n(fc), jj = fc - kc * n;
             const int ci = fc * C + ch;
             double part = fr0 == 0 ? 0.0 : cspart[ci];
             for (int g = 0; g < ng; ++g) {
