@@ -189,3 +189,29 @@ def test_labels_at_group_edges(dev, pad, offset, width_pad):
         assert _untouched(bufs[i], masks[i], 9), i
     assert torch.equal(one.flags, two.flags) and torch.equal(one.counts, two.counts)
     plan.close()
+
+
+@pytest.mark.parametrize("b", [1, 2, 3, 4, 8, 12, 16, 20, 24, 48])
+@pytest.mark.parametrize("pad", [0, 2])
+def test_mask_counts_of_every_cell_size(dev, b, pad):
+    """Cell sizes on each path of the mask count (whole short bands, four
+    columns a dword, column by column), rows of whole strips and not, bands
+    past the frame, mask bytes of any nonzero value: flags equal the oracle's."""
+    say("case: mask counts", b, pad)
+    r = np.random.Generator(np.random.PCG64(900 + b + pad))
+    shapes = [(5 * b, 96, 0), (8 * b + 1, 192, 0), (16 * b - 1, 208, 0), (3, 64, 0), (40, 250, 0), (4 * b, 16 * b, 3)]
+    fps, ms = [], []
+    for i, (h, w, k) in enumerate(shapes):
+        fps.append(dp.FrameParams(h, w, 1, dp.U8_HWC, b=b, sb=b, m=8, tau=(1, 2, 0)[i % 3] if b > 1 else 1, pad_mode=pad,
+                                  tile_cells=k))
+        ms.append((r.random((h, w)) < (0.3, 0.05, 0.6)[i % 3]) * r.choice([1, 2, 127, 128, 255], (h, w)))
+    ms = [m.astype(np.uint8) for m in ms]
+    plan = dp.Plan(fps, device=dev)
+    plan.plan([torch.from_numpy(m).to(dev) for m in ms])
+    store = plan.store_host()
+    for i, f in enumerate(fps):
+        x = np.zeros((f.height, f.width, 1), np.uint8)
+        want = oracle.forward(x, ms[i], oracle_params(f))
+        assert np.array_equal(store[i]["flags"], want["flags"]), i
+        assert tuple(store[i]["counts"]) == tuple(want["counts"]), i
+    plan.close()
