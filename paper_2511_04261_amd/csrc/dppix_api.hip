@@ -36,8 +36,8 @@ constexpr int kDefaultThreads = 256;
 constexpr int64_t kTileBytesTarget = 2048;  // padded bytes per tile row (u8)
 constexpr int64_t kPlanCellsMax = 2048;     // cells per band of one plan unit
 constexpr int64_t kPlanLdsMax = 32 * 1024;  // LDS of one plan unit
-constexpr int64_t kTileLdsTarget = 48 * 1024;
-constexpr int64_t kTileLdsMax = 150 * 1024;
+constexpr int64_t kTileLdsTarget = 48 * 1024 + 16;
+constexpr int64_t kTileLdsMax = 150 * 1024 + 16;
 constexpr int kMaxDim = 1 << 24;
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }

@@ -72,7 +72,7 @@ __host__ __device__ inline LdsPlan lds_plan(int kind, int K, int b, int n, int C
         o += al16(4u * (uint32_t)(K * C));
     p.vgc = o;
     if (kind == kFwdU8 || kind == kRecU8)
-        o += al16((uint32_t)(K * n * n * C));
+        o += al16((uint32_t)(K * n * n * C)) + 16u;   // (a pixel is read as two dwords)
     else if (kind == kFwdF32 || kind == kRecF32 || kind == kBwd)
         o += al16(4u * (uint32_t)(K * n * n * C));
     p.cxl = o;
