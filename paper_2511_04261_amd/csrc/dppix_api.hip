@@ -531,21 +531,15 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
         const FrameRec& F = p->frames[f];
         if (F.pad == DPPIX_PAD_NONE)
             continue;
-        const int PR = F.GR * F.b - F.H, PC = F.GC * F.b - F.W;
-        const int lo_r = PR > 0 ? (PR <= F.H - 1 ? F.H - 1 - PR : 0) : F.H;
-        const int lo_c = PC > 0 ? (PC <= F.W - 1 ? F.W - 1 - PC : 0) : F.W;
         for (int32_t r = 0; r < F.GR; ++r)
             for (int32_t ct = 0; ct < F.TX; ++ct) {
-                const int x0c = ct * F.K, Kt = std::min(F.K, F.GC - x0c);
-                const int y0 = r * F.b, y1 = std::min(y0 + F.b, F.H);
-                const int xa = x0c * F.b, xb = std::min((x0c + Kt) * F.b, F.W);
-                if (y0 >= F.H || xa >= F.W || (y1 <= lo_r && xb <= lo_c))
-                    continue;
-                border.push_back(f);
-                border.push_back(r * F.TX + ct);
+                const BorderArea m = border_area(F, r, ct);
+                const int32_t parts = (int32_t)(((m.n_a + m.n_b) * F.C + kBorderItems - 1) / kBorderItems);
+                for (int32_t k = 0; k < parts; ++k)
+                    border.insert(border.end(), {f, r * F.TX + ct, k, parts});
             }
     }
-    p->n_border = (int64_t)border.size() / 2;
+    p->n_border = (int64_t)border.size() / 4;
     w.border_map = o;  o = align256(o + sizeof(int32_t) * border.size());
     w.simple_counts = o; o = align256(o + sizeof(uint64_t) * 4 * (size_t)n_frames);
     std::vector<int32_t> met_map, lab_map, edge_map;
@@ -1037,10 +1031,8 @@ dppix_status_t run_backward(dppix_plan_t p, const dppix_store_t* store, const fl
     // 2. mirror terms of the pixels near padded borders: only the border
     // tiles, and no launch at all when no frame is padded
     if (p->n_border > 0) {
-        TileArgs m = a;
-        m.tile_map = reinterpret_cast<const int32_t*>(p->bound + p->ws.border_map);
-        m.n_tiles = p->n_border;
-        e = launch_backward_mirror(m, plain_threads(p), grid_for(p, 1, 1, plain_threads(p), p->n_border, 0), s);
+        e = launch_backward_mirror(a, reinterpret_cast<const int32_t*>(p->bound + p->ws.border_map), p->n_border,
+                                   plain_threads(p), s);
         if (e != hipSuccess)
             return dev_fail(e, "backward launch");
     }

@@ -35,6 +35,39 @@ struct FrameRec {
     uint32_t key0, key1, fi0, fi1;
 };
 
+// The pixels of a tile that padded rows or columns fold onto: rows [ra, y1) of
+// columns [xa, xb) (n_a of them) and rows [y0, rb) of columns [ca, xb) (n_b).
+struct BorderArea {
+    int xa, xb, y0, y1, ra, rb, ca;
+    int64_t n_a, n_b;
+};
+
+__host__ __device__ inline BorderArea border_area(const FrameRec& F, int r, int ct)
+{
+    auto lo = [](int x, int y) { return x < y ? x : y; };
+    auto hi = [](int x, int y) { return x > y ? x : y; };
+    BorderArea m;
+    const int x0c = ct * F.K, Kt = lo(F.K, F.GC - x0c);
+    m.y0 = r * F.b;
+    m.y1 = lo(m.y0 + F.b, F.H);
+    m.xa = x0c * F.b;
+    m.xb = lo((x0c + Kt) * F.b, F.W);
+    const int PR = F.GR * F.b - F.H, PC = F.GC * F.b - F.W;
+    // rows at or above lo_r (columns at or above lo_c) may have mirror preimages
+    const int lo_r = PR > 0 ? (PR <= F.H - 1 ? F.H - 1 - PR : 0) : F.H;
+    const int lo_c = PC > 0 ? (PC <= F.W - 1 ? F.W - 1 - PC : 0) : F.W;
+    m.ra = hi(m.y0, lo_r);
+    m.rb = lo(m.y1, lo_r);
+    m.ca = hi(m.xa, lo_c);
+    m.n_a = m.ra < m.y1 ? (int64_t)(m.y1 - m.ra) * (m.xb - m.xa) : 0;
+    m.n_b = m.rb > m.y0 && m.xb > m.ca ? (int64_t)(m.rb - m.y0) * (m.xb - m.ca) : 0;
+    return m;
+}
+
+// Items (channels x pixels) of a workgroup of the mirror pass: a lane's loads
+// are two levels deep, so a large tile is shared out rather than walked.
+constexpr int kBorderItems = 512;
+
 // Workspace layout of a plan (byte offsets from the bound workspace base):
 // tables written once by dp_pix_plan_bind and only read afterwards, so one
 // bound plan serves any number of concurrent calls.
@@ -42,7 +75,7 @@ struct WsLayout {
     size_t frames;        // FrameRec[n_frames]
     size_t tile_map;      // int32[n_tiles][2]: (frame, tile within frame) per scheduling index
     size_t unit_map;      // int32[n_units][2]: (frame, plan unit within frame), frame-major
-    size_t border_map;    // int32[n_border][2]: (frame, tile) of the tiles the adjoint's mirror pass visits
+    size_t border_map;    // int32[n_border][4]: (frame, tile, part, parts) of the adjoint's mirror pass
     size_t lab_map;       // int32[n_lab][2]: (frame, unit within frame) of the plan from labels, by channel count
     size_t edge_map;      // int32[n_edge][2]: the same of the label masks
     size_t met_map;       // int32[n_met][2]: (frame, unit within frame) of the metrics, by channel count
@@ -145,7 +178,8 @@ hipError_t launch_forward(const TileArgs& a, int layout, int C, int threads, siz
 hipError_t launch_reconstruct(const TileArgs& a, int layout, int C, int threads, size_t lds, int grid,
                               hipStream_t s);
 hipError_t launch_backward_reduce(const TileArgs& a, int threads, size_t lds, int grid, hipStream_t s);
-hipError_t launch_backward_mirror(const TileArgs& a, int threads, int grid, hipStream_t s);
+hipError_t launch_backward_mirror(const TileArgs& a, const int32_t* border_map, int64_t n_border, int threads,
+                                  hipStream_t s);
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
 hipError_t launch_noise_advance(uint64_t* noise, int32_t n, uint64_t step, hipStream_t s);
 hipError_t launch_edge_mask(const TileArgs& a, int C, int64_t n_units, int threads, size_t lds, hipStream_t s);
