@@ -49,6 +49,7 @@ size_t grad_scratch_need(dppix_plan_t p);
 struct LaunchGroup {
     int layout, C;
     int threads;          // workgroup size chosen for the group's tiles
+    int rec_threads;      // the same for their reconstruction
     int64_t lo, hi;       // scheduling-index range
     size_t lds_fwd, lds_rec;
 };
@@ -227,18 +228,43 @@ void xcd_runs(int32_t* map, int64_t lo, int64_t hi)
     std::copy(tmp.begin(), tmp.end(), map + 2 * lo);
 }
 
-// Workgroup size of a frame's forward and reconstruction tiles.  A u8 tile
-// with few phase-1 items (strips x groups of subgrid rows, e.g. b = 16 or
-// narrow frames) keeps more tiles in flight per CU with 128 lanes; larger
-// tiles fill 256 (measured on 64 x 1080p and 300 x 768x576 batches).
-int tile_threads(const FrameRec& F)
+// Workgroup size of a frame's forward tiles.  A tile with few phase-1 items
+// (strips x groups of subgrid rows, fp32: x channels; e.g. b = 16 or narrow
+// frames) keeps more tiles in flight per CU with 128 lanes; larger tiles fill 256
+// (measured on 64 x 1080p and 300 x 768x576 batches; fp32 forward of 64 x 3 x 218 x
+// 178, b 8: 256 / 128 lanes 21.7 / 18.2 us, of 32 x 3 x 512 x 512, b 16: 35 / 38).  A u8
+// batch of fewer tiles than there are CUs (`few`) is bound by each tile's own
+// chain, which more lanes shorten: one 1080p frame 256 / 512 lanes 13.2 / 12.6 us,
+// one 768 x 576 frame 128 / 256 / 512 lanes 13.2 / 12.2 / 11.8.
+constexpr int64_t kFewTiles = 256;
+
+int tile_threads(const FrameRec& F, int64_t tiles)
 {
+    const int64_t bytes = (int64_t)F.K * F.b * F.C;
+    if (F.layout != DPPIX_U8_HWC)
+        return F.C * std::min(F.n, kRowGroupF) * ((bytes / F.C + 3) / 4) <= 320 ? 128 : kDefaultThreads;
+    const int q = F.s == 2 ? 4 : ((F.s == 3 || F.s == 4) ? 2 : 1);
+    const int64_t items = (bytes + 15) / 16 * ((std::min(F.n, kRowGroup) + q - 1) / q);
+    if (tiles < kFewTiles)
+        return items > 256 ? 512 : (items > 128 ? kDefaultThreads : 128);
+    return items <= 320 ? 128 : kDefaultThreads;
+}
+
+// Workgroup size of a frame's reconstruction tiles.  They only write, and where a
+// tile has enough 16-byte stores more lanes cover the latency of its statistics:
+// 64 x 1080p, b 32 (3840 stores a tile): 256 / 512 lanes 78.6 / 74.1 us; 4 frames of
+// 4000 x 6000, b 16 (2000): 128 / 256 lanes 81 / 72; 100 x 576 x 768, b 16 (1152): 30.6 /
+// 35.7.  With few tiles per CU, 512 lanes leave them uneven: 8 x 1080p, 816 tiles:
+// 13.9 / 16.0.  fp32 tiles take 256 (64 x 3 x 218 x 178: 128 / 256 lanes 11.9 / 10.8).
+int rec_threads(const FrameRec& F, int64_t tiles)
+{
+    const int base = tile_threads(F, tiles);
     if (F.layout != DPPIX_U8_HWC)
         return kDefaultThreads;
-    const int64_t nstr = ((int64_t)F.K * F.b * F.C + 15) / 16;
-    const int q = F.s == 2 ? 4 : ((F.s == 3 || F.s == 4) ? 2 : 1);
-    const int64_t ngq = (std::min(F.n, kRowGroup) + q - 1) / q;
-    return nstr * ngq <= 320 ? 128 : kDefaultThreads;
+    const int64_t stores = ((int64_t)F.K * F.b * F.C + 15) / 16 * F.b;
+    if (tiles < kFewTiles || stores < 1536)
+        return base;
+    return tiles >= 2048 && stores >= 3072 ? 512 : kDefaultThreads;
 }
 
 // Plan units of the batch: fewer than kPlanUnits leave compute units idle, so
@@ -485,7 +511,7 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
     // launch per workgroup size)
     auto group_key = [&](int32_t f) {
         const FrameRec& F = p->frames[f];
-        return (F.layout * 8 + F.C) * 2 + (tile_threads(F) == kDefaultThreads ? 0 : 1);
+        return (F.layout * 8 + F.C) * 4 + (512 / tile_threads(F, tile)) / 2;
     };
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
         if (group_key(x) != group_key(y))
@@ -503,17 +529,18 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
     p->sched_base[n_frames] = acc;
     for (int32_t k = 0; k < n_frames; ++k) {
         const FrameRec& F = p->frames[order[k]];
-        const int th = tile_threads(F);
+        const int th = tile_threads(F, tile);
         if (p->groups.empty() || p->groups.back().layout != F.layout || p->groups.back().C != F.C ||
             p->groups.back().threads != th)
-            p->groups.push_back(LaunchGroup{F.layout, F.C, th, p->sched_base[k], p->sched_base[k], 0, 0});
+            p->groups.push_back(LaunchGroup{F.layout, F.C, th, 0, p->sched_base[k], p->sched_base[k], 0, 0});
         LaunchGroup& g = p->groups.back();
         g.hi = p->sched_base[k + 1];
+        g.rec_threads = std::max(g.rec_threads, rec_threads(F, tile));
         g.lds_fwd = std::max(g.lds_fwd, frame_lds(kind_fwd(F), F));
         g.lds_rec = std::max(g.lds_rec, frame_lds(kind_rec(F), F));
     }
 
-    if (p->groups.size() > (size_t)kMaxGroups) {   // 2 layouts x 4 channel counts x 2 sizes at most
+    if (p->groups.size() > (size_t)kMaxGroups) {   // 2 layouts x 4 channel counts x 3 sizes at most
         delete p;
         return fail(DPPIX_ENOTSUP, "too many launch groups");
     }
@@ -772,8 +799,11 @@ dppix_status_t check_store(const dppix_store_t* s, bool need_stats)
 // Workgroup size of the kernels outside the launch groups.
 int plain_threads(dppix_plan_t p) { return p->threads ? p->threads : kDefaultThreads; }
 
-// Workgroup size of a launch group's forward and reconstruction tiles.
-int group_threads(dppix_plan_t p, const LaunchGroup& g) { return p->threads ? p->threads : g.threads; }
+// Workgroup size of a launch group's forward (or reconstruction) tiles.
+int group_threads(dppix_plan_t p, const LaunchGroup& g, bool rec)
+{
+    return p->threads ? p->threads : (rec ? g.rec_threads : g.threads);
+}
 
 int grid_for(dppix_plan_t p, int layout, int C, int threads, int64_t tiles, size_t lds)
 {
@@ -798,7 +828,7 @@ hipError_t for_groups(dppix_plan_t p, const TileArgs& base, bool rec, Launch lau
         a.n_tiles = g.hi - g.lo;
         a.ticket = base.ticket + 2 * gi;
         const size_t lds = rec ? g.lds_rec : g.lds_fwd;
-        hipError_t e = launch(a, g, lds, grid_for(p, g.layout, g.C, group_threads(p, g), a.n_tiles, lds));
+        hipError_t e = launch(a, g, lds, grid_for(p, g.layout, g.C, group_threads(p, g, rec), a.n_tiles, lds));
         if (e != hipSuccess)
             return e;
     }
@@ -948,7 +978,7 @@ dppix_status_t dp_pix_forward(dppix_plan_t p, const void* const* images, const d
     a.clip_fg = clip_fg;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = for_groups(p, a, false, [&](const TileArgs& ga, const LaunchGroup& g, size_t lds, int grid) {
-        return launch_forward(ga, g.layout, g.C, group_threads(p, g), lds, grid, s);
+        return launch_forward(ga, g.layout, g.C, group_threads(p, g, false), lds, grid, s);
     });
     if (e != hipSuccess)
         return dev_fail(e, "forward launch");
@@ -968,7 +998,7 @@ dppix_status_t dp_pix_reconstruct(dppix_plan_t p, const dppix_store_t* store, vo
     a.outs = out;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = for_groups(p, a, true, [&](const TileArgs& ga, const LaunchGroup& g, size_t lds, int grid) {
-        return launch_reconstruct(ga, g.layout, g.C, group_threads(p, g), lds, grid, s);
+        return launch_reconstruct(ga, g.layout, g.C, group_threads(p, g, true), lds, grid, s);
     });
     if (e != hipSuccess)
         return dev_fail(e, "reconstruct launch");
@@ -1061,7 +1091,7 @@ dppix_status_t dp_pix_debug_sums(dppix_plan_t p, const void* const* images, cons
     a.dbg_fine = fine;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = for_groups(p, a, false, [&](const TileArgs& ga, const LaunchGroup& g, size_t lds, int grid) {
-        return launch_forward(ga, g.layout, g.C, group_threads(p, g), lds, grid, s);
+        return launch_forward(ga, g.layout, g.C, group_threads(p, g, false), lds, grid, s);
     });
     if (e != hipSuccess)
         return dev_fail(e, "forward launch");

@@ -16,7 +16,7 @@ namespace dppix {
 constexpr int kStrip = 16;             // bytes one lane moves per row (dwordx4)
 constexpr int kMaxThreads = 512;
 constexpr int kMaxB = 256;             // 255 * 256 rows fits a 16-bit lane sum
-constexpr int kMaxGroups = 16;         // launch groups: layout x channels x workgroup size
+constexpr int kMaxGroups = 24;         // launch groups: layout x channels x workgroup size
 constexpr int kTicketWords = 2 * kMaxGroups;      // two per launch group (resident-grid tickets)
 
 // One frame as the kernels see it (host computes everything derivable).

@@ -13,7 +13,7 @@ import numpy as np
 import pytest
 
 import oracle
-from tests.helpers import chw_to_hwc, compare_frame, oracle_params
+from tests.helpers import chw_to_hwc, compare_frame, hwc_to_chw, oracle_params
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -215,3 +215,42 @@ def test_mask_counts_of_every_cell_size(dev, b, pad):
         assert np.array_equal(store[i]["flags"], want["flags"]), i
         assert tuple(store[i]["counts"]) == tuple(want["counts"]), i
     plan.close()
+
+
+# frames, height, width, b, s_b, layout: every workgroup size of forward and
+# reconstruction (few tiles: 128, 256, 512 lanes; many: 128 or 256, the
+# reconstruction of large tiles in a large batch 512), and batches of several
+BATCHES = [[(1, 64, 16, 16, 4, dp.U8_HWC)], [(1, 64, 200, 16, 4, dp.U8_HWC)], [(2, 96, 700, 32, 4, dp.U8_HWC)],
+           [(60, 90, 333, 16, 4, dp.U8_HWC)], [(60, 120, 640, 16, 4, dp.U8_HWC)], [(70, 1024, 640, 32, 8, dp.U8_HWC)],
+           [(70, 1024, 640, 32, 8, dp.U8_HWC), (5, 61, 100, 8, 4, dp.U8_HWC), (3, 77, 300, 16, 8, dp.F32_CHW)],
+           [(40, 61, 50, 8, 4, dp.F32_CHW), (2, 130, 512, 16, 2, dp.F32_CHW)]]
+
+
+@pytest.mark.parametrize("batch", BATCHES, ids=range(len(BATCHES)))
+def test_workgroup_sizes_give_equal_results(batch, dev):
+    """The sizes chosen per launch group against one fixed size: equal bytes."""
+    fps, images = [], []
+    rng = np.random.default_rng(17)
+    for n, h, w, b, s, layout in batch:
+        x = rng.integers(0, 256, (h, w, 3), dtype=np.uint8)
+        if layout == dp.F32_CHW:
+            x = hwc_to_chw(x).astype(np.float32)
+        x = torch.from_numpy(x).to(dev)
+        for _ in range(n):
+            fps.append(dp.FrameParams(h, w, 3, layout, b=b, sb=s, m=8, eps_bg=1.0, eps_fg=0.5, tau=1, seed=9,
+                                      frame_index=len(fps)))
+            images.append(x)
+    masks = [torch.from_numpy(rng.integers(0, 40, (f.height, f.width), dtype=np.uint8) // 39).to(dev) for f in fps]
+    got = []
+    for threads in (0, 256):
+        plan = dp.Plan(fps, device=dev, threads=threads)
+        plan.plan(masks)
+        fused = [torch.empty_like(x) for x in images]
+        plan.forward(images, out=fused)
+        rebuilt = [torch.empty_like(x) for x in images]
+        plan.reconstruct(rebuilt)
+        torch.cuda.synchronize()
+        got.append((fused, rebuilt))
+    for i in range(len(fps)):
+        for k in range(2):
+            assert torch.equal(got[0][k][i], got[1][k][i]), (i, k)
