@@ -1223,32 +1223,60 @@ __global__ __launch_bounds__(256) void k_plan_simple(TileArgs a)
         a.counts[i] = a.simple_counts[i];
 }
 
-// One workgroup per frame: exclusive scan of the per-tile complex counts into
-// each tile's count of complex cells before it, and the frame's simple and
-// complex cell counts; k_scan_frames, launched next, turns the per-frame
-// counts into store offsets.  (Electing a last workgroup here instead needs
-// an agent-scope release in every workgroup, an L2 write-back on gfx950: the
-// plan call of the 256-frame batch took 3 us longer that way.)
+// Exclusive scan of a frame's per-tile complex counts into each tile's count of
+// complex cells before it; returns the frame's total.  The rounds are a chain of
+// a load, a scan and two barriers, about 0.8 us each: where one tile a lane would
+// take several, a lane takes eight consecutive ones (8 x 1080p, b 2, 1620 tiles a
+// frame: plan 19.4 -> 16.2 us; 16 x 1080p, b 4, 810: 15.3 -> 13.6; 24 frames of four
+// sizes, up to 2250: 49.9 -> 45.8, k_scan_tiles 9.1 -> 5.5 of it).
+template <int TILES>
+__device__ __forceinline__ uint32_t scan_tiles_n(const TileArgs& a, int64_t t0, int64_t nt, uint32_t* wave_tot)
+{
+    const auto* cnt = (const __attribute__((address_space(1))) uint32_t*)(a.tile_cnt + t0);
+    auto* fg = (__attribute__((address_space(1))) uint32_t*)(a.tile_fg + t0);
+    uint32_t carry = 0;
+    for (int64_t base = 0; base < nt; base += TILES * (int64_t)blockDim.x) {
+        const int64_t i = base + TILES * (int64_t)threadIdx.x;
+        uint32_t v[TILES], sum = 0;
+#pragma unroll
+        for (int k = 0; k < TILES; ++k)
+            v[k] = i + k < nt ? cnt[i + k] : 0u;
+#pragma unroll
+        for (int k = 0; k < TILES; ++k)
+            sum += v[k];
+        uint32_t tot;
+        uint32_t run = carry + block_exclusive_scan<uint32_t>(sum, wave_tot, tot);
+#pragma unroll
+        for (int k = 0; k < TILES; ++k) {
+            if (i + k < nt)
+                fg[i + k] = run;
+            run += v[k];
+        }
+        carry += tot;
+    }
+    return carry;
+}
+
+__device__ __forceinline__ uint32_t scan_frame_tiles(const TileArgs& a, int64_t t0, int64_t nt, uint32_t* wave_tot)
+{
+    return nt <= blockDim.x ? scan_tiles_n<1>(a, t0, nt, wave_tot) : scan_tiles_n<8>(a, t0, nt, wave_tot);
+}
+
+// One workgroup per frame: the tile prefixes and the frame's simple and complex
+// cell counts; k_scan_frames, launched next, turns the per-frame counts into
+// store offsets.  (Electing a last workgroup here instead needs an agent-scope
+// release in every workgroup, an L2 write-back on gfx950: the plan call of the
+// 256-frame batch took 3 us longer that way.)
 __global__ __launch_bounds__(256) void k_scan_tiles(TileArgs a)
 {
     __shared__ uint32_t wave_tot[9];
     const int f = blockIdx.x;
     const FrameRec F = a.frames[f];
-    const int64_t nt = (int64_t)F.GR * F.TX;
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < nt; base += blockDim.x) {
-        const int64_t i = base + threadIdx.x;
-        const uint32_t v = i < nt ? a.tile_cnt[F.tile_base + i] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_exclusive_scan<uint32_t>(v, wave_tot, tot);
-        if (i < nt)
-            a.tile_fg[F.tile_base + i] = carry + ex;
-        carry += tot;
-    }
+    const uint32_t total = scan_frame_tiles(a, F.tile_base, (int64_t)F.GR * F.TX, wave_tot);
     if (threadIdx.x == 0) {
         const uint64_t cells = (uint64_t)F.GR * F.GC;
-        a.counts[4 * f + 0] = cells - carry;
-        a.counts[4 * f + 1] = (uint64_t)carry;
+        a.counts[4 * f + 0] = cells - total;
+        a.counts[4 * f + 1] = (uint64_t)total;
     }
 }
 
@@ -1269,7 +1297,6 @@ __global__ __launch_bounds__(256) void k_scan_prefix(TileArgs a)
     const int f = blockIdx.x, tid = threadIdx.x, NT = blockDim.x;
     const FrameRec F = a.frames[f];
     const int64_t t0 = F.tile_base;
-    const int64_t nt = (int64_t)F.GR * F.TX;
     // tile counts of the earlier frames: 16 bytes a load, all in flight
     const int64_t n4 = t0 >> 2;
     const v4u* c4 = reinterpret_cast<const v4u*>(a.tile_cnt);
@@ -1287,18 +1314,9 @@ __global__ __launch_bounds__(256) void k_scan_prefix(TileArgs a)
     }
     uint32_t before;
     block_exclusive_scan<uint32_t>(part, wave_tot, before);
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < nt; base += NT) {
-        const int64_t i = base + tid;
-        const uint32_t v = i < nt ? a.tile_cnt[t0 + i] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_exclusive_scan<uint32_t>(v, wave_tot, tot);
-        if (i < nt)
-            a.tile_fg[t0 + i] = carry + ex;
-        carry += tot;
-    }
+    const uint32_t total = scan_frame_tiles(a, t0, (int64_t)F.GR * F.TX, wave_tot);
     if (tid == 0) {
-        const uint64_t nf = carry, nb = (uint64_t)F.GR * (uint64_t)F.GC - nf;
+        const uint64_t nf = total, nb = (uint64_t)F.GR * (uint64_t)F.GC - nf;
         const uint64_t bb = (uint64_t)F.C * ((uint64_t)F.cell_base - before);
         const uint64_t fb = (uint64_t)F.n * (uint64_t)F.n * (uint64_t)F.C * (uint64_t)before;
         a.counts[4 * f + 0] = nb;

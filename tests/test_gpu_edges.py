@@ -254,3 +254,45 @@ def test_workgroup_sizes_give_equal_results(batch, dev):
     for i in range(len(fps)):
         for k in range(2):
             assert torch.equal(got[0][k][i], got[1][k][i]), (i, k)
+
+
+# frames of the batch: (count, height, width, channels, b, s_b, tile_cells); one C and n or several, 1 to 513
+# frames, tiles of a frame around 8, 2048 and 4096 of the scan's rounds, prefixes that end inside a 16-byte group
+SCANS = [[(1, 64, 64, 3, 2, 1, 1)], [(3, 128, 128, 1, 2, 1, 1), (2, 5, 5, 3, 5, 1, 0)],
+         [(1, 7, 5, 1, 1, 1, 1), (1, 90, 91, 2, 2, 1, 1), (1, 3, 3, 4, 1, 1, 1), (1, 91, 91, 3, 2, 2, 1)],
+         [(511, 6, 9, 3, 4, 2, 1), (1, 9, 9, 1, 4, 1, 0)], [(512, 6, 9, 3, 4, 2, 1), (1, 9, 9, 1, 4, 1, 0)],
+         [(40, 33, 65, 3, 16, 4, 1), (40, 47, 31, 1, 8, 4, 1)], [(90, 40, 60, 3, 4, 2, 1), (3, 16, 16, 3, 16, 4, 0)],
+         [(2, 128, 300, 3, 2, 1, 1)], [(1, 256, 64, 1, 2, 1, 1), (7, 17, 19, 3, 4, 4, 1)]]
+
+
+@pytest.mark.parametrize("batch", SCANS, ids=range(len(SCANS)))
+def test_store_offsets_of_any_batch(batch, dev):
+    """Counts and offsets of every frame against sums over its flags; the statistics end up where they say."""
+    fps, masks, images = [], [], []
+    rng = np.random.default_rng(23)
+    for n, h, w, c, b, s, k in batch:
+        for _ in range(n):
+            fps.append(dp.FrameParams(h, w, c, b=b, sb=s, m=8, eps_bg=float("inf"), eps_fg=float("inf"), tau=1, seed=9,
+                                      frame_index=len(fps), tile_cells=k))
+    order = rng.permutation(len(fps))
+    fps = [fps[i] for i in order]
+    for f in fps:
+        masks.append(torch.from_numpy((rng.random((f.height, f.width)) < 0.2).astype(np.uint8)).to(dev))
+        images.append(torch.from_numpy(rng.integers(0, 256, (f.height, f.width, f.channels), dtype=np.uint8)).to(dev))
+    plan = dp.Plan(fps, device=dev)
+    plan.plan(masks)
+    fused = [torch.empty_like(x) for x in images]
+    plan.forward(images, out=fused)
+    rebuilt = [torch.empty_like(x) for x in images]
+    plan.reconstruct(rebuilt)
+    torch.cuda.synchronize()
+    counts = plan.store.counts.cpu().numpy().view(np.uint64).reshape(len(fps), 4)
+    bg = fg = 0
+    for i, (f, st) in enumerate(zip(fps, plan.store_host())):
+        n2 = (f.b // f.sb) ** 2
+        nf = int((st["flags"] != 0).sum())
+        nb = st["flags"].size - nf
+        assert counts[i].tolist() == [nb, nf, bg, fg], i
+        bg += nb * f.channels
+        fg += nf * n2 * f.channels
+        assert torch.equal(fused[i], rebuilt[i]), i
