@@ -320,9 +320,11 @@ void map_units(const dppix_plan& p, Units units, std::vector<int32_t>& map, std:
                 (*first)[2 * (size_t)f] = (int64_t)map.size() / 2;
                 (*first)[2 * (size_t)f + 1] = u;
             }
+            const size_t at = map.size();
+            map.resize(at + 2 * (size_t)u);
             for (int64_t i = 0; i < u; ++i) {
-                map.push_back(f);
-                map.push_back((int32_t)i);
+                map[at + 2 * i] = f;
+                map[at + 2 * i + 1] = (int32_t)i;
             }
         }
         lo[C] = (int64_t)map.size() / 2;
@@ -558,13 +560,17 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
         const FrameRec& F = p->frames[f];
         if (F.pad == DPPIX_PAD_NONE)
             continue;
-        for (int32_t r = 0; r < F.GR; ++r)
-            for (int32_t ct = 0; ct < F.TX; ++ct) {
+        for (int32_t r = 0; r < F.GR; ++r) {
+            // a band above the folded rows: the tiles from the first folded column on
+            const BorderArea band = border_area(F, r, 0);
+            const int32_t ct0 = band.n_a > 0 ? 0 : std::min(F.TX, band.lo_c / (F.K * F.b));
+            for (int32_t ct = ct0; ct < F.TX; ++ct) {
                 const BorderArea m = border_area(F, r, ct);
                 const int32_t parts = (int32_t)(((m.n_a + m.n_b) * F.C + kBorderItems - 1) / kBorderItems);
                 for (int32_t k = 0; k < parts; ++k)
                     border.insert(border.end(), {f, r * F.TX + ct, k, parts});
             }
+        }
     }
     p->n_border = (int64_t)border.size() / 4;
     w.border_map = o;  o = align256(o + sizeof(int32_t) * border.size());

@@ -39,6 +39,7 @@ struct FrameRec {
 // columns [xa, xb) (n_a of them) and rows [y0, rb) of columns [ca, xb) (n_b).
 struct BorderArea {
     int xa, xb, y0, y1, ra, rb, ca;
+    int lo_c;                 // first column that may be folded onto
     int64_t n_a, n_b;
 };
 
@@ -55,10 +56,10 @@ __host__ __device__ inline BorderArea border_area(const FrameRec& F, int r, int 
     const int PR = F.GR * F.b - F.H, PC = F.GC * F.b - F.W;
     // rows at or above lo_r (columns at or above lo_c) may have mirror preimages
     const int lo_r = PR > 0 ? (PR <= F.H - 1 ? F.H - 1 - PR : 0) : F.H;
-    const int lo_c = PC > 0 ? (PC <= F.W - 1 ? F.W - 1 - PC : 0) : F.W;
+    m.lo_c = PC > 0 ? (PC <= F.W - 1 ? F.W - 1 - PC : 0) : F.W;
     m.ra = hi(m.y0, lo_r);
     m.rb = lo(m.y1, lo_r);
-    m.ca = hi(m.xa, lo_c);
+    m.ca = hi(m.xa, m.lo_c);
     m.n_a = m.ra < m.y1 ? (int64_t)(m.y1 - m.ra) * (m.xb - m.xa) : 0;
     m.n_b = m.rb > m.y0 && m.xb > m.ca ? (int64_t)(m.rb - m.y0) * (m.xb - m.ca) : 0;
     return m;

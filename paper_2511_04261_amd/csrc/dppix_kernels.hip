@@ -322,8 +322,9 @@ __device__ __forceinline__ void store_colsums16(uint16_t* dst, const uint32_t (&
 // or than its padding mirrors, is read element by element instead.
 // 24 RGB photos of odd widths (22.9 MP, b 16 / s_b 4), before (strips off the
 // 16-byte grid and at the right edge gathered and stored byte by byte) and
-// after: forward 151 -> 46 us, reconstruction 89 -> 27 us, plan 53 -> 15 us;
-// 64 fp32 crops of 218 x 178: forward 40 -> 30 us.  Aligned batches unchanged.
+// after: forward 151 -> 44 us, reconstruction 89 -> 27 us (23 with the present
+// workgroup sizes), plan 53 -> 14 us; 64 fp32 crops of 218 x 178: forward 40 -> 30
+// us (18 with them).  Aligned batches unchanged.
 struct Strips {
     int real, nvec;
     bool vec;
@@ -498,7 +499,8 @@ __device__ void scan_frames(const TileArgs& a, uint64_t* wave_tot)
 // whole and b a multiple of 4, four columns are counted by one dot product;
 // whole bands of 2 or 4 rows take eight rows an item and count cell by cell.
 // 16 x 1080p, b 4: plan 24.5 -> 15.5 us (with the units halved), b 8: 14.5 -> 11.9;
-// 8 x 1080p, b 2: 30.1 -> 19.4; 64 x 1080p, b 32: 25.8 -> 25.2 (HBM-bound).
+// 8 x 1080p, b 2: 30.1 -> 19.4; 64 x 1080p, b 32: 25.8 -> 25.2 (HBM-bound).  With
+// the scan's eight tiles a lane the first three are 13.6, 11.4 and 16.2.
 // ==========================================================================
 constexpr int kPlanRows = 16;   // padded mask rows one lane sums per item
 constexpr int kPlanBatch = 8;   // row loads issued back to back
