@@ -179,6 +179,11 @@ __device__ __forceinline__ double laplace_sample(const FrameRec& F, uint32_t id,
 // fp32.  pass = the clip did not bind (gradient flows).  inv_area: 1 / area
 // when that is exact (area a power of two: the product then equals the
 // quotient bit for bit), else 0 (divide).
+// FLOATS: the sum is of fp32 pixels and may be NaN (a NaN pixel, or both
+// infinities in one cell), which the comparisons let through as they let it
+// through in the oracle: a diverged input must not come out as a valid black.
+// Sums of bytes are finite, and take the min and max of half the instructions.
+template <bool FLOATS>
 __device__ __forceinline__ float release(double sum, double area, double inv_area, int noisy, double sigma,
                                          const FrameRec& F, uint32_t id, int ch, int level, uint8_t& pass)
 {
@@ -189,6 +194,8 @@ __device__ __forceinline__ float release(double sum, double area, double inv_are
     const double mu = inv_area != 0.0 ? sum * inv_area : sum / area;
     const double z = noisy ? mu + laplace_sample(F, id, ch, level, sigma) : mu;
     pass = (uint8_t)(z >= 0.0 && z <= 255.0);
+    if constexpr (FLOATS)
+        return (float)(z < 0.0 ? 0.0 : (z > 255.0 ? 255.0 : z));
     return (float)fmin(fmax(z, 0.0), 255.0);
 }
 
@@ -1791,7 +1798,7 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
                 for (int k = 1; k < C; ++k)
                     Sc = ch == k ? S[k] : Sc;
                 uint8_t pass;
-                const float v = release((double)Sc, area, inv_s, F.noise_fg, F.sigma_fg, F, id, ch, 1, pass);
+                const float v = release<false>((double)Sc, area, inv_s, F.noise_fg, F.sigma_fg, F, id, ch, 1, pass);
                 a.fg[at + ch] = v;
                 if (a.clip_fg)
                     a.clip_fg[at + ch] = pass;
@@ -1812,7 +1819,7 @@ __device__ void forward_tile_u8(const TileArgs& a, const FrameRec& F, const Tile
         if (!cflag[kc]) {
             const uint32_t id = (uint32_t)(r * F.GC + x0c + kc);
             uint8_t pass;
-            const float v = release((double)S, stat_area(F, r * b, (x0c + kc) * b, b), exact_inv_area(F, b),
+            const float v = release<false>((double)S, stat_area(F, r * b, (x0c + kc) * b, b), exact_inv_area(F, b),
                                     F.noise_bg, F.sigma_bg, F, id, ch, 0, pass);
             const uint64_t at = bg_base + (uint64_t)cidx[kc] * C + ch;
             a.bg[at] = v;
@@ -2055,7 +2062,7 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
                     const int row0 = r * b + fr * s;
                     const uint32_t id = (uint32_t)(r * n + fr) * (uint32_t)(F.GC * n) + (uint32_t)(x0c * n + fc);
                     uint8_t pass;
-                    const float v = release(S, stat_area(F, row0, x0c * b + fc * s, s), inv_s, F.noise_fg,
+                    const float v = release<true>(S, stat_area(F, row0, x0c * b + fc * s, s), inv_s, F.noise_fg,
                                             F.sigma_fg, F, id, ch, 1, pass);
                     const uint64_t at = fg_base + ((uint64_t)cidx[kc] * nn + fr * n + jj) * C + ch;
                     a.fg[at] = v;
@@ -2078,7 +2085,7 @@ __device__ void forward_tile_f32(const TileArgs& a, const FrameRec& F, const Til
             S += cspart[(kc * n + jj) * C + ch];
         const uint32_t id = (uint32_t)(r * F.GC + x0c + kc);
         uint8_t pass;
-        const float v = release(S, stat_area(F, r * b, (x0c + kc) * b, b), inv_b, F.noise_bg, F.sigma_bg, F, id,
+        const float v = release<true>(S, stat_area(F, r * b, (x0c + kc) * b, b), inv_b, F.noise_bg, F.sigma_bg, F, id,
                                 ch, 0, pass);
         const uint64_t at = bg_base + (uint64_t)cidx[kc] * C + ch;
         a.bg[at] = v;
