@@ -19,6 +19,45 @@ constexpr int kMaxB = 256;             // 255 * 256 rows fits a 16-bit lane sum
 constexpr int kMaxGroups = 24;         // launch groups: layout x channels x workgroup size
 constexpr int kTicketWords = 2 * kMaxGroups;      // two per launch group (resident-grid tickets)
 
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// Unpadded border mode (Algorithm 1): positions past the frame are absent —
+// they add nothing to sums or mask counts, and each (sub)cell's mean divides
+// by its real pixel count.
+constexpr int kPadNone = 2;
+
+// Mirror index of padded coordinate x >= 0 into [0, L).
+__host__ __device__ __forceinline__ int fold(int x, int L, int mode)
+{
+    if (x < L)
+        return x;
+    if (mode == 0) {
+        if (x < 2 * L)          // first mirror image, the common case
+            return 2 * L - 1 - x;
+        const int p = 2 * L;
+        const int y = x % p;
+        return y < L ? y : p - 1 - y;
+    }
+    if (L == 1)
+        return 0;
+    if (x < 2 * L - 1)
+        return 2 * L - 2 - x;
+    const int p = 2 * L - 2;
+    const int y = x % p;
+    return y < L ? y : p - y;
+}
+
+// Mirror index of a coordinate in [-1, 2L) for the Sobel stencil: -1 mirrors
+// like the frame's own padding, the unpadded mode mirrors like the symmetric one.
+__host__ __device__ __forceinline__ int edge_fold(int x, int L, int mode)
+{
+    if (mode == kPadNone)   // the Sobel stencil mirrors like the symmetric mode
+        mode = 0;
+    if (x < 0)
+        return (mode == 0 || L == 1) ? 0 : 1;
+    return fold(x, L, mode);
+}
+
 // One frame as the kernels see it (host computes everything derivable).
 struct FrameRec {
     int32_t H, W, C, layout;
@@ -153,6 +192,7 @@ struct TileArgs {
 // LDS columns of a staged row (the right edge's groups reach past the last).
 constexpr int kLabBlock = 4;
 constexpr int kLabCols = 992;
+constexpr int kLabLeft = 16;                      // LDS columns before column 0
 __host__ __device__ inline int label_chunk(int W)
 {
     const int n = (W + kLabCols - 1) / kLabCols;
@@ -160,6 +200,84 @@ __host__ __device__ inline int label_chunk(int W)
 }
 __host__ __device__ inline int label_threads(int cols) { return (cols / 4 + 8 + 63) & ~63; }
 __host__ __device__ inline int label_stride(int cols) { return cols + 64; }
+__host__ __device__ inline int label_groups(int cols) { return (cols + 16) / 16 + 1; }   // of a staged row
+
+// One 16-pixel group of the staged columns [px0 - 1, px0 + cols], as a lane
+// keeps it from block to block: where its pixels come from and how their sums
+// reach the row.  Column x of the frame is staged at kLabLeft + x - px0.
+enum LabGroup : int {
+    kLabNone,      // nothing of the group is needed
+    kLabInside,    // sixteen pixels of the frame
+    kLabMirror,    // all past the right edge: the sixteen pixels they mirror, reversed
+    kLabCross,     // across the right edge: the frame's last sixteen pixels give both sides
+    kLabSingle     // anything else (left halo, narrow frames): pixel by pixel
+};
+
+struct LabPlace {
+    int kind, x, from;     // first column of the group, first pixel its vectors hold
+    int pa, pb;            // columns [pa, pb) of the group that are needed
+
+    __host__ __device__ __forceinline__ void setup(int g, int px0, int cols, int W, int pad)
+    {
+        x = px0 + 16 * (g - 1);
+        pa = x > px0 - 1 ? x : px0 - 1;
+        pb = x + 16 < px0 + cols + 1 ? x + 16 : px0 + cols + 1;
+        const int mirrored = (pad == 1 ? 2 * W - 2 : 2 * W - 1) - (x + 15);
+        from = x;
+        if (pa >= pb || (x < 0 && px0 == 0 && W >= 16))
+            kind = kLabNone;   // (column -1 is written by the group that holds its mirror image)
+        else if (x >= 0 && x + 16 <= W)
+            kind = kLabInside;
+        else if (x >= W && mirrored >= 0 && mirrored + 16 <= W) {
+            kind = kLabMirror;
+            from = mirrored;
+        } else if (x >= 0 && x < W && W >= 16) {
+            kind = kLabCross;
+            from = W - 16;
+        } else
+            kind = kLabSingle;
+    }
+
+    __host__ __device__ __forceinline__ bool vector() const { return kind != kLabNone && kind != kLabSingle; }
+
+    // The sums of the sixteen pixels from `from` on (pairs, the first in the
+    // low half) into the staged row S.
+    __host__ __device__ __forceinline__ void put(v4u lo, v4u hi, uint16_t* S, int px0, int W, int pad) const
+    {
+        uint16_t* d = S + kLabLeft + x - px0;
+        if (__builtin_expect(kind == kLabMirror, 0)) {
+            asm volatile("");   // a branch of its own: few lanes reverse
+            const v4u a = v4u{hi.w, hi.z, hi.y, hi.x}, b = v4u{lo.w, lo.z, lo.y, lo.x};
+            lo = (a >> 16) | (a << 16);
+            hi = (b >> 16) | (b << 16);
+        }
+        if (kind == kLabCross) {
+            // sums of the frame's last sixteen columns at their places, and
+            // reversed at the places that mirror them (what they overlap of
+            // the groups beside them, they write alike).  Where the walk
+            // itself starts past the edge, the former lie before the row and
+            // no column needs them.
+            const bool real = W > px0;
+            uint16_t* e = S + kLabLeft + from - px0;
+            uint16_t* m = S + kLabLeft + (pad == 1 ? W - 1 : W) - px0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t pr = i < 4 ? lo[i & 3] : hi[i & 3];
+                m[15 - 2 * i] = (uint16_t)pr;
+                m[14 - 2 * i] = (uint16_t)(pr >> 16);
+                if (real) {
+                    e[2 * i] = (uint16_t)pr;
+                    e[2 * i + 1] = (uint16_t)(pr >> 16);
+                }
+            }
+            return;
+        }
+        reinterpret_cast<v4u*>(d)[0] = lo;
+        reinterpret_cast<v4u*>(d)[1] = hi;
+        if (x == 0 && px0 == 0)   // (of a walk that starts further right, column -1 is no column)
+            d[-1] = (uint16_t)(pad == 1 ? lo.x >> 16 : lo.x);
+    }
+};
 
 // Host-side launchers (defined in dppix_kernels.hip).
 // prefix_scan: every frame has the same C and n and the batch has at most

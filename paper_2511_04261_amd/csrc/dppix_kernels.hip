@@ -42,7 +42,6 @@
 namespace dppix {
 namespace {
 
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 // 16-byte streaming accesses through global (not flat) address space: frame
@@ -201,27 +200,6 @@ __device__ __forceinline__ float release(double sum, double area, double inv_are
 
 __device__ __forceinline__ uint8_t to_u8(float v) { return (uint8_t)rintf(v); }
 
-// Mirror index of padded coordinate x >= 0 into [0, L).
-__device__ __forceinline__ int fold(int x, int L, int mode)
-{
-    if (x < L)
-        return x;
-    if (mode == 0) {
-        if (x < 2 * L)          // first mirror image, the common case
-            return 2 * L - 1 - x;
-        const int p = 2 * L;
-        const int y = x % p;
-        return y < L ? y : p - 1 - y;
-    }
-    if (L == 1)
-        return 0;
-    if (x < 2 * L - 1)
-        return 2 * L - 2 - x;
-    const int p = 2 * L - 2;
-    const int y = x % p;
-    return y < L ? y : p - y;
-}
-
 // Quotients x / d of item numbers by one divisor, 0 <= x < 2^20: the rounded
 // (x + 1/2) / d is off by less than 2^-22 of itself, so less than the half
 // step that keeps it from the next integer.  Three instructions, where the
@@ -231,22 +209,6 @@ struct FastDiv {
     __device__ __forceinline__ explicit FastDiv(int d) : inv(__builtin_amdgcn_rcpf((float)d)), half(0.5f * inv) {}
     __device__ __forceinline__ int operator()(int x) const { return (int)fmaf((float)x, inv, half); }
 };
-
-// Unpadded border mode (Algorithm 1): positions past the frame are absent —
-// they add nothing to sums or mask counts, and each (sub)cell's mean divides
-// by its real pixel count.
-constexpr int kPadNone = 2;
-
-// Mirror index of a coordinate in [-1, 2L) for the Sobel stencil: -1 mirrors
-// like the frame's own padding, the unpadded mode mirrors like the symmetric one.
-__device__ __forceinline__ int edge_fold(int x, int L, int mode)
-{
-    if (mode == kPadNone)   // the Sobel stencil mirrors like the symmetric mode
-        mode = 0;
-    if (x < 0)
-        return (mode == 0 || L == 1) ? 0 : 1;
-    return fold(x, L, mode);
-}
 
 // 1 / side^2 when that is exact and every statistic of that side has area
 // side^2 (mirror padding, side a power of two), else 0.
@@ -869,8 +831,6 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(5))
 // lane, no load in flight while a chunk was labelled, and frames off the
 // 16-byte grid staged pixel by pixel).
 // --------------------------------------------------------------------------
-constexpr int kLabLeft = 16;                      // LDS columns before column 0
-
 // Channel sums of 16 consecutive pixels from their 16 C bytes, as eight
 // dwords of two 16-bit sums each (pixel 2k low, 2k + 1 high).
 template <int C>
@@ -921,51 +881,13 @@ __device__ __forceinline__ void pixel_sums16(const v4u (&w)[C], v4u& lo, v4u& hi
     hi = v4u{pr[4], pr[5], pr[6], pr[7]};
 }
 
-// One 16-pixel group of the staged columns, as a lane keeps it from block to
-// block: where its pixels come from and how their sums reach LDS.  Column x
-// of the frame is staged at kLabLeft + x - px0.
-enum LabGroup : int {
-    kLabNone,      // nothing of the group is needed
-    kLabInside,    // sixteen pixels of the frame
-    kLabMirror,    // all past the right edge: the sixteen pixels they mirror, reversed
-    kLabCross,     // across the right edge: the frame's last sixteen pixels give both sides
-    kLabSingle     // anything else (left halo, narrow frames): pixel by pixel
-};
-
+// A lane's group and its sums into the staged row S: from the vectors of its
+// source pixels, or, pixel by pixel, from the row itself.
 template <int C>
-struct LabStage {
-    int kind, x, from;     // first column of the group, first pixel its vectors hold
-    int pa, pb;            // columns [pa, pb) of the group that are needed
-
-    __device__ __forceinline__ void setup(int g, int px0, int cols, int W, int pad)
-    {
-        x = px0 + 16 * (g - 1);
-        pa = max(x, px0 - 1);
-        pb = min(x + 16, px0 + cols + 1);
-        const int mirrored = (pad == 1 ? 2 * W - 2 : 2 * W - 1) - (x + 15);
-        from = x;
-        if (pa >= pb || (x < 0 && px0 == 0 && W >= 16))
-            kind = kLabNone;   // (column -1 is written by the group that holds its mirror image)
-        else if (x >= 0 && x + 16 <= W)
-            kind = kLabInside;
-        else if (x >= W && mirrored >= 0 && mirrored + 16 <= W) {
-            kind = kLabMirror;
-            from = mirrored;
-        } else if (x >= 0 && x < W && W >= 16) {
-            kind = kLabCross;
-            from = W - 16;
-        } else
-            kind = kLabSingle;
-    }
-
-    __device__ __forceinline__ bool vector() const { return kind != kLabNone && kind != kLabSingle; }
-
-    // The group's channel sums into the staged row S, from the vectors of its
-    // source pixels (or, pixel by pixel, from the row itself).
+struct LabStage : LabPlace {
     __device__ __forceinline__ void store(const v4u (&w)[C], const uint8_t* row, uint16_t* S, int px0, int W,
                                           int pad) const
     {
-        uint16_t* d = S + kLabLeft + x - px0;
         if (kind == kLabSingle) {
             for (int c = pa; c < pb; ++c) {
                 const g_u8* p = (const g_u8*)(row + (int64_t)edge_fold(c, W, pad) * C);
@@ -973,36 +895,13 @@ struct LabStage {
 #pragma unroll
                 for (int ch = 0; ch < C; ++ch)
                     sum += p[ch];
-                d[c - x] = (uint16_t)sum;
+                S[kLabLeft + c - px0] = (uint16_t)sum;
             }
             return;
         }
         v4u lo, hi;
         pixel_sums16<C>(w, lo, hi);
-        if (__builtin_expect(kind == kLabMirror, 0)) {
-            asm volatile("");   // a branch of its own: few lanes reverse
-            const v4u a = v4u{hi.w, hi.z, hi.y, hi.x}, b = v4u{lo.w, lo.z, lo.y, lo.x};
-            lo = (a >> 16) | (a << 16);
-            hi = (b >> 16) | (b << 16);
-        }
-        if (kind == kLabCross) {
-            // sums of the frame's last sixteen columns at their places, and
-            // reversed at the places that mirror them (what they overlap of
-            // the groups beside them, they write alike)
-            uint16_t* e = S + kLabLeft + from - px0;
-            uint16_t* m = S + kLabLeft + (pad == 1 ? W - 1 : W) - px0;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t pr = i < 4 ? lo[i & 3] : hi[i & 3];
-                e[2 * i] = m[15 - 2 * i] = (uint16_t)pr;
-                e[2 * i + 1] = m[14 - 2 * i] = (uint16_t)(pr >> 16);
-            }
-            return;
-        }
-        reinterpret_cast<v4u*>(d)[0] = lo;
-        reinterpret_cast<v4u*>(d)[1] = hi;
-        if (x == 0)
-            d[-1] = (uint16_t)(pad == 1 ? lo.x >> 16 : lo.x);
+        put(lo, hi, S, px0, W, pad);
     }
 };
 
@@ -1064,7 +963,7 @@ __device__ __forceinline__ void label_walk(const uint8_t* img, int64_t pitch, in
                                            int px0, int cols, int thr, uint16_t* S, int stride, Emit emit)
 {
     const int tid = threadIdx.x;
-    const int G = (cols + 16) / 16 + 1;              // groups of a staged row
+    const int G = label_groups(cols);
     const int srow = tid / G;
     const int nst = rows + 2, nblk = (nst + kLabBlock - 1) / kLabBlock;
     LabStage<C> st;

@@ -137,3 +137,31 @@ def test_edge_mask_tiles_starting_on_odd_columns(dev, H, W, C, b, K):
     want = oracle.forward(img, want_mask, oracle_params(fp))
     compare_frame(plan.store_host()[0], want, out.cpu().numpy(), "odd tile starts %dx%dx%d b%d K%d" % (H, W, C, b, K))
     plan.close()
+
+
+# (H, W, C, b, tile_cells): frames whose second walk of 992 columns starts in
+# the padding less than sixteen columns past the right edge, and tiles of
+# sixteen columns, whose second one starts a group after the frame's first
+WALKS = [(30, 985, 1, 64, 0), (26, 977, 1, 256, 0), (26, 991, 1, 24, 0), (14, 986, 1, 12, 0), (22, 981, 1, 20, 0),
+         (25, 1971, 1, 24, 0), (9, 991, 1, 3, 0), (40, 985, 3, 64, 16), (33, 100, 3, 16, 1), (17, 64, 1, 8, 2)]
+
+
+@pytest.mark.parametrize("pad", [0, 1, 2])
+def test_plan_labels_of_walks_past_the_edge(dev, pad):
+    say("case: plan_labels, walks that start past the right edge", pad)
+    r = np.random.Generator(np.random.PCG64(60 + pad))
+    fps = [dp.FrameParams(H, W, C, dp.U8_HWC, b=b, sb=b, m=8, tau=1 + i % 3, pad_mode=pad, tile_cells=k)
+           for i, (H, W, C, b, k) in enumerate(WALKS)]
+    imgs = [r.integers(0, 256, (H, W, C)).astype(np.uint8) // (1 + 9 * (r.random((H, W, 1)) < 0.7)).astype(np.uint8)
+            for H, W, C, b, k in WALKS]
+    ti = [torch.from_numpy(x).to(dev) for x in imgs]
+    plan = dp.Plan(fps, device=dev)
+    one, two = plan.new_store(), plan.new_store()
+    plan.plan(plan.edge_masks(ti, 90), store=two)
+    plan.plan_labels(ti, 90, store=one)
+    torch.cuda.synchronize()
+    assert torch.equal(one.flags, two.flags) and torch.equal(one.counts, two.counts)
+    for f, x, got in zip(fps, imgs, one.host()):
+        want = oracle.forward(x, oracle.edge_mask(x, 90, pad), oracle_params(f))
+        assert np.array_equal(got["flags"], want["flags"]), (f.width, f.b)
+    plan.close()

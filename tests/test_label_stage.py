@@ -1,0 +1,24 @@
+"""The label kernels' staging of channel sums, run on the host: its index code
+(which pixels a 16-column group reads, where their sums go) is compiled with
+AddressSanitizer and walked over widths, cell sizes, tile widths and border
+modes, for the label masks and for plans from labels (walks that start inside
+the frame, at its edge and in its padding).  No GPU is needed."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+
+
+@pytest.mark.skipif(not os.path.exists(CLANG), reason="needs ROCm's clang")
+def test_staged_columns_of_every_walk(tmp_path):
+    exe = str(tmp_path / "label_stage")
+    subprocess.check_call([CLANG, "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-std=c++17", "-O2", "-g",
+                           "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-Wno-unused-result",
+                           "-I", os.path.join(ROOT, "paper_2511_04261_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "sanitize", "label_stage_driver.cpp"), "-o", exe])
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0")
+    r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), (r.stdout + r.stderr)[-4000:]
