@@ -383,12 +383,14 @@ class Plan:
             raise ValueError("need one tensor per frame (%d), got %d" % (len(self.frames), len(ptrs)))
         return self._table(tuple(ptrs), stream)
 
-    def _table(self, key, stream=None):
-        """The table of a tuple of device addresses (pointer_table)."""
+    def _table(self, key, stream=None, addresses=None):
+        """The table of a tuple of device addresses (pointer_table), or of
+        what ``addresses()`` lists.  The cache is looked at once: another
+        thread's call may evict the table at any time."""
         torch = _torch()
         tab = self._tables.get(key)
         if tab is None:
-            tab = torch.tensor(key, dtype=torch.int64).to(self.device)
+            tab = torch.tensor(key if addresses is None else addresses(), dtype=torch.int64).to(self.device)
             self._tables[key] = tab
             while len(self._tables) > self.MAX_TABLES:
                 self._tables.popitem(last=False)
@@ -462,16 +464,8 @@ class Plan:
     def _batch_table(self, x):
         """The pointer table of a batch that the plan holds, kept by its base
         address (the images follow from it)."""
-        base = x.data_ptr()
-        key = (base,)
-        if key not in self._tables and len(self.frames) > 1:
-            step = 4 * x.stride(0)
-            tab = _torch().tensor([base + i * step for i in range(x.shape[0])], dtype=_torch().int64).to(self.device)
-            self._tables[key] = tab
-            while len(self._tables) > self.MAX_TABLES:
-                self._tables.popitem(last=False)
-            return tab
-        return self._table(key)
+        base, step = x.data_ptr(), 4 * x.stride(0)
+        return self._table((base,), None, lambda: [base + i * step for i in range(len(self.frames))])
 
     def _call_layout(self):
         """Byte offsets of what a call's backward reads, in one buffer: flags,

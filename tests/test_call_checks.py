@@ -109,3 +109,31 @@ def test_overlap_by_addresses_agrees_with_the_spans():
             assert want is None, d
         except ValueError as e:
             assert str(e) == want, d
+
+
+class _Evicting(dict):
+    """A table cache that another thread empties after every look at it."""
+
+    def __contains__(self, key):
+        found = super().__contains__(key)
+        self.clear()
+        return found or True
+
+    def move_to_end(self, key):
+        pass
+
+    def popitem(self, last=True):
+        raise AssertionError("nothing to evict")
+
+
+@pytest.mark.parametrize("n", [1, 3])
+def test_batch_table_holds_every_image_when_it_was_evicted(n):
+    """A batch's pointer table has one address per frame, also where the table
+    of its base address goes away between two looks at the cache (the kernels
+    read an entry per frame)."""
+    plan = dp.Plan.__new__(dp.Plan)
+    plan.frames, plan.device, plan._tables = [None] * n, torch.device("cpu"), _Evicting()
+    x = torch.zeros((n, 3, 4, 5))
+    for _ in range(2):
+        assert plan._batch_table(x).tolist() == [x[i].data_ptr() for i in range(n)]
+        plan._tables.clear()
