@@ -62,12 +62,12 @@ struct dppix_plan {
     int64_t n_tiles = 0;
     int64_t n_units = 0;
     // units of the metrics, the plan from labels and the label masks: those of
-    // the frames with C channels are [lo[C - 1], lo[C]) of their map
+    // the frames with C channels are the spans [chan[C - 1], chan[C])
     int32_t met_rows = 0, edge_rows = 0;    // rows of a unit
-    std::vector<int64_t> met_lo, lab_lo, edge_lo;
+    std::vector<UnitSpan> met, lab, edge, border;
+    int32_t chan[5] = {0, 0, 0, 0, 0};
     int lab_threads = 64, edge_threads = 64;
     size_t lab_cells = 0;               // counters of the largest unit of the plan from labels
-    int64_t n_border = 0;               // tiles with pixels that mirrored padding folds onto
     bool prefix_scan = false;           // the plan's scan needs no hand-off between workgroups
     int64_t total_cells = 0;
     int64_t total_fine = 0;
@@ -300,40 +300,25 @@ void spread_units(dppix_plan& p)
         p.lds[kPlan] = std::max<size_t>(p.lds[kPlan], plan_lds(F.cnb, F.ctx, F.K));
 }
 
-// A map of units, frames of one channel count after another (lo: see
-// dppix_plan): (frame, unit within frame) pairs; first: each frame's first
-// unit and their number.
+// Spans of the units of frames in the order given; units(F): a frame's.
 template <typename Units>
-void map_units(const dppix_plan& p, Units units, std::vector<int32_t>& map, std::vector<int64_t>& lo,
-               std::vector<int64_t>* first)
+std::vector<UnitSpan> span_units(const dppix_plan& p, const std::vector<int32_t>& order, Units units)
 {
-    const int32_t n = (int32_t)p.frames.size();
-    lo.assign(5, 0);
-    if (first != nullptr)
-        first->assign(2 * (size_t)n, 0);
-    for (int C = 1; C <= 4; ++C) {
-        for (int32_t f = 0; f < n && !p.any_f32; ++f) {   // (the metrics and labels take bytes)
-            if (p.frames[f].C != C)
-                continue;
-            const int64_t u = units(p.frames[f]);
-            if (first != nullptr) {
-                (*first)[2 * (size_t)f] = (int64_t)map.size() / 2;
-                (*first)[2 * (size_t)f + 1] = u;
-            }
-            const size_t at = map.size();
-            map.resize(at + 2 * (size_t)u);
-            for (int64_t i = 0; i < u; ++i) {
-                map[at + 2 * i] = f;
-                map[at + 2 * i + 1] = (int32_t)i;
-            }
-        }
-        lo[C] = (int64_t)map.size() / 2;
+    std::vector<UnitSpan> out(order.size() + 1);
+    int64_t at = 0;
+    for (size_t k = 0; k < order.size(); ++k) {
+        out[k] = UnitSpan{at, order[k], 0};
+        at += units(p.frames[order[k]]);
     }
+    out.back() = UnitSpan{at, 0, 0};
+    return out;
 }
+
+int64_t span_total(const std::vector<UnitSpan>& spans) { return spans.empty() ? 0 : spans.back().first; }
 
 // Rows of a unit, step * m - over for the largest m up to `most` that gives
 // the batch `wanted` units; units(F, rows) counts a frame's.  Huge batches:
-// no more units than twice the tiles (the map's size).
+// no more units than twice the tiles (a launch has at most 2^31).
 template <typename Units>
 int32_t unit_rows(const dppix_plan& p, Units units, int32_t step, int32_t over, int32_t most, int64_t wanted)
 {
@@ -553,39 +538,40 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
     w.frames = o;      o = align256(o + sizeof(FrameRec) * n_frames);
     w.tile_map = o;    o = align256(o + sizeof(int32_t) * 2 * (size_t)p->n_tiles);
     w.unit_map = o;    o = align256(o + sizeof(int32_t) * 2 * (size_t)p->n_units);
-    // Tiles of the adjoint's mirror pass: those holding a real pixel that a
-    // padded row or column folds onto (the same test the kernel applies).
-    std::vector<int32_t> border;
-    for (int32_t f = 0; f < n_frames; ++f) {
-        const FrameRec& F = p->frames[f];
-        if (F.pad == DPPIX_PAD_NONE)
-            continue;
-        for (int32_t r = 0; r < F.GR; ++r) {
-            // a band above the folded rows: the tiles from the first folded column on
-            const BorderArea band = border_area(F, r, 0);
-            const int32_t ct0 = band.n_a > 0 ? 0 : std::min(F.TX, band.lo_c / (F.K * F.b));
-            for (int32_t ct = ct0; ct < F.TX; ++ct) {
-                const BorderArea m = border_area(F, r, ct);
-                const int32_t parts = (int32_t)(((m.n_a + m.n_b) * F.C + kBorderItems - 1) / kBorderItems);
-                for (int32_t k = 0; k < parts; ++k)
-                    border.insert(border.end(), {f, r * F.TX + ct, k, parts});
-            }
-        }
-    }
-    p->n_border = (int64_t)border.size() / 4;
-    w.border_map = o;  o = align256(o + sizeof(int32_t) * border.size());
     w.simple_counts = o; o = align256(o + sizeof(uint64_t) * 4 * (size_t)n_frames);
-    std::vector<int32_t> met_map, lab_map, edge_map;
-    std::vector<int64_t> met_base;
-    p->met_rows = unit_rows(*p, metrics_units, 7, 6, 10, kMetUnits);
-    p->edge_rows = unit_rows(*p, edge_units, 4, 2, 4, kEdgeUnits);
-    map_units(*p, [&](const FrameRec& F) { return metrics_units(F, p->met_rows); }, met_map, p->met_lo, &met_base);
-    map_units(*p, [&](const FrameRec& F) { return edge_units(F, p->edge_rows); }, edge_map, p->edge_lo, nullptr);
-    map_units(*p, [&](const FrameRec& F) { return F.TX * ceil_div(F.GR, F.lnb); }, lab_map, p->lab_lo, nullptr);
-    w.lab_map = o;     o = align256(o + sizeof(int32_t) * lab_map.size());
-    w.edge_map = o;    o = align256(o + sizeof(int32_t) * edge_map.size());
-    w.met_map = o;     o = align256(o + sizeof(int32_t) * met_map.size());
-    w.met_base = o;    o = align256(o + sizeof(int64_t) * met_base.size());
+    // Units of the kernels with units of their own, by frame: the metrics and
+    // the labels take bytes, frames of one channel count after another (a
+    // launch each), the adjoint floats.
+    std::vector<int32_t> by_chan;
+    if (p->any_f32) {
+        for (int32_t f = 0; f < n_frames; ++f)
+            if (p->frames[f].pad != DPPIX_PAD_NONE && !p->any_u8)
+                by_chan.push_back(f);
+        p->border = span_units(*p, by_chan, [](const FrameRec& F) {
+            const BorderArea m = border_area(F);
+            return (int64_t)F.C * (border_parts(m.nA) + border_parts(m.nB));
+        });
+    } else {
+        for (int C = 1; C <= 4; ++C) {
+            for (int32_t f = 0; f < n_frames; ++f)
+                if (p->frames[f].C == C)
+                    by_chan.push_back(f);
+            p->chan[C] = (int32_t)by_chan.size();
+        }
+        p->met_rows = unit_rows(*p, metrics_units, 7, 6, 10, kMetUnits);
+        p->edge_rows = unit_rows(*p, edge_units, 4, 2, 4, kEdgeUnits);
+        p->met = span_units(*p, by_chan, [&](const FrameRec& F) { return metrics_units(F, p->met_rows); });
+        p->edge = span_units(*p, by_chan, [&](const FrameRec& F) { return edge_units(F, p->edge_rows); });
+        p->lab = span_units(*p, by_chan, [](const FrameRec& F) { return F.TX * ceil_div(F.GR, F.lnb); });
+    }
+    auto place = [&](size_t& at, const std::vector<UnitSpan>& spans) {
+        at = o;
+        o = align256(o + sizeof(UnitSpan) * spans.size());
+    };
+    place(w.border_spans, p->border);
+    place(w.lab_spans, p->lab);
+    place(w.edge_spans, p->edge);
+    place(w.met_spans, p->met);
     w.total = o;
     // Per-call state carried by each store.
     StateLayout& sl = p->st;
@@ -607,8 +593,6 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
         }
     for (const LaunchGroup& g : p->groups)
         xcd_runs(map, g.lo, g.hi);
-    if (!border.empty())
-        std::memcpy(p->host_tables.data() + w.border_map, border.data(), sizeof(int32_t) * border.size());
     {
         // without masks every cell is simple: n_bg = cells, n_fg = 0, and the
         // frames' statistics packed back to back in batch order
@@ -624,13 +608,13 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
             bg_off += cells * (uint64_t)F.C;
         }
     }
-    auto put = [&](size_t at, const std::vector<int32_t>& map) {
-        std::copy(map.begin(), map.end(), reinterpret_cast<int32_t*>(p->host_tables.data() + at));
+    auto put = [&](size_t at, const std::vector<UnitSpan>& spans) {
+        std::copy(spans.begin(), spans.end(), reinterpret_cast<UnitSpan*>(p->host_tables.data() + at));
     };
-    put(w.lab_map, lab_map);
-    put(w.edge_map, edge_map);
-    put(w.met_map, met_map);
-    std::memcpy(p->host_tables.data() + w.met_base, met_base.data(), sizeof(int64_t) * met_base.size());
+    put(w.border_spans, p->border);
+    put(w.lab_spans, p->lab);
+    put(w.edge_spans, p->edge);
+    put(w.met_spans, p->met);
     int32_t* umap = reinterpret_cast<int32_t*>(p->host_tables.data() + w.unit_map);
     for (int32_t f = 0, u = 0; f < n_frames; ++f)
         for (int32_t i = 0; i < p->frames[f].cunits; ++i, ++u) {
@@ -655,7 +639,7 @@ dppix_status_t dp_pix_plan_sizes(dppix_plan_t p, dppix_sizes_t* out)
     out->clip_bytes_bg = p->bg_cap;
     out->clip_bytes_fg = p->fg_cap;
     out->grad_scratch_bytes = grad_scratch_need(p);
-    out->metrics_scratch_bytes = align256(16 * (size_t)std::max(p->n_tiles, p->met_lo[4]));
+    out->metrics_scratch_bytes = align256(16 * (size_t)std::max(p->n_tiles, span_total(p->met)));
     out->n_tiles = p->n_tiles;
     out->total_pixels = p->total_pixels;
     out->forward_launches = (int64_t)p->groups.size();
@@ -823,6 +807,25 @@ int grid_for(dppix_plan_t p, int layout, int C, int threads, int64_t tiles, size
     return (int)std::max<int64_t>(1, g);
 }
 
+// One launch per channel count that the batch has, over the units of its frames.
+template <typename Launch>
+hipError_t for_channels(dppix_plan_t p, const TileArgs& base, const std::vector<UnitSpan>& spans, size_t at, Launch launch)
+{
+    for (int C = 1; C <= 4; ++C) {
+        const int32_t lo = p->chan[C - 1], n = p->chan[C] - lo;
+        if (n == 0)
+            continue;
+        TileArgs a = base;
+        a.spans = reinterpret_cast<const UnitSpan*>(p->bound + at) + lo;
+        a.n_spans = n;
+        a.sched_offset = spans[lo].first;
+        const hipError_t e = launch(a, C, spans[lo + n].first - spans[lo].first);
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
+}
+
 // One launch per group: its scheduling range and its own ticket pair.
 template <typename Launch>
 hipError_t for_groups(dppix_plan_t p, const TileArgs& base, bool rec, Launch launch)
@@ -937,13 +940,9 @@ dppix_status_t dp_pix_plan_labels(dppix_plan_t p, const void* const* images, int
     a.images = images;
     a.edge_threshold = threshold;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    a.lab_map = reinterpret_cast<const int32_t*>(p->bound + p->ws.lab_map);
-    hipError_t e = hipSuccess;
-    for (int C = 1; C <= 4 && e == hipSuccess; ++C) {
-        a.sched_offset = p->lab_lo[C - 1];
-        e = launch_plan_labels(a, C, p->lab_lo[C] - p->lab_lo[C - 1], p->lab_threads,
-                               label_lds(p->lab_threads) + 4 * p->lab_cells, s);
-    }
+    hipError_t e = for_channels(p, a, p->lab, p->ws.lab_spans, [&](const TileArgs& ca, int C, int64_t units) {
+        return launch_plan_labels(ca, C, units, p->lab_threads, label_lds(p->lab_threads) + 4 * p->lab_cells, s);
+    });
     if (e == hipSuccess)
         e = launch_scan(a, p->prefix_scan, s);
     if (e != hipSuccess)
@@ -1064,11 +1063,12 @@ dppix_status_t run_backward(dppix_plan_t p, const dppix_store_t* store, const fl
                                           grid_for(p, 1, 1, plain_threads(p), p->n_tiles, p->lds[kBwd]), s);
     if (e != hipSuccess)
         return dev_fail(e, "backward launch");
-    // 2. mirror terms of the pixels near padded borders: only the border
-    // tiles, and no launch at all when no frame is padded
-    if (p->n_border > 0) {
-        e = launch_backward_mirror(a, reinterpret_cast<const int32_t*>(p->bound + p->ws.border_map), p->n_border,
-                                   plain_threads(p), s);
+    // 2. mirror terms of the pixels near padded borders: no launch at all
+    // when no frame is padded
+    if (span_total(p->border) > 0) {
+        a.spans = reinterpret_cast<const UnitSpan*>(p->bound + p->ws.border_spans);
+        a.n_spans = (int32_t)p->border.size() - 1;
+        e = launch_backward_mirror(a, span_total(p->border), plain_threads(p), s);
         if (e != hipSuccess)
             return dev_fail(e, "backward launch");
     }
@@ -1121,15 +1121,12 @@ dppix_status_t dp_pix_edge_mask(dppix_plan_t p, const void* const* images, int32
     a.masks_out = masks_out;
     a.edge_threshold = threshold;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    a.edge_map = reinterpret_cast<const int32_t*>(p->bound + p->ws.edge_map);
     a.edge_rows = p->edge_rows;
-    for (int C = 1; C <= 4; ++C) {
-        a.sched_offset = p->edge_lo[C - 1];
-        hipError_t e = launch_edge_mask(a, C, p->edge_lo[C] - p->edge_lo[C - 1], p->edge_threads,
-                                        label_lds(p->edge_threads), s);
-        if (e != hipSuccess)
-            return dev_fail(e, "edge mask launch");
-    }
+    hipError_t e = for_channels(p, a, p->edge, p->ws.edge_spans, [&](const TileArgs& ca, int C, int64_t units) {
+        return launch_edge_mask(ca, C, units, p->edge_threads, label_lds(p->edge_threads), s);
+    });
+    if (e != hipSuccess)
+        return dev_fail(e, "edge mask launch");
     return DPPIX_OK;
 }
 
@@ -1143,23 +1140,21 @@ dppix_status_t dp_pix_metrics(dppix_plan_t p, const void* const* images, const v
         return fail(DPPIX_EINVAL, "metrics are computed on U8_HWC frames");
     if (images == nullptr || recons == nullptr || out == nullptr)
         return fail(DPPIX_EINVAL, "images, recons and out are required");
-    if (scratch == nullptr || scratch_bytes < 16 * (size_t)p->met_lo[4])
+    if (scratch == nullptr || scratch_bytes < 16 * (size_t)span_total(p->met))
         return fail(DPPIX_ENOMEM, "scratch smaller than metrics_scratch_bytes");
     TileArgs a = base_args(p, nullptr);
     a.images = images;
     a.outs = const_cast<void* const*>(recons);
-    a.met_map = reinterpret_cast<const int32_t*>(p->bound + p->ws.met_map);
-    a.met_base = reinterpret_cast<const int64_t*>(p->bound + p->ws.met_base);
     a.met_partial = static_cast<double*>(scratch);
     a.met_rows = p->met_rows;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    for (int C = 1; C <= 4; ++C) {
-        a.sched_offset = p->met_lo[C - 1];
-        hipError_t e = launch_metrics(a, C, p->met_lo[C] - p->met_lo[C - 1], s);
-        if (e != hipSuccess)
-            return dev_fail(e, "metrics launch");
-    }
-    hipError_t e = launch_metrics_reduce(a, out, s);
+    hipError_t e = for_channels(p, a, p->met, p->ws.met_spans, [&](const TileArgs& ca, int C, int64_t units) {
+        return launch_metrics(ca, C, units, s);
+    });
+    if (e != hipSuccess)
+        return dev_fail(e, "metrics launch");
+    a.spans = reinterpret_cast<const UnitSpan*>(p->bound + p->ws.met_spans);
+    e = launch_metrics_reduce(a, out, s);
     if (e != hipSuccess)
         return dev_fail(e, "metrics reduce launch");
     return DPPIX_OK;

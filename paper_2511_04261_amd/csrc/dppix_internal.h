@@ -74,39 +74,82 @@ struct FrameRec {
     uint32_t key0, key1, fi0, fi1;
 };
 
-// The pixels of a tile that padded rows or columns fold onto: rows [ra, y1) of
-// columns [xa, xb) (n_a of them) and rows [y0, rb) of columns [ca, xb) (n_b).
-struct BorderArea {
-    int xa, xb, y0, y1, ra, rb, ca;
-    int lo_c;                 // first column that may be folded onto
-    int64_t n_a, n_b;
+// Units of a batch by frame: entry k says that the k-th frame with units of a
+// kind is `frame` and its first unit `first`; the entry after the last holds the
+// number of units.  A kernel finds its unit's frame by a search that a wave
+// does together, one load for 64 frames, so the table grows with the frames
+// alone.  (Maps with an entry per unit were written and uploaded with every
+// plan.  dp_pix_plan_create on the host, with them and now: 256 frames of 576 x
+// 768 to 4000 x 6000: 6.6 -> 0.41 ms, workspace 6.1 -> 1.5 MB; 64 of 1300 x
+// 2050, b 256: 5.7 ms -> 16 us; 16 fp32 of 2161 x 3841, b 256: 451 -> 5 us.  The
+// search costs a kernel about 0.3 us.)
+struct UnitSpan {
+    int64_t first;
+    int32_t frame, pad_;
 };
 
-__host__ __device__ inline BorderArea border_area(const FrameRec& F, int r, int ct)
+// The pixels that padded rows or columns fold onto: all columns of rows [ra,
+// re) (nA of them), and columns [ca, ce) of the other rows (nB).  A padding
+// that folds more than once may reach any row (column).
+struct BorderArea {
+    int ra, re, ca, ce;
+    uint32_t nA, nB;          // (fewer than 256 padded rows or columns: below 2^32)
+};
+
+__host__ __device__ inline BorderArea border_area(const FrameRec& F)
 {
-    auto lo = [](int x, int y) { return x < y ? x : y; };
-    auto hi = [](int x, int y) { return x > y ? x : y; };
-    BorderArea m;
-    const int x0c = ct * F.K, Kt = lo(F.K, F.GC - x0c);
-    m.y0 = r * F.b;
-    m.y1 = lo(m.y0 + F.b, F.H);
-    m.xa = x0c * F.b;
-    m.xb = lo((x0c + Kt) * F.b, F.W);
     const int PR = F.GR * F.b - F.H, PC = F.GC * F.b - F.W;
-    // rows at or above lo_r (columns at or above lo_c) may have mirror preimages
-    const int lo_r = PR > 0 ? (PR <= F.H - 1 ? F.H - 1 - PR : 0) : F.H;
-    m.lo_c = PC > 0 ? (PC <= F.W - 1 ? F.W - 1 - PC : 0) : F.W;
-    m.ra = hi(m.y0, lo_r);
-    m.rb = lo(m.y1, lo_r);
-    m.ca = hi(m.xa, m.lo_c);
-    m.n_a = m.ra < m.y1 ? (int64_t)(m.y1 - m.ra) * (m.xb - m.xa) : 0;
-    m.n_b = m.rb > m.y0 && m.xb > m.ca ? (int64_t)(m.rb - m.y0) * (m.xb - m.ca) : 0;
+    const int edge = F.pad == 1 ? 1 : 0;   // the reflected mode does not repeat the last row
+    BorderArea m;
+    m.ra = PR <= F.H - edge ? F.H - edge - PR : 0;
+    m.re = PR <= F.H - edge ? F.H - edge : F.H;
+    m.ca = PC <= F.W - edge ? F.W - edge - PC : 0;
+    m.ce = PC <= F.W - edge ? F.W - edge : F.W;
+    m.nA = (uint32_t)(m.re - m.ra) * (uint32_t)F.W;
+    m.nB = (uint32_t)(F.H - (m.re - m.ra)) * (uint32_t)(m.ce - m.ca);
     return m;
 }
 
-// Items (channels x pixels) of a workgroup of the mirror pass: a lane's loads
-// are two levels deep, so a large tile is shared out rather than walked.
-constexpr int kBorderItems = 512;
+// A unit of the mirror pass: up to kBorderPixels pixels of one channel and one
+// of the two areas, row by row (a lane's loads are two levels deep, so they are
+// shared out).
+constexpr uint32_t kBorderPixels = 512;
+__host__ __device__ inline uint32_t border_parts(uint32_t n) { return n / kBorderPixels + (n % kBorderPixels != 0); }
+
+struct BorderPart {
+    int ch, y0, x0;           // channel, and row and column of pixel p0 within the area
+    bool rows;                // of the area of whole rows
+    uint32_t wide;            // of the area
+    int n;                    // pixels
+
+    __host__ __device__ inline BorderPart(const BorderArea& m, int W, int unit)
+    {
+        const uint32_t parts_a = border_parts(m.nA), parts = parts_a + border_parts(m.nB);
+        ch = (int)((uint32_t)unit / parts);
+        const uint32_t part = (uint32_t)unit - (uint32_t)ch * parts;
+        rows = part < parts_a;
+        wide = rows ? (uint32_t)W : (uint32_t)(m.ce - m.ca);
+        const uint32_t p0 = (part - (rows ? 0u : parts_a)) * kBorderPixels, left = (rows ? m.nA : m.nB) - p0;
+        n = (int)(left < kBorderPixels ? left : kBorderPixels);
+        y0 = (int)(p0 / wide);
+        x0 = (int)(p0 - (uint32_t)y0 * wide);
+    }
+
+    // The frame's row and column of pixel k; by_wide divides by `wide`.
+    template <typename Div>
+    __host__ __device__ inline void pixel(const BorderArea& m, int k, const Div& by_wide, int& y, int& x) const
+    {
+        const int q = by_wide(x0 + k);
+        y = y0 + q;
+        x = x0 + k - q * (int)wide;
+        if (rows)
+            y += m.ra;
+        else {
+            y += y < m.ra ? 0 : m.re - m.ra;
+            x += m.ca;
+        }
+    }
+};
 
 // Workspace layout of a plan (byte offsets from the bound workspace base):
 // tables written once by dp_pix_plan_bind and only read afterwards, so one
@@ -115,11 +158,10 @@ struct WsLayout {
     size_t frames;        // FrameRec[n_frames]
     size_t tile_map;      // int32[n_tiles][2]: (frame, tile within frame) per scheduling index
     size_t unit_map;      // int32[n_units][2]: (frame, plan unit within frame), frame-major
-    size_t border_map;    // int32[n_border][4]: (frame, tile, part, parts) of the adjoint's mirror pass
-    size_t lab_map;       // int32[n_lab][2]: (frame, unit within frame) of the plan from labels, by channel count
-    size_t edge_map;      // int32[n_edge][2]: the same of the label masks
-    size_t met_map;       // int32[n_met][2]: (frame, unit within frame) of the metrics, by channel count
-    size_t met_base;      // int64[n_frames][2]: first metrics unit of each frame, and their number
+    size_t border_spans;  // UnitSpan[fp32 frames + 1]: units of the adjoint's mirror pass
+    size_t lab_spans;     // UnitSpan[u8 frames + 1], by channel count: units of the plan from labels
+    size_t edge_spans;    // the same of the label masks
+    size_t met_spans;     // the same of the metrics
     size_t simple_counts; // uint64[n_frames][4]: store counts of a call without masks (every cell simple)
     size_t total;
 };
@@ -174,12 +216,12 @@ struct TileArgs {
     // complexity label
     uint8_t* const* masks_out;
     int32_t edge_threshold;
-    const int32_t* lab_map;
-    const int32_t* edge_map;
     int32_t edge_rows;        // rows of a label mask unit
+    // units of the label kernels, the metrics and the mirror pass: the spans
+    // of this launch's frames (one more entry than frames)
+    const UnitSpan* spans;
+    int32_t n_spans;
     // utility metrics: per unit (SSIM partial sum, squared-error sum)
-    const int32_t* met_map;
-    const int64_t* met_base;
     double* met_partial;
     int32_t met_rows;         // rows of a metrics unit
 };
@@ -297,8 +339,7 @@ hipError_t launch_forward(const TileArgs& a, int layout, int C, int threads, siz
 hipError_t launch_reconstruct(const TileArgs& a, int layout, int C, int threads, size_t lds, int grid,
                               hipStream_t s);
 hipError_t launch_backward_reduce(const TileArgs& a, int threads, size_t lds, int grid, hipStream_t s);
-hipError_t launch_backward_mirror(const TileArgs& a, const int32_t* border_map, int64_t n_border, int threads,
-                                  hipStream_t s);
+hipError_t launch_backward_mirror(const TileArgs& a, int64_t n_units, int threads, hipStream_t s);
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
 hipError_t launch_noise_advance(uint64_t* noise, int32_t n, uint64_t step, hipStream_t s);
 hipError_t launch_edge_mask(const TileArgs& a, int C, int64_t n_units, int threads, size_t lds, hipStream_t s);

@@ -210,6 +210,19 @@ struct FastDiv {
     __device__ __forceinline__ int operator()(int x) const { return (int)fmaf((float)x, inv, half); }
 };
 
+// The same for 0 <= x < 2^24: the quotient is at most one off (a reciprocal one
+// ulp off, d >= 3; those of 1 and 2 are exact), and the remainder says which way.
+struct WideDiv {
+    FastDiv by;
+    int d;
+    __device__ __forceinline__ explicit WideDiv(int d_) : by(d_), d(d_) {}
+    __device__ __forceinline__ int operator()(int x) const
+    {
+        const int q = by(x), r = x - q * d;
+        return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
+    }
+};
+
 // 1 / side^2 when that is exact and every statistic of that side has area
 // side^2 (mirror padding, side a power of two), else 0.
 __device__ __forceinline__ double exact_inv_area(const FrameRec& F, int side)
@@ -393,6 +406,37 @@ __device__ __forceinline__ TileCoord tile_of(const TileArgs& a, int64_t sched_id
     tc.r = (int)(local / (uint32_t)F.TX);
     tc.ct = (int)(local - (uint32_t)tc.r * (uint32_t)F.TX);
     return tc;
+}
+
+// The frame of a unit and the unit's number within it, by the launch's spans:
+// each wave compares 64 of them at a time (one load up to 64 frames, two up to
+// 4096).  Every lane of the wave calls it.
+struct UnitCoord {
+    int f, local;
+};
+
+__device__ __forceinline__ UnitCoord unit_of(const TileArgs& a, int64_t unit)
+{
+    const int lane = threadIdx.x & 63;
+    const auto* spans = (const __attribute__((address_space(1))) UnitSpan*)a.spans;
+    int lo = 0, n = a.n_spans;
+    while (n > 64) {
+        const int step = (n + 63) >> 6, at = lane * step;
+        const bool before = at < n && spans[lo + at].first <= unit;
+        const int last = __popcll(__ballot(before)) - 1;
+        lo += last * step;
+        n = min(step, n - last * step);
+    }
+    UnitSpan s = {0, 0, 0};
+    if (lane < n) {
+        s.first = spans[lo + lane].first;
+        s.frame = spans[lo + lane].frame;
+    }
+    const int last = __popcll(__ballot(lane < n && s.first <= unit)) - 1;
+    UnitCoord u;
+    u.f = __builtin_amdgcn_readlane(s.frame, last);
+    u.local = (int)unit - __builtin_amdgcn_readlane((int)s.first, last);   // (below 2^31, whatever the high words)
+    return u;
 }
 
 // ==========================================================================
@@ -1035,8 +1079,8 @@ __global__ __launch_bounds__(256) void k_plan_labels(TileArgs a)
     extern __shared__ __align__(16) uint8_t lds[];
     const int tid = threadIdx.x, NT = blockDim.x;
     const int64_t unit = a.sched_offset + blockIdx.x;
-    const int f = (int)uniform_u32((uint32_t)a.lab_map[2 * unit]);
-    const int local = (int)uniform_u32((uint32_t)a.lab_map[2 * unit + 1]);
+    const UnitCoord u = unit_of(a, unit);
+    const int f = u.f, local = u.local;
     const FrameRec& F = a.frames[f];
     const int b = F.b, K = F.K, W = F.W, pad = F.pad;
     const int r0 = (local / F.TX) * F.lnb, ct = local % F.TX;
@@ -2345,45 +2389,35 @@ __device__ __forceinline__ float g_at(const TileArgs& a, const FrameRec& F, int 
 // grad_in (broadcast by the reduction's tile), so only
 // the pixels that have mirror preimages are visited, and only the mirror
 // terms are added.  Nothing to do in the unpadded mode.
-__global__ __launch_bounds__(kMaxThreads) void k_backward_mirror(TileArgs a, const int32_t* border_map)
+__global__ __launch_bounds__(kMaxThreads) void k_backward_mirror(TileArgs a)
 {
-    const int64_t idx = 4 * (int64_t)blockIdx.x;
-    const int f = (int)uniform_u32((uint32_t)border_map[idx]);
-    const uint32_t tile = uniform_u32((uint32_t)border_map[idx + 1]);
-    const uint32_t part = uniform_u32((uint32_t)border_map[idx + 2]), parts = uniform_u32((uint32_t)border_map[idx + 3]);
+    const UnitCoord u = unit_of(a, blockIdx.x);
+    const int f = u.f;
     const FrameRec& F = a.frames[f];
-    const int b = F.b, H = F.H, W = F.W, C = F.C, pad = F.pad;
-    const int tr = (int)(tile / (uint32_t)F.TX), ct = (int)(tile % (uint32_t)F.TX), x0c = ct * F.K;
-    const BorderArea m = border_area(F, tr, ct);
+    const int b = F.b, H = F.H, W = F.W, pad = F.pad;
+    const BorderArea m = border_area(F);
+    const BorderPart part(m, W, u.local);
+    const int ch = part.ch;
     const int PR = F.GR * b - H, PC = F.GC * b - W;
-    const uint32_t wA = (uint32_t)(m.xb - m.xa), wB = (uint32_t)(m.xb - m.ca), nA = (uint32_t)m.n_a;
     const int64_t pitch = F.pitch, plane = pitch * H;
-    g_f32w* gi = (g_f32w*)a.grad_in[f];
+    g_f32w* gi = (g_f32w*)a.grad_in[f] + plane * ch;
     // Where the padding folds onto the frame once, a pixel has at most one
     // padded row and one padded column, which lie in the last band and the
     // last column of cells: their statistics' loads are all in flight
-    // together, an item per (channel, pixel).  (64 x 3 x 218 x 178, b 8: the
-    // adjoint 88.5 -> 27 us; a search over the padding, channel after channel,
-    // was one chain of dependent loads, every position's cell a division, and one
-    // workgroup walked the whole of a tile.)
+    // together.  (64 x 3 x 218 x 178, b 8: the adjoint 88.5 -> 27 us; a search
+    // over the padding, channel after channel, was one chain of dependent
+    // loads, every position's cell a division, and one workgroup walked the
+    // whole of a tile.)
     const int last = pad == 0 ? 1 : 2;              // mirror of y: 2 H - last - y
     const bool once = PR <= H - (last - 1) && PC <= W - (last - 1);
-    const uint32_t nn = (uint32_t)(m.n_a + m.n_b);
-    const FastDiv by_b(b), by_s(F.s);
-    for (uint32_t it = part * blockDim.x + threadIdx.x; it < C * nn; it += parts * blockDim.x) {
-        const int ch = (int)(it / nn);
-        const uint32_t q = it - ch * nn;
+    const FastDiv by_s(F.s);
+    const WideDiv by_b(b), by_wide((int)part.wide);
+    for (int k = threadIdx.x; k < part.n; k += blockDim.x) {
         int y, x;
-        if (q < nA) {
-            y = m.ra + (int)(q / wA);
-            x = m.xa + (int)(q % wA);
-        } else {
-            y = m.y0 + (int)((q - nA) / wB);
-            x = m.ca + (int)((q - nA) % wB);
-        }
-        g_f32w* dst = gi + plane * ch + (int64_t)y * pitch + x;
-        const int dc = by_b(x - m.xa), cx = x0c + dc;
-        const int i = by_s(y - m.y0), j = by_s(x - m.xa - dc * b);
+        part.pixel(m, k, by_wide, y, x);
+        g_f32w* dst = gi + (int64_t)y * pitch + x;
+        const int cy = by_b(y), cx = by_b(x);
+        const int i = by_s(y - cy * b), j = by_s(x - cx * b);
         float acc = 0.f;
         if (once) {
             const int yy = 2 * H - last - y, xx = 2 * W - last - x;
@@ -2393,7 +2427,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_backward_mirror(TileArgs a, con
             const float old = *dst;
             const float g0 = rows ? g_at(a, F, f, F.GR - 1, cx, im, j, ch) : 0.f;
             const float g1 = rows && cols ? g_at(a, F, f, F.GR - 1, F.GC - 1, im, jm, ch) : 0.f;
-            const float g2 = cols ? g_at(a, F, f, tr, F.GC - 1, i, jm, ch) : 0.f;
+            const float g2 = cols ? g_at(a, F, f, cy, F.GC - 1, i, jm, ch) : 0.f;
             acc = (g0 + g1) + g2;
             if (acc != 0.f)
                 *dst = old + acc;
@@ -2410,7 +2444,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_backward_mirror(TileArgs a, con
             }
         for (int xx = W; xx < F.GC * b; ++xx)
             if (fold(xx, W, pad) == x)
-                acc += g_at(a, F, f, tr, F.GC - 1, i, by_s(xx - (F.GC - 1) * b), ch);
+                acc += g_at(a, F, f, cy, F.GC - 1, i, by_s(xx - (F.GC - 1) * b), ch);
         if (acc != 0.f)
             *dst += acc;
     }
@@ -2434,8 +2468,8 @@ __global__ __launch_bounds__(256) void k_edge_mask(TileArgs a)
     extern __shared__ __align__(16) uint8_t lds[];
     const int tid = threadIdx.x;
     const int64_t unit = a.sched_offset + blockIdx.x;
-    const int f = (int)uniform_u32((uint32_t)a.edge_map[2 * unit]);
-    const int local = (int)uniform_u32((uint32_t)a.edge_map[2 * unit + 1]);
+    const UnitCoord u = unit_of(a, unit);
+    const int f = u.f, local = u.local;
     const FrameRec& F = a.frames[f];
     const int H = F.H, W = F.W;
     const int chunks = (W + kLabCols - 1) / kLabCols, width = label_chunk(W);
@@ -2678,8 +2712,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     using Sh = MetShape<C>;
     const int tid = threadIdx.x;
     const int64_t unit = a.sched_offset + blockIdx.x;
-    const int f = (int)uniform_u32((uint32_t)a.met_map[2 * unit]);
-    const int local = (int)uniform_u32((uint32_t)a.met_map[2 * unit + 1]);
+    const UnitCoord u = unit_of(a, unit);
+    const int f = u.f, local = u.local;
     const FrameRec& F = a.frames[f];
     const int H = F.H, W = F.W;
     const int64_t pitch = F.pitch;
@@ -2830,9 +2864,9 @@ __global__ __launch_bounds__(256) void k_metrics_reduce(TileArgs a, double* out)
 {
     __shared__ double red[4];
     __shared__ unsigned long long red_se[4];
-    const int f = blockIdx.x, tid = threadIdx.x;
+    const int f = a.spans[blockIdx.x].frame, tid = threadIdx.x;
     const FrameRec& F = a.frames[f];
-    const int64_t base = a.met_base[2 * f], n = a.met_base[2 * f + 1];
+    const int64_t base = a.spans[blockIdx.x].first, n = a.spans[blockIdx.x + 1].first - base;
     double t = 0.0;
     unsigned long long e = 0;
     for (int64_t i = tid; i < n; i += 256) {
@@ -3022,10 +3056,9 @@ hipError_t launch_backward_reduce(const TileArgs& a, int threads, size_t lds, in
     return launch_tiles(k_backward_reduce, a, threads, lds, grid, s);
 }
 
-hipError_t launch_backward_mirror(const TileArgs& a, const int32_t* border_map, int64_t n_border, int threads,
-                                  hipStream_t s)
+hipError_t launch_backward_mirror(const TileArgs& a, int64_t n_units, int threads, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_backward_mirror, dim3((unsigned)n_border), dim3(threads), 0, s, a, border_map);
+    hipLaunchKernelGGL(k_backward_mirror, dim3((unsigned)n_units), dim3(threads), 0, s, a);
     return hipGetLastError();
 }
 

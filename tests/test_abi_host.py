@@ -295,3 +295,24 @@ def test_default_tile_width(H, W, b, K):
     assert st == 0
     assert info(h, L).tile_cells == K
     L.dp_pix_plan_destroy(h)
+
+
+@pytest.mark.parametrize("sizes,n,b,s,layout", [
+    ([(1300, 2050)], 64, 256, 256, "u8"), ([(2161, 3841)], 16, 256, 64, "f32"),
+    ([(576, 768), (1080, 1920), (2160, 3840), (4000, 6000)], 64, 32, 8, "u8"), ([(1365, 2047)], 24, 256, 256, "u8"),
+    ([(64, 64)], 500, 16, 16, "u8"), ([(218, 178)], 64, 8, 4, "f32"), ([(1080, 1920)], 1, 32, 8, "u8")])
+def test_plan_tables_grow_with_frames_and_tiles_alone(sizes, n, b, s, layout):
+    """What making a plan writes and uploads: a record and a few table entries
+    per frame, the scheduling entries of its tiles, and nothing that grows with
+    the padded area or with the units of calls that may never come."""
+    L = lib()
+    descs = (_lib.FrameDesc * n)()
+    for i in range(n):
+        h, w = sizes[i % len(sizes)]
+        descs[i] = dp.FrameParams(h, w, 3, dp.U8_HWC if layout == "u8" else dp.F32_CHW, b=b, sb=s, m=16).desc()
+    handle = ctypes.c_void_p()
+    _lib.check(L.dp_pix_plan_create(descs, n, ctypes.byref(handle)))
+    sz = _lib.Sizes()
+    _lib.check(L.dp_pix_plan_sizes(handle, ctypes.byref(sz)))
+    assert sz.workspace_bytes <= 16 * sz.n_tiles + 512 * n + 4096
+    L.dp_pix_plan_destroy(handle)
