@@ -354,7 +354,10 @@ int64_t metrics_units(const FrameRec& F, int32_t rows)
 // Units of the label masks: equal chunks of columns x segments of rows.  A
 // unit stages two rows more than it labels, in blocks of four: 4 m - 2 rows, m
 // at most 4 (64 x 1080p: m = 3 / 4 / 8 / 16: 92 / 95 / 101 / 114 us; 16 x 1080p: m
-// = 2 / 3 / 4 / 8: 29 / 25 / 25 / 25 us).
+// = 2 / 3 / 4 / 8: 29 / 25 / 25 / 25 us).  Wanted: a workgroup of up to four
+// waves for each SIMD, and two of the single waves that frames of up to 227
+// columns take (256 RGB frames of 64 x 64: m = 1 / 2 / 3 / 4: 9.7 / 7.3 / 7.4 / 8.6 us;
+// 512 of 32 x 32: 9.6 / 7.3 / 7.5 / 8.6; 64 of 218 x 178: 9.2 / 8.1 / 8.8 / 8.7).
 constexpr int64_t kEdgeUnits = 1024;
 
 // LDS of a walk's two blocks of staged rows.
@@ -559,7 +562,7 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
             p->chan[C] = (int32_t)by_chan.size();
         }
         p->met_rows = unit_rows(*p, metrics_units, 7, 6, 10, kMetUnits);
-        p->edge_rows = unit_rows(*p, edge_units, 4, 2, 4, kEdgeUnits);
+        p->edge_rows = unit_rows(*p, edge_units, 4, 2, 4, p->edge_threads == 64 ? 2 * kEdgeUnits : kEdgeUnits);
         p->met = span_units(*p, by_chan, [&](const FrameRec& F) { return metrics_units(F, p->met_rows); });
         p->edge = span_units(*p, by_chan, [&](const FrameRec& F) { return edge_units(F, p->edge_rows); });
         p->lab = span_units(*p, by_chan, [](const FrameRec& F) { return F.TX * ceil_div(F.GR, F.lnb); });
