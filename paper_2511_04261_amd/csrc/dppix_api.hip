@@ -66,6 +66,7 @@ struct dppix_plan {
     int32_t met_rows = 0, edge_rows = 0;    // rows of a unit
     std::vector<UnitSpan> met, lab, edge, border;
     int32_t chan[5] = {0, 0, 0, 0, 0};
+    bool met_narrow[4] = {false, false, false, false};   // narrow units of the metrics, by channel count
     int lab_threads = 64, edge_threads = 64;
     size_t lab_cells = 0;               // counters of the largest unit of the plan from labels
     bool prefix_scan = false;           // the plan's scan needs no hand-off between workgroups
@@ -338,7 +339,7 @@ int32_t unit_rows(const dppix_plan& p, Units units, int32_t step, int32_t over, 
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Units of the utility metrics: columns of metrics_unit_pixels(C) pixels x
+// Units of the utility metrics: columns of metrics_unit_pixels pixels x
 // segments of rows.  A unit reads six rows more than it has, and works in
 // blocks of seven, so a segment is 7 m - 6 rows; wanted: four rounds of the
 // 768 workgroups the GPU holds at once (16 x 1080p: m = 3 / 6 / 10: 196 / 170 /
@@ -346,9 +347,25 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // A lane's squared errors (at most 16 * 255^2 a block) fit 32 bits up to m = 4096.
 constexpr int64_t kMetUnits = 3000;
 
-int64_t metrics_units(const FrameRec& F, int32_t rows)
+int64_t metrics_units(const FrameRec& F, bool narrow, int32_t rows)
 {
-    return ceil_div(F.W, metrics_unit_pixels(F.C)) * ceil_div(F.H, rows);
+    return ceil_div(F.W, metrics_unit_pixels(F.C, narrow)) * ceil_div(F.H, rows);
+}
+
+// Whether the frames of C channels take narrow units: their windows fill less
+// than 77 % of the wide units' lanes (narrow / wide units: RGB, 76 %, 64 and 256
+// frames of 128 x 128: 15.6 / 15.2 and 38 / 45 us; 78 %, 32 of 256 x 256: 26 / 25;
+// 54 %, 256 of 218 x 178: 92 / 108; 96 %, 128 of 160 x 160: 36 / 30).
+bool metrics_narrow(const dppix_plan& p, int C)
+{
+    int64_t windows = 0, lanes = 0;
+    const int64_t unit = metrics_unit_pixels(C, false);
+    for (const FrameRec& F : p.frames)
+        if (F.C == C) {
+            windows += (int64_t)F.H * std::max(F.W - 6, 0);
+            lanes += (int64_t)F.H * ceil_div(F.W, unit) * unit;
+        }
+    return (double)windows < 0.77 * (double)lanes;
 }
 
 // Units of the label masks: equal chunks of columns x segments of rows.  A
@@ -561,9 +578,12 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
                     by_chan.push_back(f);
             p->chan[C] = (int32_t)by_chan.size();
         }
-        p->met_rows = unit_rows(*p, metrics_units, 7, 6, 10, kMetUnits);
+        for (int C = 1; C <= 4; ++C)
+            p->met_narrow[C - 1] = metrics_narrow(*p, C);
+        auto met_units = [&](const FrameRec& F, int32_t rows) { return metrics_units(F, p->met_narrow[F.C - 1], rows); };
+        p->met_rows = unit_rows(*p, met_units, 7, 6, 10, kMetUnits);
         p->edge_rows = unit_rows(*p, edge_units, 4, 2, 4, p->edge_threads == 64 ? 2 * kEdgeUnits : kEdgeUnits);
-        p->met = span_units(*p, by_chan, [&](const FrameRec& F) { return metrics_units(F, p->met_rows); });
+        p->met = span_units(*p, by_chan, [&](const FrameRec& F) { return met_units(F, p->met_rows); });
         p->edge = span_units(*p, by_chan, [&](const FrameRec& F) { return edge_units(F, p->edge_rows); });
         p->lab = span_units(*p, by_chan, [](const FrameRec& F) { return F.TX * ceil_div(F.GR, F.lnb); });
     }
@@ -1152,7 +1172,7 @@ dppix_status_t dp_pix_metrics(dppix_plan_t p, const void* const* images, const v
     a.met_rows = p->met_rows;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = for_channels(p, a, p->met, p->ws.met_spans, [&](const TileArgs& ca, int C, int64_t units) {
-        return launch_metrics(ca, C, units, s);
+        return launch_metrics(ca, C, p->met_narrow[C - 1], units, s);
     });
     if (e != hipSuccess)
         return dev_fail(e, "metrics launch");

@@ -343,8 +343,8 @@ hipError_t launch_backward_mirror(const TileArgs& a, int64_t n_units, int thread
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
 hipError_t launch_noise_advance(uint64_t* noise, int32_t n, uint64_t step, hipStream_t s);
 hipError_t launch_edge_mask(const TileArgs& a, int C, int64_t n_units, int threads, size_t lds, hipStream_t s);
-hipError_t launch_metrics(const TileArgs& a, int C, int64_t n_units, hipStream_t s);
-int metrics_unit_pixels(int C);   // pixels of a row one metrics unit covers
+hipError_t launch_metrics(const TileArgs& a, int C, bool narrow, int64_t n_units, hipStream_t s);
+int metrics_unit_pixels(int C, bool narrow);   // pixels of a row one metrics unit covers
 hipError_t launch_metrics_reduce(const TileArgs& a, double* out, hipStream_t s);
 hipError_t occupancy_forward(int layout, int C, int threads, size_t lds, int* blocks_per_cu);
 

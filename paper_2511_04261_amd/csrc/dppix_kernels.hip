@@ -2535,19 +2535,29 @@ __global__ __launch_bounds__(256) void k_edge_mask(TileArgs a)
 // ==========================================================================
 constexpr int kMetBlock = 7;                    // rows per block: the window's height
 
-// Pixels of a unit (their windows start in it, and their squared errors are
-// its own), 16-pixel groups of a staged row (the windows reach 6 pixels
-// further), and bytes of a staged plane row.
-template <int C>
+// A unit's lanes, windows of a lane, pixels (their windows start in it, and
+// their squared errors are its own), 16-pixel groups of a staged row (the
+// windows reach 6 pixels further), and bytes of a staged plane row.
+//
+// NARROW: one wave a unit and one window a lane, for batches whose frames leave
+// the lanes of wide units idle (metrics_narrow; an idle wave still holds its
+// registers, and there are twelve waves' worth on a CU).  256 RGB frames of 64
+// x 64: 23.6 us wide, 14.4 narrow, 13.0 with a kernel of a window a lane and
+// four workgroups a frame; 512 of 32 x 32: 24 / 11.1 / 10.6; 64 of 218 x 178:
+// 39.8 / 29.6 / 62; 256 gray ones of 64 x 64: 19 / 8.9 / 10.0.  Pairs of windows
+// in single waves: 15.4 and, of four channels, 20 us instead of 17.3.
+template <int C, bool NARROW>
 struct MetShape {
-    static constexpr int kCw = C == 3 ? 160 : 512 / C;
+    static constexpr int kThreads = NARROW ? 64 : 256;
+    static constexpr int kWin = NARROW ? 1 : 2;
+    static constexpr int kCw = kThreads * kWin / C / 16 * 16;
     static constexpr int kGroups = kCw / 16 + 1;
     static constexpr int kRow = 16 * kGroups;
 };
 
-template <int C>
+template <int C, bool NARROW>
 struct MetLds {
-    alignas(16) uint8_t px[2][2][C][kMetBlock][MetShape<C>::kRow];   // [buffer][frame]
+    alignas(16) uint8_t px[2][2][C][kMetBlock][MetShape<C, NARROW>::kRow];   // [buffer][frame]
     double red[4];
     unsigned long long red_se[4];
 };
@@ -2572,6 +2582,21 @@ __device__ __forceinline__ void add_row_moments(const uint32_t* xr, const uint32
     t[1][2] = __builtin_amdgcn_udot4(yb, yb, __builtin_amdgcn_udot4(ya, ya1, t[1][2], false), false);
     t[0][3] = __builtin_amdgcn_udot4(xb0, yb, __builtin_amdgcn_udot4(xa, ya, t[0][3], false), false);
     t[1][3] = __builtin_amdgcn_udot4(xb, yb, __builtin_amdgcn_udot4(xa1, ya, t[1][3], false), false);
+}
+
+// The same for one window, the 7 taps from byte `sh`.
+__device__ __forceinline__ void add_row_moments(const uint32_t* xr, const uint32_t* yr, uint32_t sh,
+                                                uint32_t (&t)[1][4])
+{
+    const uint32_t xa = __builtin_amdgcn_alignbyte(xr[1], xr[0], sh), ya = __builtin_amdgcn_alignbyte(yr[1], yr[0], sh);
+    const uint32_t xb = __builtin_amdgcn_alignbyte(xr[2], xr[1], sh) & 0x00FFFFFFu;
+    const uint32_t yb = __builtin_amdgcn_alignbyte(yr[2], yr[1], sh) & 0x00FFFFFFu;
+    constexpr uint32_t one = 0x01010101u;
+    t[0][0] = __builtin_amdgcn_udot4(xb, one, __builtin_amdgcn_udot4(xa, one, t[0][0], false), false);
+    t[0][1] = __builtin_amdgcn_udot4(yb, one, __builtin_amdgcn_udot4(ya, one, t[0][1], false), false);
+    t[0][2] = __builtin_amdgcn_udot4(xb, xb, __builtin_amdgcn_udot4(xa, xa, t[0][2], false), false);
+    t[0][2] = __builtin_amdgcn_udot4(yb, yb, __builtin_amdgcn_udot4(ya, ya, t[0][2], false), false);
+    t[0][3] = __builtin_amdgcn_udot4(xb, yb, __builtin_amdgcn_udot4(xa, ya, t[0][3], false), false);
 }
 
 // A quarter of SSIM's numerator and its denominator (A B / 4 and D E above)
@@ -2705,11 +2730,13 @@ struct MetGroup {
 
 // Three waves per SIMD: the ring of a pair of windows is 56 registers, and with
 // the 128 of four waves the kernel spills (444 us instead of 164, 16 x 1080p).
-template <int C>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_metrics(TileArgs a)
+template <int C, bool NARROW>
+__global__ __launch_bounds__((NARROW ? 64 : 256)) __attribute__((amdgpu_waves_per_eu(3))) void
+k_metrics(TileArgs a)
 {
-    __shared__ MetLds<C> L;
-    using Sh = MetShape<C>;
+    __shared__ MetLds<C, NARROW> L;
+    using Sh = MetShape<C, NARROW>;
+    constexpr int NT = Sh::kThreads, kWin = Sh::kWin;
     const int tid = threadIdx.x;
     const int64_t unit = a.sched_offset + blockIdx.x;
     const UnitCoord u = unit_of(a, unit);
@@ -2731,7 +2758,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     // Staging of a block: an item per (frame, row, 16-pixel group).  Where
     // they do not fill the workgroup, another wave begins each block, so that
     // every SIMD gets its share.
-    constexpr int kItems = 2 * kMetBlock * Sh::kGroups, kPer = (kItems + 255) / 256;
+    constexpr int kItems = 2 * kMetBlock * Sh::kGroups, kPer = (kItems + NT - 1) / NT;
     const int narrow = W >= 16 ? -1 : W;
     MetGroup<C> grp[kPer];
     struct Item {
@@ -2739,7 +2766,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         bool in;
     };
     auto item = [&](int blk, int i) {
-        const int it = ((tid + 64 * blk) & 255) + 256 * i;
+        const int it = ((tid + 64 * blk) & (NT - 1)) + NT * i;
         Item m;
         m.y = it / (kMetBlock * Sh::kGroups);
         const int q = it - m.y * (kMetBlock * Sh::kGroups);
@@ -2776,15 +2803,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             se += sq_diff16(*reinterpret_cast<const v4u*>(&L.px[blk & 1][0][ech][erow][16 * eg]),
                             *reinterpret_cast<const v4u*>(&L.px[blk & 1][1][ech][erow][16 * eg]));
     };
-    // this lane's (channel, pair of windows)
-    constexpr int kPairs = Sh::kCw / 2;
-    const int ch = tid / kPairs, pair = tid - ch * kPairs;
-    const bool works = ch < C && p0 + 2 * pair < W - 6 && nrow >= kMetBlock;
-    const double second = p0 + 2 * pair + 1 < W - 6 ? 1.0 : 0.0;
-    const uint32_t sh = 2u * (uint32_t)(pair & 1);
-    const int word = pair >> 1;
-    uint32_t t[2][4] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
-    uint32_t ring[kMetBlock][2][4];
+    // this lane's (channel, first window)
+    constexpr int kLanes = Sh::kCw / kWin;
+    const int ch = tid / kLanes, w0 = kWin * (tid - ch * kLanes);
+    const bool works = ch < C && p0 + w0 < W - 6 && nrow >= kMetBlock;
+    const double second = p0 + w0 + 1 < W - 6 ? 1.0 : 0.0;
+    const uint32_t sh = (uint32_t)(w0 & 3);
+    const int word = w0 >> 2;
+    uint32_t t[kWin][4] = {};
+    uint32_t ring[kMetBlock][kWin][4];
     // One block of rows.  `first`: windows end only with its last row, and
     // start at the unit's first; `full`: all seven rows are there (no branch
     // between them, so their loads and sums interleave).
@@ -2797,23 +2824,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
                 break;
             add_row_moments(xr + j * (Sh::kRow / 4), yr + j * (Sh::kRow / 4), sh, t);
             if (!first || j == kMetBlock - 1) {
-                uint32_t w[2][4];
+                uint32_t w[kWin][4];
 #pragma unroll
-                for (int m = 0; m < 8; ++m)
+                for (int m = 0; m < 4 * kWin; ++m)
                     w[m >> 2][m & 3] = t[m >> 2][m & 3] - (first ? 0u : ring[j][m >> 2][m & 3]);
-                double n0, d0, n1, d1;
-                ssim_ratio(w[0][0], w[0][1], w[0][2], w[0][3], n0, d0);
-                ssim_ratio(w[1][0], w[1][1], w[1][2], w[1][3], n1, d1);
                 // n0 / d0 + n1 / d1 over one reciprocal, refined by one
                 // Newton step (it squares the relative error); the
                 // denominators are normal numbers below 2^62
-                const double den = d0 * d1;
+                double n0, d0, n1, d1;
+                ssim_ratio(w[0][0], w[0][1], w[0][2], w[0][3], n0, d0);
+                double num = n0, den = d0;
+                if constexpr (kWin == 2) {
+                    ssim_ratio(w[1][0], w[1][1], w[1][2], w[1][3], n1, d1);
+                    num = fma(n0, d1, second * n1 * d0);
+                    den = d0 * d1;
+                }
                 double r = __builtin_amdgcn_rcp(den);
                 r = fma(r, fma(-den, r, 1.0), r);
-                acc = fma(fma(n0, d1, second * n1 * d0), r, acc);
+                acc = fma(num, r, acc);
             }
 #pragma unroll
-            for (int m = 0; m < 8; ++m)
+            for (int m = 0; m < 4 * kWin; ++m)
                 ring[j][m >> 2][m & 3] = t[m >> 2][m & 3];
         }
     };
@@ -2851,9 +2882,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
     lds_barrier();
     if (tid == 0) {
-        a.met_partial[2 * unit] = (L.red[0] + L.red[1]) + (L.red[2] + L.red[3]);
+        a.met_partial[2 * unit] = NARROW ? L.red[0] : (L.red[0] + L.red[1]) + (L.red[2] + L.red[3]);
         reinterpret_cast<unsigned long long*>(a.met_partial)[2 * unit + 1] =
-            (L.red_se[0] + L.red_se[1]) + (L.red_se[2] + L.red_se[3]);
+            NARROW ? L.red_se[0] : (L.red_se[0] + L.red_se[1]) + (L.red_se[2] + L.red_se[3]);
     }
 }
 
@@ -3076,27 +3107,36 @@ hipError_t launch_edge_mask(const TileArgs& a, int C, int64_t n_units, int threa
     return hipGetLastError();
 }
 
-hipError_t launch_metrics(const TileArgs& a, int C, int64_t n_units, hipStream_t s)
+template <int C>
+hipError_t launch_metrics_c(const TileArgs& a, bool narrow, int64_t n_units, hipStream_t s)
 {
-    if (n_units == 0)
-        return hipSuccess;
-    const dim3 grid((unsigned)n_units), block(256);
-    switch (C) {
-    case 1: hipLaunchKernelGGL(k_metrics<1>, grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_metrics<2>, grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL(k_metrics<3>, grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL(k_metrics<4>, grid, block, 0, s, a); break;
-    }
+    const dim3 grid((unsigned)n_units);
+    if (narrow)
+        hipLaunchKernelGGL((k_metrics<C, true>), grid, dim3(MetShape<C, true>::kThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_metrics<C, false>), grid, dim3(MetShape<C, false>::kThreads), 0, s, a);
     return hipGetLastError();
 }
 
-int metrics_unit_pixels(int C)
+hipError_t launch_metrics(const TileArgs& a, int C, bool narrow, int64_t n_units, hipStream_t s)
+{
+    if (n_units == 0)
+        return hipSuccess;
+    switch (C) {
+    case 1: return launch_metrics_c<1>(a, narrow, n_units, s);
+    case 2: return launch_metrics_c<2>(a, narrow, n_units, s);
+    case 3: return launch_metrics_c<3>(a, narrow, n_units, s);
+    default: return launch_metrics_c<4>(a, narrow, n_units, s);
+    }
+}
+
+int metrics_unit_pixels(int C, bool narrow)
 {
     switch (C) {
-    case 1: return MetShape<1>::kCw;
-    case 2: return MetShape<2>::kCw;
-    case 3: return MetShape<3>::kCw;
-    default: return MetShape<4>::kCw;
+    case 1: return narrow ? MetShape<1, true>::kCw : MetShape<1, false>::kCw;
+    case 2: return narrow ? MetShape<2, true>::kCw : MetShape<2, false>::kCw;
+    case 3: return narrow ? MetShape<3, true>::kCw : MetShape<3, false>::kCw;
+    default: return narrow ? MetShape<4, true>::kCw : MetShape<4, false>::kCw;
     }
 }
 

@@ -92,3 +92,29 @@ def test_mirror_units(dev, n, pad):
         at += xs[i].size
         assert np.abs(got - hwc_to_chw(gw)).max() <= 1e-5 * max(1.0, np.abs(gw).max()), i
     plan.close()
+
+
+@pytest.mark.parametrize("c", [1, 2, 3, 4])
+@pytest.mark.parametrize("narrow", [True, False])
+def test_metrics_of_narrow_and_wide_units(dev, c, narrow):
+    """Widths around the edges of both kinds of metrics units (a wave's and a
+    workgroup's lanes), in a batch whose frames take the one kind, or, with a
+    frame that outweighs them, the other: MSE exact, SSIM within 1e-9."""
+    print("case: metrics units", c, narrow, file=sys.stderr, flush=True)
+    r = np.random.Generator(np.random.PCG64(40 + c))
+    small, wide = 64 // c // 16 * 16, 512 // c // 16 * 16
+    widths = [7, 15, 16, 17, 23] + [w + d for w in (small, 2 * small, wide) for d in (-1, 0, 1, 6, 7)]
+    shapes = [((7, 8, 14, 21, 30, 33)[i % 6], max(w, 7)) for i, w in enumerate(widths)]
+    if not narrow:
+        shapes.append((400, 4 * wide))
+    xs = [r.integers(0, 256, (h, w, c)) for h, w in shapes]
+    ys = [np.clip(x // 3 + r.integers(0, 90, x.shape), 0, 255).astype(np.uint8) for x in xs]
+    xs = [x.astype(np.uint8) for x in xs]
+    _, ti = _views(xs, dev)
+    _, to = _views(ys, dev)
+    plan = dp.Plan([dp.FrameParams(h, w, c, dp.U8_HWC, b=8) for h, w in shapes], device=dev)
+    got = plan.metrics(ti, to).cpu().numpy()
+    for i in range(len(shapes)):
+        mse, ssim = oracle.metrics(xs[i], ys[i])
+        assert abs(got[i, 0] - mse) <= 1e-12 * mse and abs(got[i, 1] - ssim) <= 1e-9, (shapes[i], got[i], ssim)
+    plan.close()
