@@ -317,6 +317,16 @@ std::vector<UnitSpan> span_units(const dppix_plan& p, const std::vector<int32_t>
 
 int64_t span_total(const std::vector<UnitSpan>& spans) { return spans.empty() ? 0 : spans.back().first; }
 
+// Units of each of the n frames from span lo on, if they have as many, else 0.
+int32_t equal_units(const std::vector<UnitSpan>& spans, int32_t lo, int32_t n)
+{
+    const int64_t u = spans[lo + 1].first - spans[lo].first;
+    for (int32_t k = lo; k < lo + n; ++k)
+        if (spans[k + 1].first - spans[k].first != u)
+            return 0;
+    return (int32_t)u;
+}
+
 // Rows of a unit, step * m - over for the largest m up to `most` that gives
 // the batch `wanted` units; units(F, rows) counts a frame's.  Huge batches:
 // no more units than twice the tiles (a launch has at most 2^31).
@@ -841,6 +851,7 @@ hipError_t for_channels(dppix_plan_t p, const TileArgs& base, const std::vector<
         TileArgs a = base;
         a.spans = reinterpret_cast<const UnitSpan*>(p->bound + at) + lo;
         a.n_spans = n;
+        a.span_units = equal_units(spans, lo, n);
         a.sched_offset = spans[lo].first;
         const hipError_t e = launch(a, C, spans[lo + n].first - spans[lo].first);
         if (e != hipSuccess)
@@ -1091,6 +1102,7 @@ dppix_status_t run_backward(dppix_plan_t p, const dppix_store_t* store, const fl
     if (span_total(p->border) > 0) {
         a.spans = reinterpret_cast<const UnitSpan*>(p->bound + p->ws.border_spans);
         a.n_spans = (int32_t)p->border.size() - 1;
+        a.span_units = equal_units(p->border, 0, a.n_spans);
         e = launch_backward_mirror(a, span_total(p->border), plain_threads(p), s);
         if (e != hipSuccess)
             return dev_fail(e, "backward launch");

@@ -81,8 +81,7 @@ struct FrameRec {
 // alone.  (Maps with an entry per unit were written and uploaded with every
 // plan.  dp_pix_plan_create on the host, with them and now: 256 frames of 576 x
 // 768 to 4000 x 6000: 6.6 -> 0.41 ms, workspace 6.1 -> 1.5 MB; 64 of 1300 x
-// 2050, b 256: 5.7 ms -> 16 us; 16 fp32 of 2161 x 3841, b 256: 451 -> 5 us.  The
-// search costs a kernel about 0.3 us.)
+// 2050, b 256: 5.7 ms -> 16 us; 16 fp32 of 2161 x 3841, b 256: 451 -> 5 us.)
 struct UnitSpan {
     int64_t first;
     int32_t frame, pad_;
@@ -221,6 +220,7 @@ struct TileArgs {
     // of this launch's frames (one more entry than frames)
     const UnitSpan* spans;
     int32_t n_spans;
+    int32_t span_units;       // units of each frame if all have as many, else 0
     // utility metrics: per unit (SSIM partial sum, squared-error sum)
     double* met_partial;
     int32_t met_rows;         // rows of a metrics unit

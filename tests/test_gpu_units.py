@@ -118,3 +118,28 @@ def test_metrics_of_narrow_and_wide_units(dev, c, narrow):
         mse, ssim = oracle.metrics(xs[i], ys[i])
         assert abs(got[i, 0] - mse) <= 1e-12 * mse and abs(got[i, 1] - ssim) <= 1e-9, (shapes[i], got[i], ssim)
     plan.close()
+
+
+@pytest.mark.parametrize("n", [2, 66])
+def test_frames_of_as_many_units(dev, n):
+    """Batches in which every frame has as many units (the unit's frame then
+    comes from a division), also of one channel count only."""
+    print("case: equal frames", n, file=sys.stderr, flush=True)
+    r = np.random.Generator(np.random.PCG64(n))
+    cs = [3] * n if n == 2 else [1 + i % 4 for i in range(n)]
+    xs = [(r.integers(0, 256, (50, 190, c)) // (1 + 9 * (r.random((50, 190, 1)) < 0.7))).astype(np.uint8) for c in cs]
+    ys = [np.clip(x // 3 + r.integers(0, 90, x.shape), 0, 255).astype(np.uint8) for x in xs]
+    _, ti = _views(xs, dev)
+    _, to = _views(ys, dev)
+    plan = dp.Plan([dp.FrameParams(50, 190, c, dp.U8_HWC, b=8, sb=4, m=8, tau=2) for c in cs], device=dev)
+    masks = plan.edge_masks(ti, 60)
+    one, two = plan.new_store(), plan.new_store()
+    plan.plan(masks, store=two)
+    plan.plan_labels(ti, 60, store=one)
+    got = plan.metrics(ti, to).cpu().numpy()
+    assert torch.equal(one.flags, two.flags) and torch.equal(one.counts, two.counts)
+    for i in range(n):
+        assert np.array_equal(masks[i].cpu().numpy(), oracle.edge_mask(xs[i], 60, 0)), i
+        want = oracle.metrics(xs[i], ys[i])
+        assert abs(got[i, 0] - want[0]) <= 1e-12 * want[0] and abs(got[i, 1] - want[1]) <= 1e-9, i
+    plan.close()
