@@ -268,14 +268,17 @@ int rec_threads(const FrameRec& F, int64_t tiles)
     return tiles >= 2048 && stores >= 3072 ? 512 : kDefaultThreads;
 }
 
-// Plan units of the batch: fewer than kPlanUnits leave compute units idle, so
-// units of several bands are halved, down to kPlanItems strip items (a wave
-// and a bit).  64 frames of 218 x 178, b 8: 64 units of 336 items 13.5 us, 256 of
-// 84: 10.3, 1792 of 12: 14; 16 x 1080p, b 4: 544 units of 960 items 17.2 us, 1088
-// of 480: 15.4; 32 frames of 512 x 512, b 16: 256 units of 128 items 7.8 us, 1024 of
-// 32: 8.7.
-constexpr int64_t kPlanUnits = 1024;
-constexpr int64_t kPlanItems = 72;
+// Plan units of the batch.  Fewer than two a compute unit (kPlanUnits) leave
+// some idle, so units of several bands are halved, down to kPlanItems strip
+// items (a wave and a bit): 64 frames of 218 x 178, b 8: 64 units of 336 items
+// 13.5 us, 256 of 84: 10.3, 1792 of 12: 14; 24 photos of odd sizes, b 16: 393 of up
+// to 256 15.2, 729 of up to 160 14.1; 16 x 512 x 512 fp32, b 4: 10.8 whole, 7.9
+// halved.  Up to kPlanUnitsFull more halving only pays while a unit still
+// fills its 256 lanes: 16 x 1080p, b 4: 544 units of 960 items 17.2 us, 1088 of
+// 480: 15.4; but 32 x 720 x 1280, b 12: 640 of 243 12.6, 1920 of 81 16.8; 100 x 480
+// x 640, b 12: 700 of 246 12.7, 1400 of 123 15.4.
+constexpr int64_t kPlanUnits = 512, kPlanUnitsFull = 1024;
+constexpr int64_t kPlanItems = 72, kPlanItemsFull = 256;
 
 void spread_units(dppix_plan& p)
 {
@@ -288,10 +291,11 @@ void spread_units(dppix_plan& p)
         p.n_units = 0;
         for (const FrameRec& F : p.frames)
             p.n_units += F.cunits;
-        if (p.n_units >= kPlanUnits)
+        if (p.n_units >= kPlanUnitsFull)
             break;
+        const int64_t least = p.n_units < kPlanUnits ? kPlanItems : kPlanItemsFull;
         for (FrameRec& F : p.frames)
-            if (F.cnb > 1 && items(F, (F.cnb + 1) / 2) >= kPlanItems) {
+            if (F.cnb > 1 && items(F, (F.cnb + 1) / 2) >= least) {
                 F.cnb = (F.cnb + 1) / 2;
                 F.cunits = ((F.GR + F.cnb - 1) / F.cnb) * ((F.TX + F.ctx - 1) / F.ctx);
                 more = true;
