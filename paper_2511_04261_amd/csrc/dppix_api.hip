@@ -346,7 +346,7 @@ int32_t unit_rows(const dppix_plan& p, Units units, int32_t step, int32_t over, 
     int32_t m = most;
     while (m > 2 && total(m) < wanted)
         --m;
-    while (m < 2048 && total(m) > 2 * p.n_tiles + (1 << 20))
+    while (2 * m <= kMetBlocksMax && total(m) > 2 * p.n_tiles + (1 << 20))
         m *= 2;
     return step * m - over;
 }
@@ -358,7 +358,7 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // blocks of seven, so a segment is 7 m - 6 rows; wanted: four rounds of the
 // 768 workgroups the GPU holds at once (16 x 1080p: m = 3 / 6 / 10: 196 / 170 /
 // 164 us; one 6000 x 4000 frame: m = 3 / 6 / 8 / 10: 155 / 131 / 125 / 129 us).
-// A lane's squared errors (at most 16 * 255^2 a block) fit 32 bits up to m = 4096.
+// At most kMetBlocksMax blocks (a lane's squared errors).
 constexpr int64_t kMetUnits = 3000;
 
 int64_t metrics_units(const FrameRec& F, bool narrow, int32_t rows)

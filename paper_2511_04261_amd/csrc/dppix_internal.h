@@ -343,6 +343,10 @@ hipError_t launch_backward_mirror(const TileArgs& a, int64_t n_units, int thread
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
 hipError_t launch_noise_advance(uint64_t* noise, int32_t n, uint64_t step, hipStream_t s);
 hipError_t launch_edge_mask(const TileArgs& a, int C, int64_t n_units, int threads, size_t lds, hipStream_t s);
+// Blocks of seven rows of a metrics unit at most: a lane adds the squared
+// errors of one 16-pixel group of each in 32 bits.
+constexpr int64_t kMetBlocksMax = 4096;
+static_assert(kMetBlocksMax * 16 * 255 * 255 <= (int64_t)UINT32_MAX, "a lane's squared errors fit 32 bits");
 hipError_t launch_metrics(const TileArgs& a, int C, bool narrow, int64_t n_units, hipStream_t s);
 int metrics_unit_pixels(int C, bool narrow);   // pixels of a row one metrics unit covers
 hipError_t launch_metrics_reduce(const TileArgs& a, double* out, hipStream_t s);
