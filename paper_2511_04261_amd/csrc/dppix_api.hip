@@ -676,7 +676,7 @@ dppix_status_t dp_pix_plan_sizes(dppix_plan_t p, dppix_sizes_t* out)
     out->clip_bytes_bg = p->bg_cap;
     out->clip_bytes_fg = p->fg_cap;
     out->grad_scratch_bytes = grad_scratch_need(p);
-    out->metrics_scratch_bytes = align256(16 * (size_t)std::max(p->n_tiles, span_total(p->met)));
+    out->metrics_scratch_bytes = align256(16 * (size_t)std::max<int64_t>(1, span_total(p->met)));
     out->n_tiles = p->n_tiles;
     out->total_pixels = p->total_pixels;
     out->forward_launches = (int64_t)p->groups.size();

@@ -2511,8 +2511,8 @@ __global__ __launch_bounds__(256) void k_edge_mask(TileArgs a)
 // sample covariances, K1 = 0.01, K2 = 0.03, range 255, channels averaged).
 // With uint8 inputs every window sum of x, y, x^2, y^2 and xy is an integer,
 // so the sums are exact and so are the numerators below; only the final
-// ratio is fp64.  Each tile writes its partial sums; k_metrics_reduce adds
-// them per frame in tile order (deterministic).
+// ratio is fp64.  Each unit writes its partial sums; k_metrics_reduce adds a
+// frame's in a fixed order (strided over the lanes, then a tree).
 //
 // SSIM of a window from its integer sums s0 = sum x, s1 = sum y, s2 = sum x^2,
 // s3 = sum y^2, s4 = sum xy over np = 49 pixels: with ux = s0/49, the sample

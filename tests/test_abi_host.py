@@ -316,3 +316,18 @@ def test_plan_tables_grow_with_frames_and_tiles_alone(sizes, n, b, s, layout):
     _lib.check(L.dp_pix_plan_sizes(handle, ctypes.byref(sz)))
     assert sz.workspace_bytes <= 16 * sz.n_tiles + 512 * n + 4096
     L.dp_pix_plan_destroy(handle)
+
+
+def test_metrics_scratch_is_what_their_units_write():
+    """16 bytes a unit of the metrics, whatever the plan's tiles: a fine grid's
+    many tiles ask for no more than a coarse one's."""
+    L = lib()
+    got = []
+    for b in (2, 32):
+        d = (_lib.FrameDesc * 4)(*[dp.FrameParams(1080, 1920, 3, b=b, sb=b, m=16).desc() for _ in range(4)])
+        h, sz = ctypes.c_void_p(), _lib.Sizes()
+        _lib.check(L.dp_pix_plan_create(d, 4, ctypes.byref(h)))
+        _lib.check(L.dp_pix_plan_sizes(h, ctypes.byref(sz)))
+        got.append(sz.metrics_scratch_bytes)
+        L.dp_pix_plan_destroy(h)
+    assert got[0] == got[1] >= 256
