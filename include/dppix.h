@@ -326,15 +326,22 @@ dppix_status_t dp_pix_backward_static(dppix_plan_t plan, const dppix_store_t* st
  * Execution options, graphs, diagnostics.
  * ------------------------------------------------------------------------- */
 
-/* Launch shape of the tile kernels: threads per workgroup (64..512, multiple
- * of 64; 0 = the default: 256, except forward and reconstruction tiles with
- * few row items per tile, which run 128 per workgroup in a launch of their
- * own) and the work distribution: persistent = 0 launches one
+/* Launch shape of the tile kernels (forward, reconstruction, the plan from
+ * masks, adjoint): threads per workgroup, 64..512, a multiple of 64.  0 = the
+ * default: 256, except that frames are grouped by what their tiles hold, a
+ * launch each.  Forward tiles with few row items take 128 (u8 and fp32), u8
+ * forward tiles with many items take 512 in batches of fewer than 256 tiles.
+ * Reconstruction has a size of its own per group: that of the forward, 256 for
+ * u8 tiles with many 16-byte stores (512 in batches of 2048 tiles or more)
+ * and for fp32 tiles.  The label masks, the plan from labels and the metrics
+ * choose their own sizes, 64 to 256, and ignore `threads`.
+ * The work distribution: persistent = 0 launches one
  * workgroup per tile (the hardware dispatcher feeds the CUs; the default);
  * persistent = 1 launches as many workgroups as the CUs hold at once and
  * persistent = k in 2..64 launches k per CU — those workgroups stay resident
- * and pull tiles from an atomic ticket in the workspace.  Results never
- * depend on these. */
+ * and pull tiles from an atomic ticket in the store's state (forward,
+ * reconstruction and the adjoint's reduction; the other kernels have no such
+ * form).  Results never depend on these. */
 dppix_status_t dp_pix_plan_set_launch(dppix_plan_t plan, int32_t threads, int32_t persistent);
 
 /* Capture plan + forward (+ fused reconstruction) on the stream into a HIP
