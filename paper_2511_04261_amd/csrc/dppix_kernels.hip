@@ -34,7 +34,9 @@
 #include <utility>
 
 // Register budget of the u8 forward kernel, as resident waves per SIMD: 4
-// leaves 128 VGPRs (no spills with all of a subgrid row's loads in flight).
+// leaves 128 VGPRs for all of a subgrid row's loads in flight.  That is just
+// short: the compiler keeps up to 20 bytes a lane in scratch (RGB) and about 190
+// scalar registers in lanes of vector registers.
 #ifndef DPPIX_FWD_WAVES_PER_EU
 #define DPPIX_FWD_WAVES_PER_EU 4
 #endif
@@ -2087,8 +2089,8 @@ __device__ __forceinline__ void run_tiles(const TileArgs& a, uint8_t* lds, Body 
     }
 }
 
-// Five waves per SIMD: enough resident tiles per CU to keep HBM busy while
-// other waves are in their LDS phases (the register budget still fits).
+// DPPIX_FWD_WAVES_PER_EU waves per SIMD: enough resident tiles per CU to keep HBM
+// busy while other waves are in their LDS phases.
 template <int C, bool DBG = false>
 __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(DPPIX_FWD_WAVES_PER_EU))) void
 k_forward_u8(TileArgs a)
