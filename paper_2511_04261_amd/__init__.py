@@ -157,15 +157,19 @@ def check_no_alias(images, outs):
 
 def _expected(d):
     """What a frame's tensor looks like by its descriptor: dtype, shape,
-    stride, and the bytes it spans."""
+    stride, the bytes it spans, and shape and stride of its other form (a gray
+    frame without its channel axis), or None."""
     torch = _torch()
+    flat = None
     if d.layout == U8_HWC:
         dtype, size = torch.uint8, 1
         shape, stride = (d.height, d.width, d.channels), (d.pitch, d.channels, 1)
+        if d.channels == 1:
+            flat = (shape[:2], stride[:2])
     else:
         dtype, size = torch.float32, 4
         shape, stride = (d.channels, d.height, d.width), (d.pitch * d.height, d.pitch, 1)
-    return dtype, shape, stride, (1 + sum((n - 1) * st for n, st in zip(shape, stride))) * size
+    return dtype, shape, stride, (1 + sum((n - 1) * st for n, st in zip(shape, stride))) * size, flat
 
 
 class Store:
@@ -410,9 +414,10 @@ class Plan:
         index = self.device.index
         out = []
         for i, t in enumerate(tensors):
-            dtype, shape, stride, _ = self._expect[i]
-            if not (t.shape == shape and t.stride() == stride and t.dtype == dtype and t.is_cuda and
-                    (index is None or t.get_device() == index)):
+            dtype, shape, stride, _, flat = self._expect[i]
+            if not ((t.shape == shape and t.stride() == stride or
+                     flat is not None and t.shape == flat[0] and t.stride() == flat[1]) and
+                    t.dtype == dtype and t.is_cuda and (index is None or t.get_device() == index)):
                 self._check_images((t,), what, self.frames[i:i + 1])
             out.append(t.data_ptr())
         return tuple(out)

@@ -137,3 +137,20 @@ def test_batch_table_holds_every_image_when_it_was_evicted(n):
     for _ in range(2):
         assert plan._batch_table(x).tolist() == [x[i].data_ptr() for i in range(n)]
         plan._tables.clear()
+
+
+@pytest.mark.parametrize("pad", [0, 3])
+def test_gray_frames_pass_the_short_check_in_both_forms(pad):
+    """(H, W) and (H, W, 1) tensors of a gray frame are accepted without the
+    full check; the same with a gap between pixels are not."""
+    fp = dp.FrameParams(6, 5, 1, dp.U8_HWC, b=4, pitch=5 + pad)
+    plan = _plan(fp, 0)
+    full = []
+    plan._check_images = lambda tensors, what, frames=None: full.append(tensors)
+    flat = torch.zeros(200, dtype=torch.uint8)
+    for shape, stride, short in (((6, 5, 1), (5 + pad, 1, 1), True), ((6, 5), (5 + pad, 1), True), ((6, 5), (5 + pad, 2), False),
+                                 ((5, 6), (5 + pad, 1), False), ((6, 5), (6 + pad, 1), False)):
+        x = OnGpu(flat.as_strided(shape, stride))
+        assert plan._addresses([x], "images") == (flat.data_ptr(),)
+        assert (not full) == short, (shape, stride)
+        full.clear()
