@@ -523,7 +523,7 @@ __device__ void scan_frames(const TileArgs& a, uint64_t* wave_tot)
 // whole bands of 2 or 4 rows take eight rows an item and count cell by cell.
 // 16 x 1080p, b 4: plan 24.5 -> 15.5 us (with the units halved), b 8: 14.5 -> 11.9;
 // 8 x 1080p, b 2: 30.1 -> 19.4; 64 x 1080p, b 32: 25.8 -> 25.2 (HBM-bound).  With
-// the scan's eight tiles a lane the first three are 13.6, 11.4 and 16.2.
+// the scan's eight tiles a lane the first three are 13.6, 11.7 and 16.2.
 // ==========================================================================
 constexpr int kPlanRows = 16;   // padded mask rows one lane sums per item
 constexpr int kPlanBatch = 8;   // row loads issued back to back
@@ -2552,10 +2552,11 @@ constexpr int kMetBlock = 7;                    // rows per block: the window's 
 // NARROW: one wave a unit and one window a lane, for batches whose frames leave
 // the lanes of wide units idle (metrics_narrow; an idle wave still holds its
 // registers, and there are twelve waves' worth on a CU).  256 RGB frames of 64
-// x 64: 23.6 us wide, 14.4 narrow, 13.0 with a kernel of a window a lane and
-// four workgroups a frame; 512 of 32 x 32: 24 / 11.1 / 10.6; 64 of 218 x 178:
-// 39.8 / 29.6 / 62; 256 gray ones of 64 x 64: 19 / 8.9 / 10.0.  Pairs of windows
-// in single waves: 15.4 and, of four channels, 20 us instead of 17.3.
+// x 64: 23.1 us wide, 14.2 narrow, 13.0 with a kernel of a window a lane and
+// four workgroups a frame; 512 of 32 x 32: 24 / 10.7 / 10.6; 64 of 218 x 178:
+// 39.6 / 29.9 / 62; 256 gray ones of 64 x 64: 18.7 / 8.7 / 10.0.  Pairs of windows
+// in single waves were slower: 15.4 and, of four channels, 20 us where single
+// windows then took 14.4 and 17.3.
 template <int C, bool NARROW>
 struct MetShape {
     static constexpr int kThreads = NARROW ? 64 : 256;
