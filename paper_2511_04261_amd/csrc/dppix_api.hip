@@ -50,6 +50,7 @@ struct LaunchGroup {
     int layout, C;
     int threads;          // workgroup size chosen for the group's tiles
     int rec_threads;      // the same for their reconstruction
+    bool paced;           // reconstruction with paced stores: every frame's tiles ask for it
     int64_t lo, hi;       // scheduling-index range
     size_t lds_fwd, lds_rec;
 };
@@ -266,6 +267,13 @@ int rec_threads(const FrameRec& F, int64_t tiles)
     if (tiles < kFewTiles || stores < 1536)
         return base;
     return tiles >= 2048 && stores >= 3072 ? 512 : kDefaultThreads;
+}
+
+// Whether a frame's reconstruction tiles pace their stores (the sides of the
+// line: k_reconstruct_u8's PACED).
+bool rec_paced(const FrameRec& F)
+{
+    return F.layout == DPPIX_U8_HWC && F.C == 3 && F.n == 2 && (F.s == 5 || F.s == 6);
 }
 
 // Plan units of the batch.  Fewer than two a compute unit (kPlanUnits) leave
@@ -553,10 +561,11 @@ dppix_status_t dp_pix_plan_create(const dppix_frame_desc_t* descs, int32_t n_fra
         const int th = tile_threads(F, tile);
         if (p->groups.empty() || p->groups.back().layout != F.layout || p->groups.back().C != F.C ||
             p->groups.back().threads != th)
-            p->groups.push_back(LaunchGroup{F.layout, F.C, th, 0, p->sched_base[k], p->sched_base[k], 0, 0});
+            p->groups.push_back(LaunchGroup{F.layout, F.C, th, 0, true, p->sched_base[k], p->sched_base[k], 0, 0});
         LaunchGroup& g = p->groups.back();
         g.hi = p->sched_base[k + 1];
         g.rec_threads = std::max(g.rec_threads, rec_threads(F, tile));
+        g.paced = g.paced && rec_paced(F);
         g.lds_fwd = std::max(g.lds_fwd, frame_lds(kind_fwd(F), F));
         g.lds_rec = std::max(g.lds_rec, frame_lds(kind_rec(F), F));
     }
@@ -1041,7 +1050,7 @@ dppix_status_t dp_pix_reconstruct(dppix_plan_t p, const dppix_store_t* store, vo
     a.outs = out;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e = for_groups(p, a, true, [&](const TileArgs& ga, const LaunchGroup& g, size_t lds, int grid) {
-        return launch_reconstruct(ga, g.layout, g.C, group_threads(p, g, true), lds, grid, s);
+        return launch_reconstruct(ga, g.layout, g.C, g.paced, group_threads(p, g, true), lds, grid, s);
     });
     if (e != hipSuccess)
         return dev_fail(e, "reconstruct launch");

@@ -336,7 +336,8 @@ hipError_t launch_plan_labels(const TileArgs& a, int C, int64_t n_units, int thr
 // Tile counts of complex cells from the store's flags alone, then the scan.
 hipError_t launch_store_index(const TileArgs& a, bool prefix_scan, hipStream_t s);
 hipError_t launch_forward(const TileArgs& a, int layout, int C, int threads, size_t lds, int grid, hipStream_t s);
-hipError_t launch_reconstruct(const TileArgs& a, int layout, int C, int threads, size_t lds, int grid,
+// paced: RGB frames whose tiles write faster than the memory takes it (k_reconstruct_u8).
+hipError_t launch_reconstruct(const TileArgs& a, int layout, int C, bool paced, int threads, size_t lds, int grid,
                               hipStream_t s);
 hipError_t launch_backward_reduce(const TileArgs& a, int threads, size_t lds, int grid, hipStream_t s);
 hipError_t launch_backward_mirror(const TileArgs& a, int64_t n_units, int threads, hipStream_t s);

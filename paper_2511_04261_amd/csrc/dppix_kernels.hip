@@ -2109,7 +2109,16 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(5))
 // ==========================================================================
 // Reconstruction from the compact store (Sec. VI-F).
 // ==========================================================================
-template <int C>
+// PACED: a wave has at most four row stores on their way, and none when it
+// expands the next subgrid row.  Where two subgrid rows of five or six pixel
+// rows make a tile, waves otherwise issue stores faster than the memory takes
+// them, and the L2's write queues back up: 300 x 576 x 768 RGB, b 12 / s_b 6:
+// 1.41 M stall cycles (TCC_EA0_WRREQ_STALL) and 77.5 us, paced 69.4; with the
+// slower divisions that the expansion had once, 0.10 M and 72.4; b 10 / s_b 5: 99
+// and 88.4.  64 frames: 21.2 / 20.6 and 24.4 / 23.6; 64 x 1080p, b 10 / s_b 5:
+// 82.0 / 80.4; up to 16 frames 2 % slower.  Other grids gain nothing (n 2, s_b 8 and 9:
+// -1 %, s_b 4: +2 %; n 4, s_b 6 and 8: +2 and +4 %).
+template <int C, bool PACED>
 __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const TileCoord& tc, uint8_t* lds)
 {
     const int tid = threadIdx.x, NT = blockDim.x;
@@ -2177,8 +2186,11 @@ __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const 
                 const v4u v = lds16(exb + po);
                 if (F.off32) {
                     const uint32_t off = (uint32_t)(fr * s) * upitch + (uint32_t)po;
-                    for (int k = k0; k < k1; ++k)
+                    for (int k = k0; k < k1; ++k) {
                         st16_nt(band_out + (off + (uint32_t)k * upitch), v);
+                        if constexpr (PACED)
+                            asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+                    }
                 } else {
                     for (int k = k0; k < k1; ++k)
                         st16_nt(out + (int64_t)(row0 + k) * pitch + X0 + po, v);
@@ -2191,6 +2203,8 @@ __device__ void reconstruct_tile_u8(const TileArgs& a, const FrameRec& F, const 
                 }
             }
         }
+        if constexpr (PACED)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
 }
 
@@ -2231,11 +2245,11 @@ __device__ void reconstruct_tile_f32(const TileArgs& a, const FrameRec& F, const
     broadcast_tile_f32(F, r, X0, real, Kt, cflag, vgs, vgc, static_cast<float*>(a.outs[tc.f]));
 }
 
-template <int C>
+template <int C, bool PACED = false>
 __global__ __launch_bounds__(kMaxThreads) void k_reconstruct_u8(TileArgs a)
 {
     extern __shared__ __align__(16) uint8_t lds[];
-    run_tiles(a, lds, [&](const FrameRec& F, const TileCoord& tc) { reconstruct_tile_u8<C>(a, F, tc, lds); });
+    run_tiles(a, lds, [&](const FrameRec& F, const TileCoord& tc) { reconstruct_tile_u8<C, PACED>(a, F, tc, lds); });
 }
 
 __global__ __launch_bounds__(kMaxThreads) void k_reconstruct_f32(TileArgs a)
@@ -3081,10 +3095,13 @@ hipError_t launch_forward(const TileArgs& a, int layout, int C, int threads, siz
     }
 }
 
-hipError_t launch_reconstruct(const TileArgs& a, int layout, int C, int threads, size_t lds, int grid, hipStream_t s)
+hipError_t launch_reconstruct(const TileArgs& a, int layout, int C, bool paced, int threads, size_t lds, int grid,
+                              hipStream_t s)
 {
     if (layout == 1)
         return launch_tiles(k_reconstruct_f32, a, threads, lds, grid, s);
+    if (paced && C == 3)
+        return launch_tiles(k_reconstruct_u8<3, true>, a, threads, lds, grid, s);
     switch (C) {
     case 1: return launch_tiles(k_reconstruct_u8<1>, a, threads, lds, grid, s);
     case 2: return launch_tiles(k_reconstruct_u8<2>, a, threads, lds, grid, s);

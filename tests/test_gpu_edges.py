@@ -296,3 +296,37 @@ def test_store_offsets_of_any_batch(batch, dev):
         bg += nb * f.channels
         fg += nf * n2 * f.channels
         assert torch.equal(fused[i], rebuilt[i]), i
+
+
+@pytest.mark.parametrize("b", [10, 12])
+@pytest.mark.parametrize("persistent", [0, 1])
+def test_paced_reconstruction_gives_equal_bytes(dev, b, persistent):
+    """Batches whose reconstruction paces its stores (RGB, two subgrid rows of
+    five or six), of whole and ragged tiles and rows at any byte: the bytes of
+    the fused forward, and of a batch in which another frame keeps the group
+    from pacing."""
+    say("case: paced reconstruction", b, persistent)
+    r = np.random.Generator(np.random.PCG64(b))
+    shapes = [(60, 768), (61, 767), (b, 5 * b), (7, 30), (b + 1, 400), (3, 3)]
+    fps = [dp.FrameParams(h, w, 3, dp.U8_HWC, b=b, sb=b // 2, m=8, tau=1, seed=2, frame_index=i, pitch=3 * w + i % 3)
+           for i, (h, w) in enumerate(shapes)]
+    other = dp.FrameParams(50, 300, 3, dp.U8_HWC, b=16, sb=4, m=8, tau=1, seed=2, frame_index=99, pitch=900)
+    xs = [r.integers(0, 256, (f.height, f.width, 3)).astype(np.uint8) for f in fps + [other]]
+    ms = [torch.from_numpy((r.random((f.height, f.width)) < 0.02).astype(np.uint8)).to(dev) for f in fps + [other]]
+    got = []
+    for frames in (fps, fps + [other]):
+        ins, fused, rebuilt = ([_strided(f, dev, 1, fill) for f in frames] for fill in (0, 77, 77))
+        for (_, v), x in zip(ins, xs):
+            v.copy_(torch.from_numpy(x).to(dev))
+        plan = dp.Plan(frames, device=dev, persistent=persistent)
+        plan.plan(ms[:len(frames)])
+        plan.forward([v for _, v in ins], out=[v for _, v in fused])
+        plan.reconstruct([v for _, v in rebuilt])
+        torch.cuda.synchronize()
+        for i in range(len(frames)):
+            assert torch.equal(fused[i][0], rebuilt[i][0]), i
+            assert _untouched(rebuilt[i][0], rebuilt[i][1], 77), i
+        got.append([buf for buf, _ in rebuilt])
+        plan.close()
+    for i in range(len(fps)):
+        assert torch.equal(got[0][i], got[1][i]), i
